@@ -32,7 +32,7 @@ KERNEL_SOURCES = ("encode.hip", "h4d_device.h", "h4d_internal.h", "mlp.hip")
 # the library kernels behind each timed part of the step
 STEP_KERNELS = {"cast": ["k_cast_bf16"], "encode": ["k_encode"], "decode": ["k_mlp_forward"],
                 "decode_bwd": ["k_mlp_backward", "k_mlp_reduce"],
-                "scatter": ["k_tile_mask", "k_tile_plan", "k_scatter_tiled", "k_tile_combine"]}
+                "scatter": ["k_tile_pre", "k_scatter_tiled"]}
 TRAFFIC_FILE = os.path.join("profiles", "traffic_deform_paper_scene_fp32.md")
 
 
@@ -292,29 +292,16 @@ def probe_sweep(torch, _lib, E, n_loads, reps=5):
     return out
 
 
-def scatter_tile_count(rows_per_level, F=2, gbytes=4):
-    """Tiles of the table scatter: per level about 32 tiles of a power of two of rows,
-    at least 256 rows and at most 128 KiB of gradient."""
-    max_rows = (128 * 1024) // (F * gbytes)
-    tiles = 0
-    for r in rows_per_level:
-        want = -(-r // 32)
-        sh = 8
-        while (1 << sh) < max_rows and (1 << sh) < want:
-            sh += 1
-        tiles += -(-r // (1 << sh))
-    return tiles
-
-
 def achievable(torch, _lib, synth, per, pr, n):
     """Each kernel's time against the probe ceiling that matches its access pattern
     (each fraction at most 1 when the kernel runs at that ceiling):
     encode: its corner-row requests (one per x-pair whose rows are an aligned pair,
     two otherwise, counted from the corner rows) at the random-gather request rate of
     a 4 MiB, L2-resident footprint (the level slice each XCD holds);
-    scatter: the owner-computes floor, the larger of the time to stream every tile's
-    level of query masks at the copy rate and the time for the corner updates at the
-    LDS compare-and-swap rate (the queries' own loads taken as free)."""
+    scatter: the larger of the time to write and read the sorted corner pairs (2 bytes
+    for each of the 8 pairs of a query and level) at the copy rate and the time for the
+    corner updates at the LDS compare-and-swap rate (the queries' own loads taken as
+    free)."""
     w = synth.PAPER_SCENE
     g = _lib.h4d_grid_init(w.L, w.F, _lib.h4d_grid_schedule(w.L, *w.space), _lib.h4d_grid_schedule(w.L, *w.time),
                            w.T)
@@ -326,16 +313,14 @@ def achievable(torch, _lib, synth, per, pr, n):
     requests = int(n * w.L * 8 + (~paired).sum().item())
     del rows, r0, r1, paired
     t_enc = requests / (pr["gather8_4MiB_Gloads_per_s"] * 1e9)
-    level_rows = [g.offsets()[l + 1] - g.offsets()[l] for l in range(w.L)]
-    tiles = scatter_tile_count(level_rows)
-    mask_stream = tiles * n * 4                        # every tile scans its level's masks
-    t_scan = mask_stream / (pr["copy_GBps"] * 1e9)
+    pair_stream = 2 * n * w.L * 8 * 2                  # sorted pairs written and read
+    t_scan = pair_stream / (pr["copy_GBps"] * 1e9)
     t_lds = n * w.L * 16 / (pr["lds_cas_G_per_s"] * 1e9)
     t_sca = max(t_scan, t_lds)
     enc_ms, sca_ms = per["encode"], per["scatter"]
     return {"encode": {"requests": requests, "probe": "gather8_4MiB_Gloads_per_s", "floor_ms": t_enc * 1e3,
                        "ms": enc_ms, "frac": t_enc * 1e3 / enc_ms},
-            "scatter": {"tiles": tiles, "mask_stream_bytes": mask_stream, "scan_floor_ms": t_scan * 1e3,
+            "scatter": {"pair_stream_bytes": pair_stream, "stream_floor_ms": t_scan * 1e3,
                         "lds_floor_ms": t_lds * 1e3, "floor_ms": t_sca * 1e3, "ms": sca_ms,
                         "frac": t_sca * 1e3 / sca_ms}}
 
@@ -541,7 +526,7 @@ def smoothness_form(torch, _lib, synth, path, steps: int):
         torch.cuda.synchronize()
         step_ms["one_scatter" if merged else "separate"] = a.elapsed_time(b) / steps
     return {"ms": ms, "value": n / (ms / 1e3), "unit": "queries/s", "lambda": 1.0, "sigma": 1e-3,
-            "kernels": ["k_smooth", "k_tile_mask", "k_tile_plan", "k_scatter_tiled", "k_tile_combine"],
+            "kernels": ["k_smooth", "k_tile_pre", "k_scatter_tiled"],
             "training_step_ms": step_ms, "training_step_value": n / (step_ms["one_scatter"] / 1e3)}
 
 

@@ -171,13 +171,10 @@ h4d_status hash3d_encode(const h4d_grid3* g, h4d_dtype table_dt, const void* tab
  *           in layout, which writes every row, zeros where no corner lands)
  * Owner-computes scatter: one workgroup per (level, tile of consecutive table rows)
  * sums its rows' updates in LDS and adds them to d_table; no device-wide atomics.
- * A pre-pass writes a per-(query, level) mask of touched tiles (and, on hashed
- * levels, each x-pair's tile) into `workspace` (device, 16-byte aligned, at least
- * hash4d_encode_backward_workspace_bytes) so that each tile only works on the
- * queries that reach it; it also counts the queries per tile of the dense levels,
- * and a tile that many queries reach is split over several workgroups whose partial
- * tiles the workspace holds.  The LDS adds (one FP32 rounding each) make the
- * summation order, hence the last bits, vary run to run. */
+ * A pre-pass sorts the corner pairs of every (query, level) by tile into `workspace`
+ * (device, 16-byte aligned, at least hash4d_encode_backward_workspace_bytes) so that each
+ * tile only works on the updates that reach it.  The LDS adds (one FP32 rounding each)
+ * make the summation order, hence the last bits, vary run to run. */
 size_t hash4d_encode_backward_workspace_bytes(const h4d_grid* g, int64_t n);
 h4d_status hash4d_encode_backward(const h4d_grid* g, h4d_dtype grad_dt, const float* xyzt, int64_t n,
                                   h4d_layout layout, const void* d_feat, float grad_scale, void* d_table,
@@ -195,8 +192,8 @@ h4d_status hash4d_encode_backward_checked(const h4d_grid* g, h4d_dtype grad_dt, 
 /* hash4d_encode_backward without a workspace argument and without any device
  * allocation, for callers that cannot allocate: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments (minus
- * workspace / ws_bytes), kernels and results as hash4d_encode_backward.  The tile
- * masks go to a static workspace of 64 MiB (67108864 bytes) per GPU, a file-scope
+ * workspace / ws_bytes), kernels and results as hash4d_encode_backward.  The sorted
+ * pairs go to a static workspace of 64 MiB (67108864 bytes) per GPU, a file-scope
  * device array that each GPU holds from the library's load until the process ends;
  * a call whose hash4d_encode_backward_workspace_bytes(g, n) exceeds it returns
  * H4D_EINVAL and launches nothing.  No call reads what an earlier call left there.
@@ -250,7 +247,7 @@ h4d_status hash4d_deform_apply(const float* delta, int64_t n, int32_t out, const
  *   d_table += (2 lambda / n) (d w at x's corners - d w~ at x~'s corners)
  * Both encodes are recomputed per query and level, nothing is kept between calls.
  * d_table may be NULL (loss only, no workspace needed).  Otherwise `workspace`
- * (device, smoothness_workspace_bytes) receives d and the scatter's tile masks, and
+ * (device, smoothness_workspace_bytes) receives d and the scatter's sorted pairs, and
  * the gradient is added by the tiled scatter.  table_dt as hash4d_encode; loss and d_table are FP32 (FP64
  * for F64).  eps: FP32 [n, 4], 16-byte aligned. */
 size_t smoothness_workspace_bytes(const h4d_grid* g, h4d_dtype table_dt, int64_t n);
@@ -393,7 +390,7 @@ h4d_status deform_mlp_backward_checked(const h4d_mlp* m, h4d_dtype dt, const voi
 /* -------------------------------------------------- deformation path ---- */
 
 /* Workspace of hash4d_deform_backward: decoder partials, the [L, n, F] feature
- * gradient and the scatter's tile masks.  0 if the arguments are invalid. */
+ * gradient and the scatter's sorted pairs.  0 if the arguments are invalid. */
 size_t hash4d_deform_workspace_bytes(const h4d_grid* g, const h4d_mlp* m, h4d_dtype dt, int64_t n);
 
 /* Whole forward of the deformation field for n dynamic Gaussians at their

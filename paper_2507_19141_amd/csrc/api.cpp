@@ -165,13 +165,13 @@ static h4d_status check_mlp(const h4d_mlp* m, h4d_dtype dt) {
 }
 
 // Workspace of the tiled scatter for grid g and n queries.
-static size_t scatter_ws(const h4d_grid* g, int64_t n) {
+static size_t scatter_ws(const h4d_grid* g, int64_t n, bool pair = false) {
     int64_t rows[H4D_MAX_LEVELS];
     rows_of(*g, rows);
-    return scatter_ws_bytes(to_device(*g), rows, (int)n);
+    return scatter_ws_bytes(to_device(*g), rows, (int)n, pair);
 }
 
-// Deformation backward workspace: [decoder partials | d_feat [L, n, F] | tile masks].
+// Deformation backward workspace: [decoder partials | d_feat [L, n, F] | pair lists].
 static size_t deform_ws(const h4d_grid* g, const h4d_mlp* m, h4d_dtype dt, int64_t n) {
     const size_t el = dt == H4D_F64 ? sizeof(double) : sizeof(float);
     const size_t a = (mlp_workspace_bytes(dt, m->in, m->out, (int)n) + 255) / 256 * 256;
@@ -352,7 +352,7 @@ size_t hash4d_encode_backward_workspace_bytes(const h4d_grid* g, int64_t n) {
 }
 
 // Validation and launch shared by hash4d_encode_backward and its static-workspace
-// form.  static_ws: the masks go to the library's static array (static_scratch)
+// form.  static_ws: the pair lists go to the library's static array (static_scratch)
 // instead of `workspace`.
 static h4d_status encode_backward_call(const h4d_grid* g, h4d_dtype grad_dt, const float* xyzt, int64_t n,
                                        h4d_layout layout, const void* d_feat, float grad_scale, void* d_table,
@@ -462,10 +462,10 @@ h4d_status hash4d_corner_indices(const h4d_grid* g, const float* xyzt, int64_t n
     return hip_status(launch_corner_indices(d, xyzt, (int)n, rows, w, (hipStream_t)stream), "hash4d_corner_indices");
 }
 
-// Smoothness workspace: [d = G(x) - G(x + eps), level-major | tile masks].
+// Smoothness workspace: [d = G(x) - G(x + eps), level-major | pair lists].
 static size_t smooth_ws(const h4d_grid* g, h4d_dtype table_dt, int64_t n) {
     const size_t d = ((size_t)n * g->L * g->F * (table_dt == H4D_F64 ? sizeof(double) : sizeof(float)) + 255) / 256 * 256;
-    return d + scatter_ws(g, n);
+    return d + scatter_ws(g, n, true);
 }
 
 size_t smoothness_workspace_bytes(const h4d_grid* g, h4d_dtype table_dt, int64_t n) {
@@ -837,7 +837,7 @@ h4d_status hash4d_deform_backward(const h4d_grid* g, const h4d_mlp* m, h4d_dtype
     const size_t el = dt == H4D_F64 ? sizeof(double) : sizeof(float);
     const size_t part = (mlp_workspace_bytes(dt, m->in, m->out, (int)n) + 255) / 256 * 256;
     void* d_feat = ws + part;
-    void* masks = ws + part + ((size_t)n * g->L * g->F * el + 255) / 256 * 256;
+    void* lists = ws + part + ((size_t)n * g->L * g->F * el + 255) / 256 * 256;
     // decoder backward: d_feat keeps the loss scale, d_params gets grad_scale
     if ((st = hip_status(launch_mlp_backward(dt, m->in, m->out, params, feat, g->F, ls, qs, (int)n, d_delta,
                                              loss_scale, 1.0, grad_scale, d_feat, ls, qs, d_params, ws, s),
@@ -846,7 +846,7 @@ h4d_status hash4d_deform_backward(const h4d_grid* g, const h4d_mlp* m, h4d_dtype
     int64_t rows[H4D_MAX_LEVELS];
     rows_of(*g, rows);
     return hip_status(launch_scatter_tiled(d, rows, dt == H4D_F64 ? H4D_F64 : H4D_F32, xyzt, nullptr, (int)n, d_feat,
-                                           ls, qs, grad_scale, d_table, masks, s),
+                                           ls, qs, grad_scale, d_table, lists, s),
                       "hash4d_deform_backward/encode");
 }
 

@@ -585,7 +585,7 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
             const h4d_scene_desc& d = scenes[sc];
             int64_t lrows[H4D_MAX_LEVELS];
             for (int l = 0; l < d.grid.L; ++l) lrows[l] = d.grid.offset[l + 1] - d.grid.offset[l];
-            const TileMap tm = make_tile_map(p->grids_h[sc], lrows, d.grid.F, (int)sizeof(float));
+            const TileMap tm = make_tile_map(p->grids_h[sc], lrows, d.grid.F, (int)sizeof(float), (int)d.n, d.n_times, false, 0);
             tms.push_back(tm);
             for (int l = 0; l < d.grid.L; ++l) {
                 const int P = tm.tile_start[l + 1] - tm.tile_start[l];

@@ -313,16 +313,23 @@ __device__ __forceinline__ void lds_add2_two(float* p, float a0, float a1, float
     if (rv != sv) lds_add2_retry(q, b0, b1, rv);
 }
 
-// Add F values to one tile row.
+// Add F values (times w) to one tile row.
 template <typename G, int F>
-__device__ __forceinline__ void lds_add_row(G* p, const G (&v)[F], G w) {
+__device__ __forceinline__ void lds_add_values(G* p, const G (&v)[F]) {
     if constexpr (sizeof(G) == 4 && F % 2 == 0) {
 #pragma unroll
-        for (int f = 0; f < F; f += 2) lds_add2(p + f, w * v[f], w * v[f + 1]);
+        for (int f = 0; f < F; f += 2) lds_add2(p + f, v[f], v[f + 1]);
     } else {
 #pragma unroll
-        for (int f = 0; f < F; ++f) lds_add(p + f, w * v[f]);
+        for (int f = 0; f < F; ++f) lds_add(p + f, v[f]);
     }
+}
+template <typename G, int F>
+__device__ __forceinline__ void lds_add_row(G* p, const G (&v)[F], G w) {
+    G t[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) t[f] = w * v[f];
+    lds_add_values<G, F>(p, t);
 }
 
 // Add w_c gv at the corners of x that fall in table rows [base, base + cnt) to an
@@ -422,60 +429,6 @@ __device__ __forceinline__ uint32_t corner_tile_mask(const DevGrid& g, const Til
     return m;
 }
 
-// ---- per-pair tile bytes (levels whose x-pairs share a tile, tm.pair_words) ----
-// On such a level the tile of pair p = (dy, dz, dt) (bits 0, 1, 2 of p) depends only
-// on the y, z and t terms of Eq. 8: the x term is below the tile's row bits.  The
-// mask pass stores each pair's tile index (at most 255) in byte p of a 64-bit word
-// (pairs 0-3 in .x, 4-7 in .y), so that a tile workgroup finds a query's pairs in
-// its tile without hashing them again.
-__device__ __forceinline__ uint2 pair_tile_bytes(const DevGrid& g, const TileMap& tm, int l, const Cell& c) {
-    const uint32_t hy0 = (uint32_t)c.iy * g.prime[1], hy1 = hy0 + g.prime[1];
-    const uint32_t hz0 = (uint32_t)c.iz * g.prime[2], hz1 = hz0 + g.prime[2];
-    const uint32_t ht0 = (uint32_t)c.it * g.prime[3], ht1 = ht0 + g.prime[3];
-    const uint32_t sh = (uint32_t)tm.tile_shift[l];
-    uint32_t b[8];
-#pragma unroll
-    for (int p = 0; p < 8; ++p)
-        b[p] = ((((p & 1) ? hy1 : hy0) ^ ((p & 2) ? hz1 : hz0) ^ ((p & 4) ? ht1 : ht0)) & g.tmask) >> sh;
-    return make_uint2(b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24), b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24));
-}
-
-// Bit p set iff byte p of wd equals tau (tau < 256): the query's pairs in tile tau.
-__device__ __forceinline__ uint32_t pair_hits(uint2 wd, uint32_t tau) {
-    const uint32_t rep = tau * 0x01010101u;
-    const uint32_t lo = wd.x ^ rep, hi = wd.y ^ rep;
-    // exact zero-byte test: bit 7 of a byte ends up set iff the byte is zero
-    const uint32_t zl = ~(((lo & 0x7f7f7f7fu) + 0x7f7f7f7fu) | lo) & 0x80808080u;
-    const uint32_t zh = ~(((hi & 0x7f7f7f7fu) + 0x7f7f7f7fu) | hi) & 0x80808080u;
-    // gather bits 7, 15, 23, 31 into bits 24..27 (the partial products cannot carry there)
-    return (((zl >> 7) * 0x01020408u) >> 24) | ((((zh >> 7) * 0x01020408u) >> 24) << 4);
-}
-
-// Add w_c gv at both corners of x-pair p of x (same y, z, t; lower and upper x) on a
-// level whose pairs share a tile; rmask = tile rows - 1 (tiles are aligned powers of
-// two, so a row's place in its tile is its low bits).
-template <typename G, int F>
-__device__ __forceinline__ void pair_contrib(const DevGrid& g, int l, float4 x, int p, const G (&gv)[F], uint32_t rmask,
-                                             G* tile) {
-    const Cell c = level_cell(g, l, x);
-    const uint32_t dy = (uint32_t)p & 1u, dz = ((uint32_t)p >> 1) & 1u, dt = ((uint32_t)p >> 2) & 1u;
-    const uint32_t H = (((uint32_t)c.iy + dy) * g.prime[1]) ^ (((uint32_t)c.iz + dz) * g.prime[2]) ^
-                       (((uint32_t)c.it + dt) * g.prime[3]);
-    const uint32_t r0 = ((uint32_t)c.ix ^ H) & rmask;  // pi_1 = 1
-    const uint32_t r1 = (((uint32_t)c.ix + 1u) ^ H) & rmask;
-    const G wy = dy ? G(c.fy) : G(1) - G(c.fy);
-    const G wz = dz ? G(c.fz) : G(1) - G(c.fz);
-    const G wt = dt ? G(c.ft) : G(1) - G(c.ft);
-    const G w = (wy * wz) * wt;
-    const G w0 = (G(1) - G(c.fx)) * w, w1 = G(c.fx) * w;
-    if constexpr (sizeof(G) == 4 && F == 2) {
-        lds_add2_two(tile + r0 * 2, w0 * gv[0], w0 * gv[1], tile + r1 * 2, w1 * gv[0], w1 * gv[1]);
-    } else {
-        lds_add_row<G, F>(tile + r0 * F, gv, w0);
-        lds_add_row<G, F>(tile + r1 * F, gv, w1);
-    }
-}
-
 // Orders one wavefront's LDS queue writes before its reads by other lanes.
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -539,67 +492,6 @@ __device__ __forceinline__ void masked_queue_loop(int n, const uint32_t* __restr
     if (tail) last = load(queue[lane]);
     if (have) run(pend);
     if (tail) run(last);
-}
-
-// As masked_queue_loop, but run(s, active) is always called by the whole wavefront
-// (active is false for the lanes of a partial last batch), so that run may use
-// wavefront-wide operations.  Each step loads kScanLoads 16-byte groups of masks per
-// lane (1024 queries per wavefront) with their loads issued together, so a step waits
-// for its masks once; the batch loads issued while scanning are then waited for only
-// by the run of that batch, one batch later.
-constexpr int kScanLoads = 4;
-template <int BLOCK, typename Load, typename Run>
-__device__ __forceinline__ void masked_queue_loop_wave(int n, const uint32_t* __restrict__ lmask, uint32_t bit,
-                                                       int* wqueue, Load load, Run run) {
-    static_assert(BLOCK % 64 == 0, "whole wavefronts");
-    using S = decltype(load(0));
-    constexpr int kWaves = BLOCK / 64;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    int* queue = wqueue + wave * 128;
-    const uint4* __restrict__ m4 = reinterpret_cast<const uint4*>(lmask);
-    const int groups = (n + 3) >> 2;
-    int qn = 0;
-    bool have = false;  // a loaded batch waits in `pend` (wave-uniform)
-    S pend{};
-    for (int g0 = wave * 64 * kScanLoads; g0 < groups; g0 += kWaves * 64 * kScanLoads) {
-        uint4 m[kScanLoads];
-#pragma unroll
-        for (int k = 0; k < kScanLoads; ++k) {
-            const int gi = g0 + k * 64 + lane;
-            m[k] = gi < groups ? m4[gi] : make_uint4(0u, 0u, 0u, 0u);
-        }
-#pragma unroll
-        for (int k = 0; k < kScanLoads; ++k) {
-            const uint32_t mm[4] = {m[k].x, m[k].y, m[k].z, m[k].w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int q = 4 * (g0 + k * 64 + lane) + j;
-                const bool hit = (mm[j] & bit) != 0u && q < n;
-                const uint64_t bal = __ballot(hit);
-                if (hit) queue[qn + lane_rank(bal)] = q;
-                qn += (int)__popcll(bal);
-                wave_sync();
-                if (qn >= 64) {
-                    const S fresh = load(queue[lane]);
-                    const int rest = qn - 64;
-                    const int moved = lane < rest ? queue[64 + lane] : 0;
-                    wave_sync();
-                    if (lane < rest) queue[lane] = moved;
-                    wave_sync();
-                    qn = rest;
-                    if (have) run(pend, true);
-                    pend = fresh;
-                    have = true;
-                }
-            }
-        }
-    }
-    const bool tail = lane < qn;
-    S last{};
-    if (tail) last = load(queue[lane]);
-    if (have) run(pend, true);
-    if (qn > 0) run(last, tail);
 }
 
 }  // namespace h4d

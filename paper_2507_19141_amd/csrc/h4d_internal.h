@@ -72,19 +72,31 @@ struct TileMap {
     // (hashed, T a power of two of at least one tile, pi_1 = 1 and 2 N_s <= tile
     // rows: the pair's hashes differ only in bits below log2(2 N_s)).
     uint32_t pair_cotiled;
-    // Bit l set: the mask pass also stores, per (query, level), the tile of each of
-    // the eight x-pairs (one byte each), and the scatter visits a query's pairs in
-    // its tile from those bytes.  Levels with pair_cotiled and at most 256 tiles,
-    // when make_tile_map is asked for them.
-    uint32_t pair_words;
+    // Bit l set: the level's updates reach its tiles through pair lists (pair_lists.h),
+    // else through tile masks.  loose: its pairs may straddle two tiles.  On a dense list
+    // level tile_shift is the log2 of its tiles.  list_region / list_head: the level's
+    // first region of entries and first head.
+    uint32_t lists, loose;
+    int32_t list_region[H4D_MAX_LEVELS + 1];
+    int64_t list_head[H4D_MAX_LEVELS + 1];
 };
-TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gbytes, bool pair_words = false);
-// The scatter's tile masks: one 32-bit mask per (query, level), level-major with the
-// query count padded to a multiple of four so that every level starts on a 16-byte
-// boundary (the scan reads four masks per load); the per-pair tile bytes follow, 8
-// bytes per (query, level) in the same order, then the load-balance plan.
+// Pair lists: entries of one region, tiles of a list level at most, and the log2 of the
+// queries of a chunk, whose 8 pairs have up to one entry per corner set (pair: two) and
+// tile (loose: two).
+constexpr int kListEntries = 16384;
+constexpr int kListTiles = 256;
+constexpr int list_chunk_log(bool pair, bool loose) { return 11 - (pair ? 1 : 0) - (loose ? 1 : 0); }
+constexpr int kMaskChunkLog = 11, kMaskChunk = 1 << kMaskChunkLog;
+// Tiles and lists for `segs` runs of n queries each (pair: two corner sets per query).  At
+// most list_levels levels get lists, dense levels first.
+TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gbytes, int n, int segs, bool pair,
+                      int list_levels);
+// The scatter's tile masks: one 32-bit mask per (query, level) of the levels without
+// lists, level-major with the query count padded to a multiple of four so that every
+// level starts on a 16-byte boundary (the scan reads four masks per load).
 constexpr int64_t mask_stride(int64_t n) { return (n + 3) & ~(int64_t)3; }
-size_t scatter_ws_bytes(const DevGrid& g, const int64_t* level_rows, int n);
+// Workspace for n queries; pair: of the form with eps (two corner sets per query).
+size_t scatter_ws_bytes(const DevGrid& g, const int64_t* level_rows, int n, bool pair);
 // A second feature gradient for the pair form (eps set): added, times scale, at x's
 // corners only.  src == nullptr: none.
 struct MainGradArg {

@@ -1,0 +1,156 @@
+"""The table scatter's pair lists (pair_lists.h): every kind of list level (tight and loose
+hashed tiles, modulo hashing, dense levels dealt line by line), levels with too many tiles
+for lists (masks), chunk and batch boundaries, one and two corner sets, against the
+oracle; and, on the CPU, the rule that keeps every call that fits the static workspace
+within it."""
+import numpy as np
+import pytest
+
+from oracle import hash4d_oracle as O
+from paper_2507_19141_amd import _lib, synth
+from tests.util import RTOL_GRAD, needs_gpu, scaled_close
+
+# name: (F, space resolutions, time resolutions, T)
+GRIDS = {
+    "tight": (2, [40, 128], [8, 30], 1 << 14),
+    "loose": (2, [300, 2048], [9, 20], 1 << 12),          # 2 N_s above the 256 rows of a tile
+    "loose_f1": (1, [2047], [3], 1 << 11),
+    "modulo": (2, [16, 33], [5, 9], 5003),                # T no power of two
+    "dense": (2, [1, 3, 7], [1, 2, 5], 1 << 13),          # 8 .. 384 lines
+    "dense_32": (4, [31], [3], 1 << 17),                  # lines a multiple of 32 long
+    "mixed": (8, [3, 31, 600], [4, 7, 11], 1 << 13),
+    "masks": (8, [512], [40], 1 << 21),                   # 512 tiles: no lists
+}
+
+
+def _inputs(n, seed, crowded):
+    rng = np.random.default_rng(seed)
+    x = synth.uniform_xyzt(n, rng)
+    if crowded:  # every query in a few cells, one timestamp
+        x = (0.5 + 0.01 * (x - 0.5)).astype(np.float32)
+        x[:, 3] = np.float32(0.25)
+    edges = np.array([[0, 0, 0, 0], [1, 1, 1, 1], [np.nan, 0.5, 2.0, -1.0], [0.25, 0.5, 0.75, 1.0]], np.float32)
+    x[: min(n, 4)] = edges[: min(n, 4)]
+    return rng, x
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", [_lib.F32, _lib.F64], ids=["f32", "f64"])
+@pytest.mark.parametrize("name", GRIDS)
+@pytest.mark.parametrize("n,crowded", [(1, False), (513, False), (2048, True), (4097, False)])
+def test_scatter_every_list_kind(name, dt, n, crowded):
+    needs_gpu()
+    import torch
+    F, rs, rt, T = GRIDS[name]
+    L = len(rs)
+    og = O.make_grid(L, F, rs, rt, T)
+    lg = _lib.h4d_grid_init(L, F, rs, rt, T)
+    rng, x = _inputs(n, 7 * n + len(name), crowded)
+    gf = synth.upstream(n, L * F, rng)
+    real = np.float64 if dt == _lib.F64 else np.float32
+    wb = _lib.hash4d_encode_backward_workspace_bytes(lg, n)
+    ws = torch.full((wb,), 0xA5, dtype=torch.uint8, device="cuda")   # nothing is read before it is written
+    d_table = torch.full((og.E, F), float("nan"), dtype=torch.float64 if dt == _lib.F64 else torch.float32,
+                         device="cuda")
+    _lib.hash4d_encode_backward(lg, dt, _dev(x), n, _dev(gf.astype(real)), 0.5, d_table, ws, wb,
+                                _lib.QUERY_MAJOR | _lib.GRAD_OVERWRITE)
+    torch.cuda.synchronize()
+    scaled_close(d_table.cpu().numpy(), O.encode_backward(x, gf, og, 0.5), O.encode_backward(x, np.abs(gf), og, 0.5),
+                 1e-12 if dt == _lib.F64 else RTOL_GRAD, f"{name} n={n}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", ["tight", "loose", "modulo", "dense", "mixed", "masks"])
+@pytest.mark.parametrize("n,sigma", [(1, 1e-3), (1025, 1e-4), (2049, 5e-2)])
+def test_two_corner_sets(name, n, sigma):
+    # x and x + eps in one cell (one entry for both) and apart (one entry each)
+    needs_gpu()
+    import torch
+    F, rs, rt, T = GRIDS[name]
+    L = len(rs)
+    og = O.make_grid(L, F, rs, rt, T)
+    lg = _lib.h4d_grid_init(L, F, rs, rt, T)
+    rng, x = _inputs(n, n + len(name), False)
+    table = synth.table_init(og.E, F, rng)
+    eps = synth.perturbation(n, rng, sigma)
+    gf = synth.upstream(n, L * F, rng)
+    loss = torch.zeros(1, device="cuda")
+    d_table = torch.full((og.E, F), float("nan"), device="cuda")
+    wb = _lib.smoothness_workspace_bytes(lg, _lib.F32, n)
+    ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
+    _lib.hash4d_encode_backward_smooth(lg, _lib.F32, _dev(table), _dev(x), _dev(eps), n, _dev(gf), 0.5, 2.0, loss,
+                                       d_table, ws, wb, _lib.QUERY_MAJOR | _lib.GRAD_OVERWRITE)
+    torch.cuda.synchronize()
+    xp = O.perturbed(x, eps)
+    d = np.abs(O.encode(x, table, og) - O.encode(xp, table, og))
+    s = O.encode(x, np.abs(table), og) + O.encode(xp, np.abs(table), og)
+    g = 4.0 / n * (d + s)
+    scale = O.encode_backward(x, g + 0.5 * np.abs(gf), og) + O.encode_backward(xp, g, og)
+    ref = O.smoothness(x, eps, table, og, 2.0)[1] + O.encode_backward(x, gf, og, 0.5)
+    scaled_close(d_table.cpu().numpy(), ref, scale, RTOL_GRAD, f"{name} n={n} sigma={sigma}")
+
+
+@pytest.mark.gpu
+def test_more_chunks_than_one_round():
+    # 2^21 + 4001 queries: more chunks than the walk holds at a time
+    needs_gpu()
+    import torch
+    og = O.make_grid(1, 1, [24], [6], 1 << 15)
+    lg = _lib.h4d_grid_init(1, 1, [24], [6], 1 << 15)
+    n = (1 << 21) + 4001
+    rng = np.random.default_rng(5)
+    x = synth.uniform_xyzt(n, rng)
+    gf = synth.upstream(n, 1, rng)
+    wb = _lib.hash4d_encode_backward_workspace_bytes(lg, n)
+    ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
+    d_table = torch.full((og.E, 1), float("nan"), device="cuda")
+    _lib.hash4d_encode_backward(lg, _lib.F32, _dev(x), n, _dev(gf), 1.0, d_table, ws, wb, _lib.GRAD_OVERWRITE)
+    torch.cuda.synchronize()
+    scaled_close(d_table.cpu().numpy(), O.encode_backward(x, gf, og), O.encode_backward(x, np.abs(gf), og), RTOL_GRAD)
+
+
+def _static_rule(L, F, rs, rt, T, n):
+    """Bytes by which the static-workspace entry point has always decided: a mask and a
+    word per (query, level), counts per chunk of 1024, a plan and partial tiles."""
+    al = lambda b: (b + 255) // 256 * 256  # noqa: E731
+    rows = [min((s + 1) ** 3 * (t + 1), T) for s, t in zip(rs, rt)]
+    tiles = slot = 0
+    for gb in (4, 8):
+        mx, count = 131072 // (F * gb), 0
+        for r in rows:
+            sh = 8
+            while (1 << sh) < mx and (1 << sh) < -(-r // 32):
+                sh += 1
+            count += (r + (1 << sh) - 1) >> sh
+            slot = max(slot, min(1 << sh, r) * F * gb)
+        tiles = max(tiles, count)
+    pad, chunks, extra = (n + 3) // 4 * 4, (n + 1023) // 1024, min(96, max(8, tiles // 4))
+    return (al(pad * L * 4) + al(pad * L * 8) + al(L * chunks * 128) + al((tiles + extra) * 16) + 256 + al(extra * 4)
+            + 2 * extra * slot)
+
+
+@pytest.mark.parametrize("case", [("paper", 16, 2, (16, 2048), (16, 150), 1 << 19),
+                                  ("small", 4, 2, (4, 32), (4, 16), 1 << 12),
+                                  ("hashed", 32, 2, (64, 2048), (16, 150), 1 << 19),
+                                  ("one_level", 1, 4, (200, 200), (30, 30), 1 << 16),
+                                  ("loose", 8, 2, (300, 2048), (16, 64), 1 << 13),
+                                  ("modulo", 8, 8, (16, 512), (16, 64), 300_007),
+                                  ("dense", 3, 8, (2, 8), (2, 8), 1 << 20)], ids=lambda c: c[0])
+def test_static_workspace_takes_what_it_took(case):
+    # hash4d_encode_backward_noalloc accepts a call iff its workspace fits 64 MiB: every
+    # call that fits by the earlier rule still does, up to the largest of them
+    _, L, F, sp, tm, T = case
+    rs, rt = O.level_resolutions(*sp, L), O.level_resolutions(*tm, L)
+    lg = _lib.h4d_grid_init(L, F, rs, rt, T)
+    lo, hi = 1, 1 << 27
+    while lo < hi:  # the largest n within the earlier rule
+        mid = (lo + hi + 1) // 2
+        lo, hi = (mid, hi) if _static_rule(L, F, rs, rt, T, mid) <= 64 << 20 else (lo, mid - 1)
+    for n in {1, 100, 4096, 60_000, lo // 3, lo - 1, lo}:
+        if 1 <= n <= lo:
+            assert _lib.hash4d_encode_backward_workspace_bytes(lg, n) <= 64 << 20, n
