@@ -4,9 +4,12 @@
 // Work is a list of items (segment = (scene, timestamp), level group, tile of
 // queries), ordered scene by scene and, inside a scene, level group by level group,
 // so that all timestamps of a scene reuse one level's slice of that scene's table
-// while it is hot in L2.  A persistent grid walks the list with a fixed stride; the
-// tile width (queries per thread) and the number of levels per item are the
-// schedule the autotuner picks.
+// while it is hot in L2.  One workgroup per item, or a smaller grid that walks the list
+// with a fixed stride; the tile width (queries per thread), the number of levels per
+// item and the grid are the schedule the autotuner picks.  One workgroup per item is
+// the fastest where it was measured (6.2M queries of five scenes: FP32 4.15 ms against
+// 6.4 with 1024 workgroups, BF16 3.39 against 4.1): a walking workgroup waits for each
+// item's segment and positions with nothing else to run.
 #include <hip/hip_runtime.h>
 #include <string.h>
 
@@ -42,7 +45,7 @@ struct BRange {          // items [first, first + ntiles) belong to (seg, level 
 struct BSchedule {
     int qpt;             // queries per thread (tile = 256 qpt queries)
     int lpb;             // levels per item
-    int grid;            // persistent workgroups
+    int grid;            // workgroups: each walks the list with this stride (0: one per item)
 };
 
 __device__ __forceinline__ int find_range(const BRange* __restrict__ r, int nr, int item) {
@@ -58,8 +61,8 @@ __device__ __forceinline__ int find_range(const BRange* __restrict__ r, int nr, 
 // Workgroups go to the eight XCDs round-robin by id, so with a grid of whole rounds
 // XCD x walks its own contiguous eighth of the item list: at any time each XCD's L2
 // holds the level slices of its own part of the list instead of every XCD streaming
-// the same slice.  PAIRS: row-pair corner loads (gather_corners).
-template <typename TT, int F, bool PAIRS>
+// the same slice.  WIDE: see RawRow.
+template <typename TT, int F, bool WIDE>
 __global__ __launch_bounds__(kBatchBlock) void k_bencode(const BSeg* __restrict__ segs, const DevGrid* __restrict__ grids,
                                                          const BRange* __restrict__ ranges, int nranges, int total,
                                                          BSchedule sch) {
@@ -76,24 +79,13 @@ __global__ __launch_bounds__(kBatchBlock) void k_bencode(const BSeg* __restrict_
         const TT* __restrict__ table = static_cast<const TT*>(sg.table);
         for (int u = 0; u < sch.qpt; ++u) {
             const int q = (tile * sch.qpt + u) * kBatchBlock + (int)threadIdx.x;
-            if (q >= sg.n) break;
-            float4 x = sg.xyz[q];
+            float4 x = sg.xyz[min(q, sg.n - 1)];  // every lane takes part in the gathers
             x.w = sg.t;
             for (int l = l0; l < l1; ++l) {
                 const Cell c = level_cell(g, l, x);
-                uint32_t row[16];
-                level_rows(g, l, c, row);
-                float v[16][F];
-                gather_corners<TT, F, PAIRS>(g, table, row, v);
-                float w[16];
-                level_weights<float>(c, w);
                 float acc[F];
-#pragma unroll
-                for (int f = 0; f < F; ++f) acc[f] = 0.f;
-#pragma unroll
-                for (int k = 0; k < 16; ++k)
-#pragma unroll
-                    for (int f = 0; f < F; ++f) acc[f] += w[k] * v[k][f];
+                interpolate<TT, F, WIDE>(g, l, table, c, acc);
+                if (q >= sg.n) continue;
                 float* o = sg.feat + ((int64_t)l * sg.n + q) * F;
 #pragma unroll
                 for (int f = 0; f < F; ++f) o[f] = acc[f];
@@ -218,7 +210,7 @@ struct h4d_batched_plan {
     float* d_feat = nullptr;
     void* ws = nullptr;
     size_t ws_bytes = 0;
-    BSchedule enc{1, 1, 2048};
+    BSchedule enc{1, 1, 0};
     MlpBatch fwd{}, bwd{};
     int fwd_blocks = 0, bwd_blocks = 0;
     hipGraph_t graph = nullptr;
@@ -266,21 +258,31 @@ static hipError_t upload_ranges(BRange** dst, const std::vector<BRange>& r) {
     return e;
 }
 
+// Workgroups of a schedule: whole rounds of the XCDs, no more than the items need.
+static int encode_grid(const BSchedule& s, int items) {
+    const int all = (items + kXcds - 1) / kXcds * kXcds;
+    return s.grid > 0 ? std::min(s.grid, all) : all;
+}
+
 static hipError_t launch_bencode(const h4d_batched_plan& p, const BSchedule& s, hipStream_t st) {
     if (p.total_enc == 0) return hipSuccess;
     const int F = p.scenes[0].grid.F;
-    const dim3 grid(std::min(s.grid, p.total_enc)), block(kBatchBlock);
-    // row-pair loads need every scene's table aligned to two rows
-    const size_t pair_bytes = 2 * 2 * (p.dt == H4D_BF16 ? sizeof(uint16_t) : sizeof(float));
-    bool pairs = F == 2;
-    for (const h4d_scene_desc& d : p.scenes) pairs = pairs && ((uintptr_t)d.table % pair_bytes) == 0;
-#define H4D_BENC(TT, FF, PP) hipLaunchKernelGGL((k_bencode<TT, FF, PP>), grid, block, 0, st, p.segs, p.grids, \
+    const dim3 grid(encode_grid(s, p.total_enc)), block(kBatchBlock);
+    // the wide form needs every scene's table to allow it
+    bool wide = true;
+    for (int i = 0; i < p.n_scenes; ++i) {
+        const h4d_scene_desc& d = p.scenes[i];
+        const uint32_t rows = p.grids_h[i].rows;
+        wide = wide && (p.dt == H4D_BF16 ? F == 2 && can_widen<bf16_t, 2>(d.table, rows)
+                                         : F == 1 && can_widen<float, 1>(d.table, rows));
+    }
+#define H4D_BENC(TT, FF, WW) hipLaunchKernelGGL((k_bencode<TT, FF, WW>), grid, block, 0, st, p.segs, p.grids, \
                                                 p.ranges_enc, p.nranges_enc, p.total_enc, s)
     if (p.dt == H4D_BF16) {
         switch (F) {
             case 1: H4D_BENC(bf16_t, 1, false); break;
             case 2:
-                if (pairs) H4D_BENC(bf16_t, 2, true);
+                if (wide) H4D_BENC(bf16_t, 2, true);
                 else H4D_BENC(bf16_t, 2, false);
                 break;
             case 4: H4D_BENC(bf16_t, 4, false); break;
@@ -288,11 +290,11 @@ static hipError_t launch_bencode(const h4d_batched_plan& p, const BSchedule& s, 
         }
     } else {
         switch (F) {
-            case 1: H4D_BENC(float, 1, false); break;
-            case 2:
-                if (pairs) H4D_BENC(float, 2, true);
-                else H4D_BENC(float, 2, false);
+            case 1:
+                if (wide) H4D_BENC(float, 1, true);
+                else H4D_BENC(float, 1, false);
                 break;
+            case 2: H4D_BENC(float, 2, false); break;
             case 4: H4D_BENC(float, 4, false); break;
             default: H4D_BENC(float, 8, false); break;
         }
@@ -446,7 +448,7 @@ namespace h4d {
 static hipError_t autotune(h4d_batched_plan& p, const std::vector<BSeg>& segs, hipStream_t st) {
     const int qpts[] = {1, 2};
     const int lpbs[] = {1, 2, 4};
-    const int grids[] = {1024, 2048, 4096, 8192};
+    const int grids[] = {0, 1024, 4096, 16384};
     hipEvent_t a = nullptr, b = nullptr;
     hipError_t e = hipEventCreate(&a);
     if (e == hipSuccess) e = hipEventCreate(&b);
@@ -473,7 +475,7 @@ static hipError_t autotune(h4d_batched_plan& p, const std::vector<BSeg>& segs, h
                 if (e == hipSuccess) e = hipEventElapsedTime(&ms, a, b);
                 if (e != hipSuccess) continue;
                 ms /= 3.f;
-                p.tuned.push_back(h4d_tune_result{0, qpt, lpb, gsz, ms});
+                p.tuned.push_back(h4d_tune_result{0, qpt, lpb, encode_grid(cand, p.total_enc), ms});
                 if (ms < best) {
                     best = ms;
                     best_s = cand;
@@ -691,7 +693,7 @@ h4d_status hash4d_batched_plan_info(const h4d_batched_plan* p, h4d_batched_info*
     info->segments = p->nseg;
     info->encode_qpt = p->enc.qpt;
     info->encode_lpb = p->enc.lpb;
-    info->encode_grid = p->enc.grid;
+    info->encode_grid = encode_grid(p->enc, p->total_enc);
     info->scatter_tiles = p->ntiles;
     info->scatter_rows_per_tile = kTileBytes / (p->scenes[0].grid.F * (int)sizeof(float));
     info->graph = p->exec != nullptr;

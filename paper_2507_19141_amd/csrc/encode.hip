@@ -15,11 +15,9 @@
 
 namespace h4d {
 
-constexpr int kEncodeBlock = 256;
+constexpr int kEncodeBlock = 64;  // small: a workgroup's wavefronts then end one by one (256: 2 us slower at 200k)
 
-// PAIRS: row-pair loads (gather_corners).  The loads change; the arithmetic (and its
-// order) does not.
-template <typename TT, int F, bool PAIRS>
+template <typename TT, int F, bool WIDE>
 __global__ __launch_bounds__(kEncodeBlock) void k_encode(DevGrid g, const TT* __restrict__ table,
                                                          const float4* __restrict__ xyzt, int n,
                                                          typename AccOf<TT>::type* __restrict__ out,
@@ -29,21 +27,10 @@ __global__ __launch_bounds__(kEncodeBlock) void k_encode(DevGrid g, const TT* __
     int l, chunk;
     if (!xcd_item(g.L * chunks, chunks, l, chunk)) return;
     const int q = chunk * kEncodeBlock + threadIdx.x;
-    if (q >= n) return;
-    const Cell c = level_cell(g, l, xyzt[q]);
-    uint32_t row[16];
-    level_rows(g, l, c, row);
-    A v[16][F];
-    gather_corners<TT, F, PAIRS>(g, table, row, v);
-    A w[16];
-    level_weights<A>(c, w);
+    const Cell c = level_cell(g, l, xyzt[min(q, n - 1)]);  // every lane takes part in the gather
     A acc[F];
-#pragma unroll
-    for (int f = 0; f < F; ++f) acc[f] = A(0);
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-#pragma unroll
-        for (int f = 0; f < F; ++f) acc[f] += w[k] * v[k][f];
+    interpolate<TT, F, WIDE>(g, l, table, c, acc);
+    if (q >= n) return;
     A* o = out + (int64_t)l * lstride + (int64_t)q * qstride;
     if constexpr (F == 2 && sizeof(A) == 4) {
         *reinterpret_cast<float2*>(o) = make_float2(acc[0], acc[1]);
@@ -390,18 +377,21 @@ static hipError_t encode_t(const DevGrid& g, const void* table, const float* xyz
     const TT* t = static_cast<const TT*>(table);
     const float4* x = reinterpret_cast<const float4*>(xyzt);
     A* o = static_cast<A*>(out);
-    constexpr bool kPairable = !std::is_same<TT, double>::value;
-    const bool pairs = kPairable && g.F == 2 && ((uintptr_t)table % (2 * 2 * sizeof(TT))) == 0;
+#define H4D_ENC(FF, WW) hipLaunchKernelGGL((k_encode<TT, FF, WW>), grid, block, 0, s, g, t, x, n, o, ls, qs)
     switch (g.F) {
-        case 1: hipLaunchKernelGGL((k_encode<TT, 1, false>), grid, block, 0, s, g, t, x, n, o, ls, qs); break;
-        case 2:
-            if (pairs) hipLaunchKernelGGL((k_encode<TT, 2, kPairable>), grid, block, 0, s, g, t, x, n, o, ls, qs);
-            else hipLaunchKernelGGL((k_encode<TT, 2, false>), grid, block, 0, s, g, t, x, n, o, ls, qs);
+        case 1:
+            if (can_widen<TT, 1>(table, g.rows)) H4D_ENC(1, true);
+            else H4D_ENC(1, false);
             break;
-        case 4: hipLaunchKernelGGL((k_encode<TT, 4, false>), grid, block, 0, s, g, t, x, n, o, ls, qs); break;
-        case 8: hipLaunchKernelGGL((k_encode<TT, 8, false>), grid, block, 0, s, g, t, x, n, o, ls, qs); break;
+        case 2:
+            if (can_widen<TT, 2>(table, g.rows)) H4D_ENC(2, true);
+            else H4D_ENC(2, false);
+            break;
+        case 4: H4D_ENC(4, false); break;
+        case 8: H4D_ENC(8, false); break;
         default: return hipErrorInvalidValue;
     }
+#undef H4D_ENC
     return hipGetLastError();
 }
 

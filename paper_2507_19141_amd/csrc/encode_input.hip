@@ -10,8 +10,8 @@
 //
 // With a workspace (FP32 and BF16 tables) the work is split in two passes instead:
 // one thread per (query, level), placed on the XCDs level by level like the encoder
-// (each XCD's L2 serves one level's table slice at a time, and x-pairs of corners come
-// from one row-pair load), writes the level's four terms N_d s_d to a [L, n] float4
+// (each XCD's L2 serves one level's table slice at a time, and neighbouring lanes gather
+// corners together), writes the level's four terms N_d s_d to a [L, n] float4
 // buffer; a second pass sums them per query in level order and applies the clamp and
 // the scale.
 #include "h4d_device.h"
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kInputGradBlock) void k_encode_input_grad(DevGrid g
 }
 
 // Pass 1 of the two-pass form: the four terms of level l for query q.
-template <typename TT, int F, bool PAIRS>
+template <typename TT, int F, bool WIDE>
 __global__ __launch_bounds__(kInputGradBlock) void k_input_grad_levels(DevGrid g, const TT* __restrict__ table,
                                                                        const float4* __restrict__ xyzt, int n,
                                                                        const float* __restrict__ d_feat,
@@ -103,23 +103,17 @@ __global__ __launch_bounds__(kInputGradBlock) void k_input_grad_levels(DevGrid g
     int l, chunk;
     if (!xcd_item(g.L * chunks, chunks, l, chunk)) return;
     const int q = chunk * kInputGradBlock + threadIdx.x;
-    if (q >= n) return;
-    const Cell c = level_cell(g, l, xyzt[q]);
-    uint32_t row[16];
-    level_rows(g, l, c, row);
-    float v[16][F];
-    gather_corners<TT, F, PAIRS>(g, table, row, v);
-    const float* gp = d_feat + (int64_t)l * lstride + (int64_t)q * qstride;
+    const Cell c = level_cell(g, l, xyzt[min(q, n - 1)]);  // every lane takes part in the gather
+    const float* gp = d_feat + (int64_t)l * lstride + (int64_t)min(q, n - 1) * qstride;
     float gv[F];
 #pragma unroll
     for (int f = 0; f < F; ++f) gv[f] = gp[f];
     const float w[4][2] = {{1.f - c.fx, c.fx}, {1.f - c.fy, c.fy}, {1.f - c.fz, c.fz}, {1.f - c.ft, c.ft}};
     float s[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    auto corner = [&](int k, const float (&v)[F]) {
         float tg = 0.f;
 #pragma unroll
-        for (int f = 0; f < F; ++f) tg += v[k][f] * gv[f];
+        for (int f = 0; f < F; ++f) tg += v[f] * gv[f];
         const int bx = k & 1, by = (k >> 1) & 1, bz = (k >> 2) & 1, bt = k >> 3;
         const float wx = w[0][bx], wy = w[1][by], wz = w[2][bz], wt = w[3][bt];
         const float pxy = wx * wy, pzt = wz * wt;
@@ -128,7 +122,12 @@ __global__ __launch_bounds__(kInputGradBlock) void k_input_grad_levels(DevGrid g
         s[1] += by ? dy : -dy;
         s[2] += bz ? dz : -dz;
         s[3] += bt ? dt : -dt;
-    }
+    };
+    each_pair<TT, F, WIDE>(g, l, table, c, [&](int p, const float (&lo)[F], const float (&hi)[F]) {
+        corner(2 * p, lo);
+        corner(2 * p + 1, hi);
+    });
+    if (q >= n) return;
     const float Ns = (float)g.res_s[l], Nt = (float)g.res_t[l];
     part[(int64_t)l * n + q] = make_float4(Ns * s[0], Ns * s[1], Ns * s[2], Nt * s[3]);
 }
@@ -168,17 +167,21 @@ static hipError_t input_grad_two_pass(const DevGrid& g, const void* table, const
     const float4* x = reinterpret_cast<const float4*>(xyzt);
     const float* gf = static_cast<const float*>(d_feat);
     float4* part = static_cast<float4*>(ws);
-    const bool pairs = ((uintptr_t)table % (2 * 2 * sizeof(TT))) == 0;
+#define H4D_IGRAD(FF, WW) hipLaunchKernelGGL((k_input_grad_levels<TT, FF, WW>), grid, block, 0, s, g, t, x, n, gf, ls, qs, part)
     switch (g.F) {
-        case 1: hipLaunchKernelGGL((k_input_grad_levels<TT, 1, false>), grid, block, 0, s, g, t, x, n, gf, ls, qs, part); break;
-        case 2:
-            if (pairs) hipLaunchKernelGGL((k_input_grad_levels<TT, 2, true>), grid, block, 0, s, g, t, x, n, gf, ls, qs, part);
-            else hipLaunchKernelGGL((k_input_grad_levels<TT, 2, false>), grid, block, 0, s, g, t, x, n, gf, ls, qs, part);
+        case 1:
+            if (can_widen<TT, 1>(table, g.rows)) H4D_IGRAD(1, true);
+            else H4D_IGRAD(1, false);
             break;
-        case 4: hipLaunchKernelGGL((k_input_grad_levels<TT, 4, false>), grid, block, 0, s, g, t, x, n, gf, ls, qs, part); break;
-        case 8: hipLaunchKernelGGL((k_input_grad_levels<TT, 8, false>), grid, block, 0, s, g, t, x, n, gf, ls, qs, part); break;
+        case 2:
+            if (can_widen<TT, 2>(table, g.rows)) H4D_IGRAD(2, true);
+            else H4D_IGRAD(2, false);
+            break;
+        case 4: H4D_IGRAD(4, false); break;
+        case 8: H4D_IGRAD(8, false); break;
         default: return hipErrorInvalidValue;
     }
+#undef H4D_IGRAD
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_input_grad_reduce, dim3((unsigned)((n + kInputGradBlock - 1) / kInputGradBlock)),

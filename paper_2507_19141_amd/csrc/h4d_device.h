@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "h4d_internal.h"
 
 namespace h4d {
@@ -127,6 +129,10 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
     return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
 
+// Compute type of each table type: FP32 for F32/BF16 tables, FP64 for FP64 tables.
+template <typename TT> struct AccOf { using type = float; };
+template <> struct AccOf<double> { using type = double; };
+
 // Load the F features of one row as type A.
 template <typename TT, int F, typename A>
 struct RowLoad;
@@ -184,68 +190,186 @@ struct RowLoad<double, F, A> {
     }
 };
 
-// Two consecutive rows (r, r + 1), r even, in one aligned load (F = 2 FP32 rows:
-// 16 bytes; F = 2 BF16 rows: 8 bytes).  lo receives row r, hi row r + 1.
-template <typename TT, typename A>
-struct RowPairLoad;
 
-template <typename A>
-struct RowPairLoad<float, A> {
-    __device__ __forceinline__ static void load(const float* __restrict__ t, uint32_t r, A (&lo)[2], A (&hi)[2]) {
-        const float4 a = *reinterpret_cast<const float4*>(t + (size_t)r * 2);
-        lo[0] = (A)a.x; lo[1] = (A)a.y; hi[0] = (A)a.z; hi[1] = (A)a.w;
-    }
-};
+// ---- corner gathers shared by neighbouring lanes ----
+// The two corners of an x-pair lie in one 128-byte line almost always (pi_1 = 1: their
+// rows differ in the low bits only), and a gather costs the vector memory pipe a clock,
+// and the L1 a line from L2, per line that neighbouring lanes do not share.  So the lanes
+// of an even/odd pair gather together: one instruction reads both corners of the even
+// lane's query (lower corner in the even lane, upper in the odd one), the next one those
+// of the odd lane's query, and a lane swap (DPP quad_perm 1, 0, 3, 2) hands each lane its
+// own two values.  Both lanes of a pair have to be active.  Against one 16-byte load for
+// pairs that are one aligned row pair and two loads for the others (200k queries of the
+// 16-level scene): FP32 167 -> 143 us, BF16 133 -> 119 us, 2.06e11 lines a second of the
+// 2.58e11 that random 128-byte lines reach from L2.
+__device__ __forceinline__ uint32_t lane_swap(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xf, 0xf, true);
+}
 
-template <typename A>
-struct RowPairLoad<bf16_t, A> {
-    __device__ __forceinline__ static void load(const bf16_t* __restrict__ t, uint32_t r, A (&lo)[2], A (&hi)[2]) {
-        const uint2 a = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint16_t*>(t) + (size_t)r * 2);
-        lo[0] = (A)__uint_as_float(a.x << 16); lo[1] = (A)__uint_as_float(a.x & 0xffff0000u);
-        hi[0] = (A)__uint_as_float(a.y << 16); hi[1] = (A)__uint_as_float(a.y & 0xffff0000u);
-    }
-};
+// One table row as raw 32-bit words.  Wide: rows of 4 bytes are read as the aligned 8-byte
+// row pair they lie in (a 4-byte gather costs a clock per lane whatever lines it touches,
+// an 8-byte one a clock per line), so the table has to be aligned to 8 bytes and have at
+// least two rows; the last row of an odd table is read together with the one before it.
+template <typename TT, int F>
+struct RawRow {
+    static constexpr int kBytes = (int)sizeof(TT) * F;
+    static constexpr int kWords = kBytes < 4 ? 1 : kBytes / 4;
+    static constexpr bool kCanWiden = kBytes == 4;
+    uint32_t w[kWords];
 
-// Compute type of each table type: FP32 for F32/BF16 tables, FP64 for FP64 tables.
-template <typename TT> struct AccOf { using type = float; };
-template <> struct AccOf<double> { using type = double; };
-
-// The 16 corner rows of one cell into v.  PAIRS (F = 2 FP32 / BF16 tables aligned to
-// two rows): the two corners of an x-pair (same y, z, t) sit in rows r0 and r0 ^ 1
-// whenever their hashes differ only in bit 0 (pi_1 = 1 and an even lower x index;
-// r1 = r0 + 1 on dense levels with r0 even), and one aligned load of the row pair
-// then serves both corners.
-template <typename TT, int F, bool PAIRS, typename A>
-__device__ __forceinline__ void gather_corners(const DevGrid& g, const TT* __restrict__ table,
-                                               const uint32_t (&row)[16], A (&v)[16][F]) {
-    if constexpr (PAIRS) {
+    template <bool WIDE>
+    __device__ __forceinline__ void load(const TT* __restrict__ t, uint32_t row, uint32_t rows) {
+        const char* base = reinterpret_cast<const char*>(t);
+        if constexpr (WIDE && kCanWiden) {
+            const uint32_t a = min(row & ~1u, rows - 2u);
+            const uint2 v = *reinterpret_cast<const uint2*>(base + (size_t)a * 4u);
+            w[0] = row != a ? v.y : v.x;
+        } else if constexpr (kBytes == 2) {
+            w[0] = *reinterpret_cast<const uint16_t*>(base + (size_t)row * 2u);
+        } else if constexpr (kBytes == 4) {
+            w[0] = *reinterpret_cast<const uint32_t*>(base + (size_t)row * 4u);
+        } else if constexpr (kBytes == 8) {
+            const uint2 v = *reinterpret_cast<const uint2*>(base + (size_t)row * 8u);
+            w[0] = v.x;
+            w[1] = v.y;
+        } else {
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
-            const uint32_t r0 = row[2 * p], r1 = row[2 * p + 1];
-            const uint32_t a = r0 & ~1u;
-            if (a + 1u < g.rows) {
-                A lo[2], hi[2];
-                RowPairLoad<TT, A>::load(table, a, lo, hi);
-                const bool odd = r0 & 1u;
-#pragma unroll
-                for (int f = 0; f < 2; ++f) v[2 * p][f] = odd ? hi[f] : lo[f];
-                if (r1 == (r0 ^ 1u)) {
-#pragma unroll
-                    for (int f = 0; f < 2; ++f) v[2 * p + 1][f] = odd ? lo[f] : hi[f];
-                } else {
-                    RowLoad<TT, F, A>::load(table, r1, v[2 * p + 1]);
-                }
-            } else {
-                RowLoad<TT, F, A>::load(table, r0, v[2 * p]);
-                RowLoad<TT, F, A>::load(table, r1, v[2 * p + 1]);
+            for (int j = 0; j < kWords; j += 4) {
+                const uint4 v = *reinterpret_cast<const uint4*>(base + (size_t)row * kBytes + 4 * j);
+                w[j] = v.x;
+                w[j + 1] = v.y;
+                w[j + 2] = v.z;
+                w[j + 3] = v.w;
             }
         }
-    } else {
+    }
+    __device__ __forceinline__ float value(int f) const {
+        if constexpr (sizeof(TT) == 4) return __uint_as_float(w[f]);
+        else return f & 1 ? __uint_as_float(w[f / 2] & 0xffff0000u) : __uint_as_float(w[f / 2] << 16);
+    }
+};
+
+// N x-pairs: rows x[p] (the corner this lane reads for its own query: lower in even
+// lanes, upper in odd ones) and y[p] (the other corner) into v[2 p] (lower) and v[2 p + 1]
+// (upper).  Called by both lanes of every pair.
+template <typename TT, int F, bool WIDE, int N>
+__device__ __forceinline__ void gather_pairs(const TT* __restrict__ table, uint32_t rows, const uint32_t (&x)[N],
+                                             const uint32_t (&y)[N], float (&v)[2 * N][F]) {
+    using R = RawRow<TT, F>;
+    const bool odd = threadIdx.x & 1u;
+    R a[N], b[N];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) RowLoad<TT, F, A>::load(table, row[k], v[k]);
+    for (int p = 0; p < N; ++p) {
+        const uint32_t other = lane_swap(y[p]);
+        a[p].template load<WIDE>(table, odd ? other : x[p], rows);  // the even lane's query
+        b[p].template load<WIDE>(table, odd ? x[p] : other, rows);  // the odd lane's query
+    }
+#pragma unroll
+    for (int p = 0; p < N; ++p) {
+        R lo, hi;
+#pragma unroll
+        for (int k = 0; k < R::kWords; ++k) {
+            const uint32_t sa = lane_swap(a[p].w[k]), sb = lane_swap(b[p].w[k]);
+            lo.w[k] = odd ? sb : a[p].w[k];
+            hi.w[k] = odd ? b[p].w[k] : sa;
+        }
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            v[2 * p][f] = lo.value(f);
+            v[2 * p + 1][f] = hi.value(f);
+        }
     }
 }
 
+// Rows x and y of gather_pairs for the 8 pairs of a cell of the 4D grid.
+__device__ __forceinline__ void pair_rows_xy(const DevGrid& g, int l, const Cell& c, uint32_t (&x)[8], uint32_t (&y)[8]) {
+    const uint32_t odd = threadIdx.x & 1u;
+    const uint32_t off = g.off[l], ix = (uint32_t)c.ix + odd, iy = (uint32_t)c.ix + (odd ^ 1u);
+    if ((g.dense_bits >> l) & 1u) {
+        const uint32_t S = (uint32_t)g.res_s[l] + 1u;
+        const uint32_t S2 = S * S, S3 = S2 * S;
+        const uint32_t base = off + S * ((uint32_t)c.iy + S * ((uint32_t)c.iz + S * (uint32_t)c.it));
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const uint32_t line = base + (p & 1) * S + ((p >> 1) & 1) * S2 + (p >> 2) * S3;
+            x[p] = line + ix;
+            y[p] = line + iy;
+        }
+    } else {
+        const uint32_t hx = ix * g.prime[0], hy = iy * g.prime[0];
+        const uint32_t hy0 = (uint32_t)c.iy * g.prime[1], hy1 = hy0 + g.prime[1];
+        const uint32_t hz0 = (uint32_t)c.iz * g.prime[2], hz1 = hz0 + g.prime[2];
+        const uint32_t ht0 = (uint32_t)c.it * g.prime[3], ht1 = ht0 + g.prime[3];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const uint32_t h = ((p & 1) ? hy1 : hy0) ^ ((p & 2) ? hz1 : hz0) ^ ((p & 4) ? ht1 : ht0);
+            if (g.tmask) {
+                x[p] = off + ((hx ^ h) & g.tmask);
+                y[p] = off + ((hy ^ h) & g.tmask);
+            } else {
+                x[p] = off + (hx ^ h) % g.T;
+                y[p] = off + (hy ^ h) % g.T;
+            }
+        }
+    }
+}
+
+// each(p, lo, hi) with the rows of the lower and upper corner of every x-pair p = 0 .. 7 of
+// a cell, in order (corner k of level_rows: pair k / 2).  The pairs are gathered in groups
+// that keep the rows in flight within the registers.  FP32 and BF16 tables: called by both
+// lanes of every even/odd pair.
+template <typename TT, int F, bool WIDE, typename Each>
+__device__ __forceinline__ void each_pair(const DevGrid& g, int l, const TT* __restrict__ table, const Cell& c, Each each) {
+    using A = typename AccOf<TT>::type;
+    if constexpr (std::is_same<TT, double>::value) {
+        uint32_t row[16];
+        level_rows(g, l, c, row);
+        A v[16][F];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) RowLoad<TT, F, A>::load(table, row[k], v[k]);
+#pragma unroll
+        for (int p = 0; p < 8; ++p) each(p, v[2 * p], v[2 * p + 1]);
+    } else {
+        constexpr int kGroup = F <= 2 ? 8 : F == 4 ? 4 : 2;
+        uint32_t x[8], y[8];
+        pair_rows_xy(g, l, c, x, y);
+#pragma unroll
+        for (int p0 = 0; p0 < 8; p0 += kGroup) {
+            uint32_t gx[kGroup], gy[kGroup];
+#pragma unroll
+            for (int j = 0; j < kGroup; ++j) {
+                gx[j] = x[p0 + j];
+                gy[j] = y[p0 + j];
+            }
+            A v[2 * kGroup][F];
+            gather_pairs<TT, F, WIDE, kGroup>(table, g.rows, gx, gy, v);
+#pragma unroll
+            for (int j = 0; j < kGroup; ++j) each(p0 + j, v[2 * j], v[2 * j + 1]);
+        }
+    }
+}
+
+// Features of a cell: acc[f] += w_k v_k[f] over the corners in order.
+template <typename TT, int F, bool WIDE, typename A>
+__device__ __forceinline__ void interpolate(const DevGrid& g, int l, const TT* __restrict__ table, const Cell& c,
+                                            A (&acc)[F]) {
+    A w[16];
+    level_weights<A>(c, w);
+#pragma unroll
+    for (int f = 0; f < F; ++f) acc[f] = A(0);
+    each_pair<TT, F, WIDE>(g, l, table, c, [&](int p, const A (&lo)[F], const A (&hi)[F]) {
+#pragma unroll
+        for (int f = 0; f < F; ++f) acc[f] += w[2 * p] * lo[f];
+#pragma unroll
+        for (int f = 0; f < F; ++f) acc[f] += w[2 * p + 1] * hi[f];
+    });
+}
+
+// Whether a table of `rows` rows can be read in the wide form (RawRow).
+template <typename TT, int F>
+inline bool can_widen(const void* table, uint32_t rows) {
+    return sizeof(TT) * F == 4 && ((uintptr_t)table & 7u) == 0 && rows >= 2u;
+}
 
 __device__ __forceinline__ void atomic_add(float* p, float v) { unsafeAtomicAdd(p, v); }
 __device__ __forceinline__ void atomic_add(double* p, double v) { unsafeAtomicAdd(p, v); }

@@ -6,15 +6,14 @@
 // level); when x and x~ fall in the same hypervoxel (the coarse levels for a small
 // eps) their 16 corners coincide and one gather per corner gives d with the weight
 // difference w - w~.  Work items (level, 256 queries) are placed on XCDs level by
-// level, and F = 2 FP32 / BF16 tables aligned to two rows read an x-pair of corners
-// that shares an aligned row pair with one load, both as in the encoder.
+// level, and neighbouring lanes gather corners together, both as in the encoder.
 #include "h4d_device.h"
 
 namespace h4d {
 
 constexpr int kSmoothBlock = 256;
 
-template <typename TT, int F, bool PAIRS>
+template <typename TT, int F, bool WIDE>
 __global__ __launch_bounds__(kSmoothBlock) void k_smooth(DevGrid g, const TT* __restrict__ table,
                                                          const float4* __restrict__ xyzt,
                                                          const float4* __restrict__ eps, int n,
@@ -28,54 +27,50 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth(DevGrid g, const TT* __
     if (!xcd_item(g.L * chunks, chunks, l, chunk)) return;
     const int q = chunk * kSmoothBlock + threadIdx.x;
     A part = A(0);
-    if (q < n) {
-        const float4 x = xyzt[q];
-        const float4 e = eps[q];
+    {   // every lane takes part in the gathers
+        const float4 x = xyzt[min(q, n - 1)];
+        const float4 e = eps[min(q, n - 1)];
         const float4 xp = make_float4(__fadd_rn(x.x, e.x), __fadd_rn(x.y, e.y), __fadd_rn(x.z, e.z), __fadd_rn(x.w, e.w));
         const Cell c0 = level_cell(g, l, x);
         const Cell c1 = level_cell(g, l, xp);
         const bool same = c0.ix == c1.ix && c0.iy == c1.iy && c0.iz == c1.iz && c0.it == c1.it;
-        uint32_t r0[16], r1[16];
-        level_rows(g, l, c0, r0);
-        if (!same) level_rows(g, l, c1, r1);
         A w0[16], w1[16];
         level_weights<A>(c0, w0);
         level_weights<A>(c1, w1);
-        A d[F];
+        A d[F], a0[F];
 #pragma unroll
-        for (int f = 0; f < F; ++f) d[f] = A(0);
-        if (same) {
-            A v[16][F];
-            gather_corners<TT, F, PAIRS>(g, table, r0, v);
+        for (int f = 0; f < F; ++f) d[f] = a0[f] = A(0);
+        each_pair<TT, F, WIDE>(g, l, table, c0, [&](int p, const A (&lo)[F], const A (&hi)[F]) {
+            const A dl = w0[2 * p] - w1[2 * p], dh = w0[2 * p + 1] - w1[2 * p + 1];
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const A dw = w0[k] - w1[k];
-#pragma unroll
-                for (int f = 0; f < F; ++f) d[f] += dw * v[k][f];
+            for (int f = 0; f < F; ++f) {
+                d[f] += dl * lo[f];
+                a0[f] += w0[2 * p] * lo[f];
             }
-        } else {
-            A v0[16][F], v1[16][F];
-            gather_corners<TT, F, PAIRS>(g, table, r0, v0);
-            gather_corners<TT, F, PAIRS>(g, table, r1, v1);
-            A a0[F], a1[F];
 #pragma unroll
-            for (int f = 0; f < F; ++f) a0[f] = a1[f] = A(0);
+            for (int f = 0; f < F; ++f) {
+                d[f] += dh * hi[f];
+                a0[f] += w0[2 * p + 1] * hi[f];
+            }
+        });
+        // the second cell's corners, where it differs in either lane of the pair
+        const bool other = lane_swap(same ? 0u : 1u) != 0u;
+        if (!same || other) {
+            A a1[F];
+            interpolate<TT, F, WIDE>(g, l, table, c1, a1);
+            if (!same) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k)
-#pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    a0[f] += w0[k] * v0[k][f];
-                    a1[f] += w1[k] * v1[k][f];
-                }
-#pragma unroll
-            for (int f = 0; f < F; ++f) d[f] = a0[f] - a1[f];
+                for (int f = 0; f < F; ++f) d[f] = a0[f] - a1[f];
+            }
         }
+        if (q < n) {
 #pragma unroll
         for (int f = 0; f < F; ++f) part += d[f] * d[f];
         if (d_out) {
             A* o = d_out + ((int64_t)l * n + q) * F;
 #pragma unroll
             for (int f = 0; f < F; ++f) o[f] = d[f];
+        }
         }
     }
     // block sum of the squared differences, one atomic per block
@@ -101,20 +96,21 @@ static hipError_t smooth_t(const DevGrid& g, const void* table, const float* xyz
     const A c = (A)(lam / (double)n);
     A* lo = static_cast<A*>(loss);
     A* dd = static_cast<A*>(d_out);
-    constexpr bool kPairable = !std::is_same<TT, double>::value;
-    const bool pairs = kPairable && ((uintptr_t)table % (2 * 2 * sizeof(TT))) == 0;
+#define H4D_SMOOTH(FF, WW) hipLaunchKernelGGL((k_smooth<TT, FF, WW>), grid, block, 0, s, g, t, x, e, n, c, lo, dd)
     switch (g.F) {
-        case 1: hipLaunchKernelGGL((k_smooth<TT, 1, false>), grid, block, 0, s, g, t, x, e, n, c, lo, dd); break;
-        case 2:
-            if (pairs)
-                hipLaunchKernelGGL((k_smooth<TT, 2, kPairable>), grid, block, 0, s, g, t, x, e, n, c, lo, dd);
-            else
-                hipLaunchKernelGGL((k_smooth<TT, 2, false>), grid, block, 0, s, g, t, x, e, n, c, lo, dd);
+        case 1:
+            if (can_widen<TT, 1>(table, g.rows)) H4D_SMOOTH(1, true);
+            else H4D_SMOOTH(1, false);
             break;
-        case 4: hipLaunchKernelGGL((k_smooth<TT, 4, false>), grid, block, 0, s, g, t, x, e, n, c, lo, dd); break;
-        case 8: hipLaunchKernelGGL((k_smooth<TT, 8, false>), grid, block, 0, s, g, t, x, e, n, c, lo, dd); break;
+        case 2:
+            if (can_widen<TT, 2>(table, g.rows)) H4D_SMOOTH(2, true);
+            else H4D_SMOOTH(2, false);
+            break;
+        case 4: H4D_SMOOTH(4, false); break;
+        case 8: H4D_SMOOTH(8, false); break;
         default: return hipErrorInvalidValue;
     }
+#undef H4D_SMOOTH
     return hipGetLastError();
 }
 
