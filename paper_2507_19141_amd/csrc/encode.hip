@@ -235,15 +235,6 @@ __device__ __forceinline__ void add_count(int* counter, int bad) {
 // Tiles of one run of the scatter's XCD placement (16 runs).
 __host__ __device__ constexpr int scatter_run(int tiles) { return (tiles + 2 * kXcds - 1) / (2 * kXcds); }
 
-// Zero the first `values` values of the tile (whose buffer is a whole number of 16-byte
-// units).
-template <typename G>
-__device__ __forceinline__ void zero_tile(G* tile, uint32_t values) {
-    uint4* t = reinterpret_cast<uint4*>(tile);
-    const uint32_t quads = (values * (uint32_t)sizeof(G) + 15u) / 16u;
-    for (uint32_t i = threadIdx.x; i < quads; i += kScatterBlock) t[i] = make_uint4(0u, 0u, 0u, 0u);
-}
-
 // The tile's rows have no other owner: add them to d_table, or with overwrite set write
 // every row (the tiles of the levels cover all E rows); count the non-finite values
 // written if asked.
@@ -311,7 +302,7 @@ __global__ __launch_bounds__(kScatterBlock) void k_scatter_tiled(DevGrid g, Tile
     if (!scatter_tile(g, tm, l, t) || !((tm.lists >> l) & 1u)) return;
     TileRows tr = tile_rows(g, tm, l, t);
     set_copies<G, F>(tr, tm.tile_start[l + 1] - tm.tile_start[l], n);
-    zero_tile(tile, tr.copies > 1u ? tr.copies * tr.stride : tr.cnt * F);
+    zero_tile<kScatterBlock>(tile, tr.copies > 1u ? tr.copies * tr.stride : tr.cnt * F);
     __syncthreads();
     scatter_lists<G, F, PAIR>(g, tm, l, tr, xyzt, eps, n, heads, lists, src, lstride, qstride, scale, mg, walk,
                               tile + (threadIdx.x & (tr.copies - 1u)) * tr.stride);
@@ -335,7 +326,7 @@ __global__ __launch_bounds__(kScatterBlock) void k_scatter_masked(DevGrid g, Til
     uint32_t t;
     if (!scatter_tile(g, tm, l, t) || ((tm.lists >> l) & 1u)) return;
     const TileRows tr = tile_rows(g, tm, l, t);
-    zero_tile(tile, tr.cnt * F);
+    zero_tile<kScatterBlock>(tile, tr.cnt * F);
     __syncthreads();
     masked_queue_loop<kScatterBlock>(
         n, mask + (int64_t)__popc(~tm.lists & ((1u << l) - 1u)) * mask_stride(n), tile_bit(tm, l, tr.first), queue,

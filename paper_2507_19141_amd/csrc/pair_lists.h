@@ -273,9 +273,9 @@ struct TileRows {
 // 16, no more than fit, and no more rows in all than the tile's expected share of the 8 n
 // pairs (clearing and summing the copies would cost more than the retries).
 template <typename G, int F>
-__device__ __forceinline__ void set_copies(TileRows& r, int tiles, int n) {
+__device__ __forceinline__ void set_copies(TileRows& r, int tiles, int64_t n) {
     r.stride = r.cnt * F + 2u;  // a row's copies lie in different banks
-    const int64_t share = (int64_t)n * 8 / tiles;
+    const int64_t share = n * 8 / tiles;
     r.copies = 1u;
     while (r.copies < 16u && 2u * r.copies * r.stride * sizeof(G) <= (uint32_t)kTileBytes &&
            (int64_t)(2u * r.copies * r.cnt) <= share)
@@ -296,6 +296,15 @@ __device__ __forceinline__ TileRows tile_rows(const DevGrid& g, const TileMap& t
         r.cnt = min(1u << tm.tile_shift[l], (uint32_t)tm.level_rows[l] - r.first);
     }
     return r;
+}
+
+// Zero the first `values` values of the tile (whose buffer is a whole number of 16-byte
+// units).
+template <int BLOCK, typename G>
+__device__ __forceinline__ void zero_tile(G* tile, uint32_t values) {
+    uint4* t = reinterpret_cast<uint4*>(tile);
+    const uint32_t quads = (values * (uint32_t)sizeof(G) + 15u) / 16u;
+    for (uint32_t i = threadIdx.x; i < quads; i += BLOCK) t[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // put(i, at) for every value i < cnt F of the tile held in LDS; at: its index in the

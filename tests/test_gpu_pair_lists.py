@@ -8,7 +8,7 @@ import pytest
 
 from oracle import hash4d_oracle as O
 from paper_2507_19141_amd import _lib, synth
-from tests.util import RTOL_GRAD, needs_gpu, scaled_close
+from tests.util import RTOL_GRAD, mlp_backward_scale, needs_gpu, scaled_close
 
 # name: (F, space resolutions, time resolutions, T)
 GRIDS = {
@@ -154,3 +154,50 @@ def test_static_workspace_takes_what_it_took(case):
     for n in {1, 100, 4096, 60_000, lo // 3, lo - 1, lo}:
         if 1 <= n <= lo:
             assert _lib.hash4d_encode_backward_workspace_bytes(lg, n) <= 64 << 20, n
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("F,names,ns", [(2, ("loose", "modulo", "dense"), (2049, 1, 4100)), (8, ("mixed", "masks"), (700, 300)),
+                                        (1, ("loose_f1",), (5000,))], ids=["f2", "f8", "f1"])
+@pytest.mark.parametrize("zero", [False, True], ids=["accumulate", "zero_grads"])
+def test_batched_scatter_over_segments(F, names, ns, zero):
+    # a scene's timestamps are one run of chunks; with ZERO_GRADS every gradient is written
+    needs_gpu()
+    import torch
+    L = max(2, 8 // F)          # a decoder input of 8 or 16
+    scenes, descs = [], []
+    for i, (name, n) in enumerate(zip(names, ns)):
+        f, rs, rt, T = GRIDS[name]
+        rs, rt = (rs * L)[:L], (rt * L)[:L]
+        og, lg = O.make_grid(L, F, rs, rt, T), _lib.h4d_grid_init(L, F, rs, rt, T)
+        rng, x = _inputs(n, 90 + i, i == 1)
+        x = np.clip(np.nan_to_num(x), 0, 1).astype(np.float32)
+        times = [0.0, 1.0 / 3, 1.0][: 3 - i % 2]
+        table = synth.table_init(og.E, F, rng)
+        params = synth.decoder_params(L * F, rng)
+        gd = synth.upstream(n * len(times), 10, rng).reshape(len(times), n, 10)
+        init = float("nan") if zero else 0.0
+        s = {"og": og, "x": x, "times": times, "table": table, "params": params, "gd": gd,
+             "xyz": _dev(x), "table_d": _dev(table), "params_d": _dev(params), "gd_d": _dev(gd),
+             "feat": torch.empty((len(times), L, n, F), device="cuda"),
+             "delta": torch.empty((len(times), n, 10), device="cuda"),
+             "d_table": torch.full((og.E, F), init, device="cuda"),
+             "d_params": torch.full((params.size,), init, device="cuda")}
+        scenes.append(s)
+        descs.append(_lib.scene_desc(lg, n, s["xyz"], times, s["table_d"], s["params_d"], s["feat"], s["delta"],
+                                     s["gd_d"], s["d_table"], s["d_params"]))
+    flags = _lib.PLAN_GRAPH | (_lib.PLAN_ZERO_GRADS if zero else 0)
+    plan = _lib.BatchedPlan(descs, _lib.mlp_shape(L * F), _lib.F32, 1.0, flags)
+    plan.run()
+    torch.cuda.synchronize()
+    for i, s in enumerate(scenes):
+        ref, scale = np.zeros((s["og"].E, F)), np.zeros((s["og"].E, F))
+        for k, t in enumerate(s["times"]):
+            xt = s["x"].copy()
+            xt[:, 3] = np.float32(t)
+            f_ref = O.encode(xt, s["table"], s["og"])
+            ref += O.deform_backward(xt, s["table"], s["og"], s["params"], s["gd"][k])[0]
+            sf, _ = mlp_backward_scale(s["params"], f_ref, s["gd"][k])
+            scale += O.encode_backward(xt, sf, s["og"])
+        scaled_close(s["d_table"].cpu().numpy(), ref, scale, RTOL_GRAD, f"scene {i}")
+    plan.destroy()
