@@ -110,10 +110,10 @@ struct BTile {
     uint32_t tile;       // in its level
 };
 
-__global__ __launch_bounds__(kPreBlock) void k_bpre(const BSeg* __restrict__ segs, const DevGrid* __restrict__ grids,
+__global__ __launch_bounds__(pre_block(false)) __attribute__((amdgpu_waves_per_eu(pre_waves_per_eu(false)))) void k_bpre(const BSeg* __restrict__ segs, const DevGrid* __restrict__ grids,
                                                     const TileMap* __restrict__ tms,
                                                     const BScene* __restrict__ scenes) {
-    __shared__ __align__(16) PreShared sh;
+    __shared__ __align__(16) PreShared<false> sh;
     const BSeg sg = segs[blockIdx.z];
     const int l = blockIdx.y, chunk = blockIdx.x;
     const DevGrid& g = grids[sg.scene];
@@ -418,7 +418,7 @@ static hipError_t launch_bscatter(const h4d_batched_plan& p, float scale, hipStr
     if (p.ntiles == 0) return hipSuccess;
     hipError_t e = hipSuccess;
     if (p.max_chunks > 0) {
-        hipLaunchKernelGGL(k_bpre, dim3((unsigned)p.max_chunks, (unsigned)p.max_L, (unsigned)p.nseg), dim3(kPreBlock), 0,
+        hipLaunchKernelGGL(k_bpre, dim3((unsigned)p.max_chunks, (unsigned)p.max_L, (unsigned)p.nseg), dim3(pre_block(false)), 0,
                            st, p.segs, p.grids, p.tms, p.bscenes);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

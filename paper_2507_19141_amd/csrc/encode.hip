@@ -61,11 +61,11 @@ __global__ __launch_bounds__(kEncodeBlock) void k_encode(DevGrid g, const TT* __
 
 // The pre-pass.  Grid (chunks of the level with the most, L).
 template <bool PAIR>
-__global__ __launch_bounds__(kPreBlock) void k_tile_pre(DevGrid g, TileMap tm, const float4* __restrict__ xyzt,
+__global__ __launch_bounds__(pre_block(PAIR)) __attribute__((amdgpu_waves_per_eu(pre_waves_per_eu(PAIR)))) void k_tile_pre(DevGrid g, TileMap tm, const float4* __restrict__ xyzt,
                                                         const float4* __restrict__ eps, int n,
                                                         uint32_t* __restrict__ mask, uint16_t* __restrict__ lists,
                                                         uint32_t* __restrict__ heads) {
-    __shared__ __align__(16) PreShared sh;
+    __shared__ __align__(16) PreShared<PAIR> sh;
     const int l = blockIdx.y, nchunks = pre_chunks(n, pre_chunk_log(tm, l, PAIR));
     if ((int)blockIdx.x >= nchunks) return;
     tile_pre<PAIR>(g, tm, l, (int)blockIdx.x, 0, nchunks, n,
@@ -561,7 +561,7 @@ static hipError_t tiled_g(const DevGrid& g, const int64_t* level_rows, const flo
                         reinterpret_cast<uint32_t*>(ws + w.masks)};
     int chunks = 0;
     for (int l = 0; l < g.L; ++l) chunks = std::max(chunks, pre_chunks(n, pre_chunk_log(tm, l, PAIR)));
-    hipLaunchKernelGGL(k_tile_pre<PAIR>, dim3((unsigned)chunks, (unsigned)g.L), dim3(kPreBlock), 0, s, g, tm,
+    hipLaunchKernelGGL(k_tile_pre<PAIR>, dim3((unsigned)chunks, (unsigned)g.L), dim3(pre_block(PAIR)), 0, s, g, tm,
                        reinterpret_cast<const float4*>(xyzt), reinterpret_cast<const float4*>(eps), n, b.mask,
                        b.lists, b.heads);
     const hipError_t e = hipGetLastError();

@@ -83,11 +83,16 @@ __device__ __forceinline__ uint32_t corner_tiles(const DevGrid& g, const TileMap
     return apart;
 }
 
-// ---- the pre-pass: one workgroup of kPreBlock threads sorts one chunk of one level ----
-constexpr int kPreBlock = 512;
-constexpr int kPreWaves = kPreBlock / 64;
+// ---- the pre-pass: one workgroup sorts one chunk of one level ----
+// 1024 threads at eight wavefronts per SIMD (64 registers) with one corner set per query
+// (512: 36 against 35 us for 200k queries); two sets need more registers, where 512
+// threads are faster (70 against 91 us).
+constexpr int pre_block(bool pair) { return pair ? 512 : 1024; }
+constexpr int pre_waves_per_eu(bool pair) { return pair ? 4 : 8; }
 
+template <bool PAIR>
 struct PreShared {
+    static constexpr int kPreWaves = pre_block(PAIR) / 64;
     union {
         uint8_t tiles[kListEntries];     // tile of every entry, query by query
         uint16_t sorted[kListEntries];
@@ -116,10 +121,12 @@ __device__ __forceinline__ float4 perturbed(float4 x, float4 e) {
 template <bool PAIR, bool LOOSE, typename Pos>
 __device__ __forceinline__ void tile_pre_lists(const DevGrid& g, const TileMap& tm, int l, int chunk, int n, Pos pos,
                                                uint16_t* __restrict__ region, uint32_t* __restrict__ heads,
-                                               int nchunks, PreShared& sh) {
+                                               int nchunks, PreShared<PAIR>& sh) {
+    constexpr int kPreBlock = pre_block(PAIR), kPreWaves = kPreBlock / 64;
     constexpr int kSets = (PAIR ? 2 : 1) * (LOOSE ? 2 : 1);
-    constexpr int kPer = (1 << list_chunk_log(PAIR, LOOSE)) / kPreBlock;  // queries per thread, 64 apart
-    static_assert(kPer >= 1 && kPer * kPreBlock * 8 * kSets == kListEntries, "a chunk's entries fill its region");
+    constexpr int kChunk = 1 << list_chunk_log(PAIR, LOOSE), kWaveQueries = kChunk / kPreWaves;
+    constexpr int kPer = kWaveQueries / 64;  // queries per thread, 64 apart
+    static_assert(kPer >= 1 && kChunk * 8 * kSets == kListEntries, "a chunk's entries fill its region");
     constexpr int kWaveEntries = kListEntries / kPreWaves, kEach = kWaveEntries / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int P = tm.tile_start[l + 1] - tm.tile_start[l];
@@ -127,10 +134,10 @@ __device__ __forceinline__ void tile_pre_lists(const DevGrid& g, const TileMap& 
     for (int i = threadIdx.x; i < kPreWaves * P; i += kPreBlock) sh.cnt[i] = 0u;
     float4 xs[kPer], xp[kPer];  // every load in flight before the first use
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) pos(min(q0 + wave * (64 * kPer) + i * 64 + lane, n - 1), xs[i], xp[i]);
+    for (int i = 0; i < kPer; ++i) pos(min(q0 + wave * kWaveQueries + i * 64 + lane, n - 1), xs[i], xp[i]);
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        const int ql = wave * (64 * kPer) + i * 64 + lane;
+        const int ql = wave * kWaveQueries + i * 64 + lane;
         uint32_t t[kSets][2], v[kSets];
         const uint32_t all = q0 + ql < n ? 0xffu : 0u;
         const Cell c0 = level_cell(g, l, xs[i]);
@@ -154,16 +161,20 @@ __device__ __forceinline__ void tile_pre_lists(const DevGrid& g, const TileMap& 
     __syncthreads();
     uint32_t* mine = sh.cnt + wave * P;
     uint32_t key[kEach];  // tile << 16 | rank; a wavefront has at most 2^11 entries
-#pragma unroll
-    for (int j = 0; j < kEach; ++j) {
+    auto count = [&](int j) {
         const int k = wave * kWaveEntries + j * 64 + lane;
-        bool in;
-        if constexpr (kSets > 1) in = (sh.valid[k >> 3] >> (k & 7)) & 1u;
-        else in = q0 + (k >> 3) < n;
-        key[j] = ~0u;
-        if (in) {
-            const uint32_t t = sh.tiles[k];
-            key[j] = (t << 16) | atomicAdd(&mine[t], 1u);
+        const uint32_t t = sh.tiles[k];
+        key[j] = (t << 16) | atomicAdd(&mine[t], 1u);
+    };
+    if (kSets == 1 && q0 + kChunk <= n) {  // every entry exists
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) count(j);
+    } else {
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            const int k = wave * kWaveEntries + j * 64 + lane;
+            key[j] = ~0u;
+            if (kSets > 1 ? (sh.valid[k >> 3] >> (k & 7)) & 1u : q0 + (k >> 3) < n) count(j);
         }
     }
     __syncthreads();
@@ -229,7 +240,7 @@ __device__ __forceinline__ void tile_pre_lists(const DevGrid& g, const TileMap& 
 template <bool PAIR, typename Pos>
 __device__ __forceinline__ void tile_pre(const DevGrid& g, const TileMap& tm, int l, int chunk, int chunk0,
                                          int nchunks, int n, Pos pos, uint32_t* __restrict__ mask,
-                                         uint16_t* __restrict__ lists, uint32_t* __restrict__ heads, PreShared& sh) {
+                                         uint16_t* __restrict__ lists, uint32_t* __restrict__ heads, PreShared<PAIR>& sh) {
     if ((tm.lists >> l) & 1u) {
         uint16_t* region = lists + (int64_t)(tm.list_region[l] + chunk0 + chunk) * kListEntries;
         uint32_t* h = heads + tm.list_head[l] + chunk0;
@@ -238,10 +249,8 @@ __device__ __forceinline__ void tile_pre(const DevGrid& g, const TileMap& tm, in
         return;
     }
     uint32_t* lm = mask + (int64_t)__popc(~tm.lists & ((1u << l) - 1u)) * mask_stride(n);
-    constexpr int kPer = kMaskChunk / kPreBlock;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int q = chunk * kMaskChunk + i * kPreBlock + (int)threadIdx.x;
+    for (int i = 0; i < kMaskChunk / pre_block(PAIR); ++i) {
+        const int q = chunk * kMaskChunk + i * pre_block(PAIR) + (int)threadIdx.x;
         if (q >= n) return;
         float4 x, xp;
         pos(q, x, xp);
