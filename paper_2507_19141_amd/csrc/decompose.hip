@@ -24,32 +24,74 @@ __device__ __forceinline__ uint32_t motion_key(const float* __restrict__ dp, int
     return __float_as_uint(s);
 }
 
-// Select state in the workspace: [0] prefix of the key found so far, [1] rank still
-// sought among the keys with that prefix (ascending, 0-based), [2] 1 when there is
-// no threshold (every Gaussian dynamic), [3] the number of dynamic Gaussians.
-struct SelectState {
-    uint32_t prefix, rank, all, n_dyn;
-};
+// A pass reads 12 bytes per Gaussian, so the launches were what the split took its time
+// for: 11 of them, 40 us for 200k Gaussians.  Now each kernel starts with the reduction
+// that its predecessor left, every workgroup for itself (the pick of a digit from 256
+// bins; the sums of the block counts): 7 launches, 29 us.  Letting the workgroup that
+// ends a pass last pick its digit took 8.5 us per pass, against 4.0 + 2.3 in two launches:
+// every workgroup's release writes its L2 back.
 
-__global__ __launch_bounds__(kDecBlock) void k_select_init(SelectState* st, uint32_t* hist, int64_t n, int64_t n_d) {
-    if (threadIdx.x == 0) {
-        st->prefix = 0u;
-        st->all = n_d >= n ? 1u : 0u;
-        st->rank = n_d >= n ? 0u : (uint32_t)(n - n_d - 1);  // the (n_d + 1)-th largest, counted from below
-        st->n_dyn = 0u;
+// What a pass knows of the sought key: its digits so far, the rank still sought among the
+// keys with that prefix (ascending, 0-based), and 1 in `all` when there is no threshold
+// (every Gaussian dynamic).  State p is the one before digit p, state kDigits the threshold.
+struct SelectState {
+    uint32_t prefix, rank, all, pad;
+};
+constexpr int kDigits = 4;
+
+__global__ __launch_bounds__(kDecBlock) void k_select_init(SelectState* st, uint32_t* hist, int words, int64_t n,
+                                                           int64_t n_d) {
+    if (threadIdx.x == 0)  // the (n_d + 1)-th largest, counted from below
+        st[0] = SelectState{0u, n_d >= n ? 0u : (uint32_t)(n - n_d - 1), n_d >= n ? 1u : 0u, 0u};
+    for (int j = threadIdx.x; j < words; j += kDecBlock) hist[j] = 0u;
+}
+
+// State p (> 0) from the one before and that digit's histogram: the bucket holding the
+// sought rank extends the prefix.  Called by all threads; workgroup 0 stores the state
+// for the next launch.
+__device__ __forceinline__ SelectState pick_digit(SelectState* __restrict__ st, const uint32_t* __restrict__ hist,
+                                                  int p) {
+    __shared__ uint32_t wsum[kDecBlock / 64];
+    __shared__ SelectState found;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const SelectState cur = st[p - 1];
+    const uint32_t v = hist[threadIdx.x];
+    uint32_t c = v;  // inclusive scan
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t a = (uint32_t)__shfl_up((int)c, d, 64);
+        if (lane >= d) c += a;
     }
+    if (lane == 63) wsum[wave] = c;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) c += wsum[w];
+    if (c - v <= cur.rank && cur.rank < c) {  // exactly one bucket: the rank exists
+        found = SelectState{cur.prefix | (uint32_t)threadIdx.x << (32 - 8 * p), cur.rank - (c - v), cur.all, 0u};
+        if (blockIdx.x == 0) st[p] = found;
+    }
+    __syncthreads();
+    return found;
+}
+
+// The pick as a launch of its own, where the workspace holds one histogram only: it is
+// cleared for the next digit.
+__global__ __launch_bounds__(kDecBlock) void k_select_pick(SelectState* __restrict__ st, uint32_t* __restrict__ hist,
+                                                           int p) {
+    pick_digit(st, hist, p);
     hist[threadIdx.x] = 0u;
 }
 
-// Histogram of digit `shift` over the keys whose higher digits equal the prefix.
+// Histogram of digit p over the keys whose higher digits equal the prefix; state p is
+// picked from `prev`, the last digit's histogram, unless that is NULL.
 __global__ __launch_bounds__(kDecBlock) void k_select_hist(const float* __restrict__ dp, int64_t n,
-                                                           const SelectState* __restrict__ st, int shift,
+                                                           SelectState* __restrict__ st, int p,
+                                                           const uint32_t* __restrict__ prev,
                                                            uint32_t* __restrict__ hist) {
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0u;
+    const uint32_t prefix = prev ? pick_digit(st, prev, p).prefix : st[p].prefix;
     __syncthreads();
-    const uint32_t prefix = st->prefix;
-    const uint32_t hi_mask = shift == 24 ? 0u : ~((1u << (shift + 8)) - 1u);
+    const int shift = 24 - 8 * p;
+    const uint32_t hi_mask = p == 0 ? 0u : ~((1u << (shift + 8)) - 1u);
     for (int64_t i = (int64_t)blockIdx.x * kDecBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kDecBlock) {
         const uint32_t k = motion_key(dp, i);
         if ((k & hi_mask) == prefix) atomicAdd(&h[(k >> shift) & 255u], 1u);
@@ -58,48 +100,31 @@ __global__ __launch_bounds__(kDecBlock) void k_select_hist(const float* __restri
     if (h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
 }
 
-// Pick the bucket holding the sought rank, extend the prefix, clear the histogram.
-__global__ __launch_bounds__(256) void k_select_pick(SelectState* st, uint32_t* hist, int shift) {
-    __shared__ uint32_t c[256];
-    const uint32_t v = hist[threadIdx.x];
-    c[threadIdx.x] = v;
-    __syncthreads();
-    for (int d = 1; d < 256; d <<= 1) {  // inclusive scan
-        const uint32_t a = threadIdx.x >= (unsigned)d ? c[threadIdx.x - d] : 0u;
-        __syncthreads();
-        c[threadIdx.x] += a;
-        __syncthreads();
-    }
-    const uint32_t rank = st->rank;
-    const uint32_t below = c[threadIdx.x] - v;
-    __syncthreads();
-    if (below <= rank && rank < c[threadIdx.x]) {  // exactly one bucket when the rank exists
-        st->prefix |= (uint32_t)threadIdx.x << shift;
-        st->rank = rank - below;
-    }
-    hist[threadIdx.x] = 0u;
-}
-
 __device__ __forceinline__ bool is_dynamic(uint32_t key, const SelectState& s) { return s.all || key > s.prefix; }
 
-// Per block: dynamic count and the sum of the static magnitudes (FP32 norm).
-__global__ __launch_bounds__(kDecBlock) void k_split_count(const float* __restrict__ dp, int64_t n,
-                                                           const SelectState* __restrict__ st,
+// Per workgroup: dynamic count and the sum of the static magnitudes (FP32 norm) of `per`
+// runs of kDecBlock Gaussians.  The threshold is picked from `prev` unless that is NULL.
+__global__ __launch_bounds__(kDecBlock) void k_split_count(const float* __restrict__ dp, int64_t n, int per,
+                                                           SelectState* __restrict__ st,
+                                                           const uint32_t* __restrict__ prev,
                                                            uint32_t* __restrict__ counts, float* __restrict__ sums) {
     __shared__ uint32_t wc[kDecBlock / 64];
     __shared__ float ws[kDecBlock / 64];
-    const SelectState s = *st;
-    const int64_t i = (int64_t)blockIdx.x * kDecBlock + threadIdx.x;
-    bool dyn = false;
+    const SelectState s = prev ? pick_digit(st, prev, kDigits) : st[kDigits];
+    uint32_t c = 0u;
     float mag = 0.f;
-    if (i < n) {
-        dyn = is_dynamic(motion_key(dp, i), s);
-        if (!dyn) {
-            const float x = dp[3 * i], y = dp[3 * i + 1], z = dp[3 * i + 2];
-            mag = sqrtf(x * x + y * y + z * z);
+    for (int r = 0; r < per; ++r) {
+        const int64_t i = ((int64_t)blockIdx.x * per + r) * kDecBlock + threadIdx.x;
+        bool dyn = false;
+        if (i < n) {
+            dyn = is_dynamic(motion_key(dp, i), s);
+            if (!dyn) {
+                const float x = dp[3 * i], y = dp[3 * i + 1], z = dp[3 * i + 2];
+                mag += sqrtf(x * x + y * y + z * z);
+            }
         }
+        c += (uint32_t)__popcll(__ballot(dyn));
     }
-    const uint32_t c = (uint32_t)__popcll(__ballot(dyn));
     for (int o = 32; o > 0; o >>= 1) mag += __shfl_xor(mag, o, 64);
     if ((threadIdx.x & 63) == 0) {
         wc[threadIdx.x >> 6] = c;
@@ -118,108 +143,134 @@ __global__ __launch_bounds__(kDecBlock) void k_split_count(const float* __restri
     }
 }
 
-// One workgroup: block offsets (exclusive scan of the counts), the dynamic total,
-// and the static constraint added to *loss with the block sums in a fixed order.
-__global__ __launch_bounds__(1024) void k_split_scan(const uint32_t* __restrict__ counts,
-                                                     const float* __restrict__ sums, int nb, int64_t n,
-                                                     SelectState* st, uint32_t* __restrict__ offsets,
-                                                     int32_t* __restrict__ n_dynamic, float lam_s,
-                                                     float* __restrict__ loss) {
-    __shared__ uint32_t part[1024];
-    __shared__ float fpart[1024];
-    const int per = (nb + 1023) / 1024;
-    const int b = threadIdx.x * per, e = min(b + per, nb);
-    uint32_t c = 0;
-    float f = 0.f;
-    for (int i = b; i < e; ++i) {
-        c += counts[i];
-        f += sums[i];
-    }
-    part[threadIdx.x] = c;
-    fpart[threadIdx.x] = f;
-    __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {
-        const uint32_t v = threadIdx.x >= (unsigned)d ? part[threadIdx.x - d] : 0u;
-        __syncthreads();
-        part[threadIdx.x] += v;
-        __syncthreads();
-    }
-    uint32_t run = part[threadIdx.x] - c;
-    for (int i = b; i < e; ++i) {
-        offsets[i] = run;
-        run += counts[i];
-    }
-    if (threadIdx.x == 0) {
-        float total = 0.f;
-        for (int i = 0; i < 1024; ++i) total += fpart[i];
-        const uint32_t n_dyn = part[1023];
-        st->n_dyn = n_dyn;
-        if (n_dynamic) *n_dynamic = (int32_t)n_dyn;
-        const int64_t n_s = n - (int64_t)n_dyn;
-        if (loss && n_s > 0) *loss += lam_s / (float)n_s * total;
-    }
-}
-
 // Dynamic: index written at its ascending position.  Static: the constraint's gradient.
-__global__ __launch_bounds__(kDecBlock) void k_split_write(const float* __restrict__ dp, int64_t n,
+// Each workgroup adds up the counts before its own and all of them (integers: every one
+// gets the same total); workgroup 0 adds the static constraint to *loss, the sums in a
+// fixed order and in 64 bits.
+__global__ __launch_bounds__(kDecBlock) void k_split_write(const float* __restrict__ dp, int64_t n, int per,
                                                            const SelectState* __restrict__ st,
-                                                           const uint32_t* __restrict__ offsets, float lam_s,
+                                                           const uint32_t* __restrict__ counts,
+                                                           const float* __restrict__ sums, float lam_s,
                                                            int32_t* __restrict__ dyn_idx,
-                                                           uint8_t* __restrict__ is_dyn, float* __restrict__ d_dp) {
-    __shared__ uint32_t wc[kDecBlock / 64];
-    const SelectState s = *st;
-    const int64_t i = (int64_t)blockIdx.x * kDecBlock + threadIdx.x;
-    const bool dyn = i < n && is_dynamic(motion_key(dp, i), s);
-    const uint64_t bal = __ballot(dyn);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) wc[wave] = (uint32_t)__popcll(bal);
+                                                           int32_t* __restrict__ n_dynamic,
+                                                           uint8_t* __restrict__ is_dyn, float* __restrict__ loss,
+                                                           float* __restrict__ d_dp) {
+    constexpr int kWaves = kDecBlock / 64;
+    __shared__ uint32_t wb[kWaves], wt[kWaves], wc[kWaves];
+    __shared__ double wf[kWaves];
+    const SelectState s = st[kDigits];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nb = (int)gridDim.x, b = (int)blockIdx.x;
+    uint32_t before = 0u, total = 0u;
+    for (int j = threadIdx.x; j < nb; j += kDecBlock) {
+        const uint32_t c = counts[j];
+        total += c;
+        if (j < b) before += c;
+    }
+    double f = 0.0;
+    if (b == 0 && loss)
+        for (int j = threadIdx.x; j < nb; j += kDecBlock) f += (double)sums[j];
+    for (int o = 32; o > 0; o >>= 1) {
+        before += (uint32_t)__shfl_xor((int)before, o, 64);
+        total += (uint32_t)__shfl_xor((int)total, o, 64);
+        if (b == 0) f += __shfl_xor(f, o, 64);
+    }
+    if (lane == 0) {
+        wb[wave] = before;
+        wt[wave] = total;
+        wf[wave] = f;
+    }
     __syncthreads();
-    if (i >= n) return;
-    if (is_dyn) is_dyn[i] = dyn ? 1 : 0;
-    if (dyn) {
-        uint32_t pos = offsets[blockIdx.x];
-        for (int w = 0; w < wave; ++w) pos += wc[w];
-        pos += (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-        if (dyn_idx) dyn_idx[pos] = (int32_t)i;
-    } else if (d_dp) {
-        const int64_t n_s = n - (int64_t)s.n_dyn;
-        const float x = dp[3 * i], y = dp[3 * i + 1], z = dp[3 * i + 2];
-        const float mag = sqrtf(x * x + y * y + z * z);
-        if (mag > 0.f) {
-            const float c = lam_s / (float)n_s / mag;
-            d_dp[3 * i] += c * x;
-            d_dp[3 * i + 1] += c * y;
-            d_dp[3 * i + 2] += c * z;
+    uint32_t pos0 = 0u, n_dyn = 0u;
+    for (int w = 0; w < kWaves; ++w) {
+        pos0 += wb[w];
+        n_dyn += wt[w];
+    }
+    const int64_t n_s = n - (int64_t)n_dyn;
+    if (b == 0 && threadIdx.x == 0) {
+        if (n_dynamic) *n_dynamic = (int32_t)n_dyn;
+        if (loss && n_s > 0) *loss += lam_s / (float)n_s * (float)(((wf[0] + wf[1]) + wf[2]) + wf[3]);
+    }
+    for (int r = 0; r < per; ++r) {
+        const int64_t i = ((int64_t)b * per + r) * kDecBlock + threadIdx.x;
+        const bool dyn = i < n && is_dynamic(motion_key(dp, i), s);
+        const uint64_t bal = __ballot(dyn);
+        if (r > 0) __syncthreads();  // the last run's counts are read
+        if (lane == 0) wc[wave] = (uint32_t)__popcll(bal);
+        __syncthreads();
+        uint32_t pos = pos0 + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < wave) pos += wc[w];
+            pos0 += wc[w];
+        }
+        if (i >= n) continue;
+        if (is_dyn) is_dyn[i] = dyn ? 1 : 0;
+        if (dyn) {
+            if (dyn_idx) dyn_idx[pos] = (int32_t)i;
+        } else if (d_dp) {
+            const float x = dp[3 * i], y = dp[3 * i + 1], z = dp[3 * i + 2];
+            const float mag = sqrtf(x * x + y * y + z * z);
+            if (mag > 0.f) {
+                const float c = lam_s / (float)n_s / mag;
+                d_dp[3 * i] += c * x;
+                d_dp[3 * i + 1] += c * y;
+                d_dp[3 * i + 2] += c * z;
+            }
         }
     }
 }
 
+// 256 bytes of states, and words for one histogram and three per kDecBlock Gaussians.
 size_t decompose_workspace_bytes(int64_t n) {
     const int64_t nb = (n + kDecBlock - 1) / kDecBlock;
     return 256 + 256 * 4 + (size_t)nb * 4 * 3;
 }
 
+// What lies in the workspace: histograms, and the counts and sums of the split's
+// workgroups, each of which covers `per` runs of kDecBlock Gaussians.
+struct SplitPlan {
+    int hists;   // 1, or kDigits from 256 runs on, where they fit
+    int blocks, per;
+    int counts;  // word of the first count; the sums follow the counts
+};
+static SplitPlan split_plan(int64_t n) {
+    const int64_t runs = (n + kDecBlock - 1) / kDecBlock;
+    constexpr int kHist = 256;
+    SplitPlan p;
+    p.hists = runs >= 256 ? kDigits : 1;
+    // every workgroup of k_split_write reads all the counts, so at most 2048 of them; below
+    // 3 * 256 runs the counts lie over the histograms of the digits before the last
+    const bool over = p.hists == kDigits && runs < 3 * kHist;
+    const int64_t most = over ? (kDigits - 1) * kHist / 2 : 2048;
+    p.per = (int)((runs + most - 1) / most);
+    p.blocks = (int)((runs + p.per - 1) / p.per);
+    p.counts = over ? 0 : p.hists * kHist;
+    return p;
+}
+
 hipError_t launch_decompose(const float* dp, int64_t n, double k_percent, float lam_s, int32_t* dyn_idx,
                             int32_t* n_dynamic, uint8_t* is_dyn, float* loss, float* d_dp, void* ws, hipStream_t s) {
-    char* w = static_cast<char*>(ws);
-    SelectState* st = reinterpret_cast<SelectState*>(w);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(w + 256);
-    const int64_t nb = (n + kDecBlock - 1) / kDecBlock;
-    uint32_t* counts = hist + 256;
-    float* sums = reinterpret_cast<float*>(counts + nb);
-    uint32_t* offsets = reinterpret_cast<uint32_t*>(sums + nb);
+    const SplitPlan pl = split_plan(n);
+    SelectState* st = static_cast<SelectState*>(ws);
+    uint32_t* hist = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + 256);
+    uint32_t* counts = hist + pl.counts;
+    float* sums = reinterpret_cast<float*>(counts + pl.blocks);
     const int64_t n_d = (int64_t)floor(k_percent / 100.0 * (double)n);
-    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(256), 0, s, st, hist, n, n_d);
-    const int hist_blocks = (int)std::min<int64_t>(nb, 256);  // 256 device atomics per block and pass
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(k_select_hist, dim3(hist_blocks), dim3(kDecBlock), 0, s, dp, n, st, shift, hist);
-        hipLaunchKernelGGL(k_select_pick, dim3(1), dim3(256), 0, s, st, hist, shift);
+    hipLaunchKernelGGL(k_select_init, dim3(1), dim3(kDecBlock), 0, s, st, hist, pl.hists * 256, n, n_d);
+    // 256 device atomics per workgroup and pass
+    const int hist_blocks = (int)std::min<int64_t>((n + kDecBlock - 1) / kDecBlock, 256);
+    const uint32_t* prev = nullptr;
+    for (int p = 0; p < kDigits; ++p) {
+        uint32_t* h = pl.hists == 1 ? hist : hist + p * 256;
+        hipLaunchKernelGGL(k_select_hist, dim3(hist_blocks), dim3(kDecBlock), 0, s, dp, n, st, p, prev, h);
+        if (pl.hists == 1)
+            hipLaunchKernelGGL(k_select_pick, dim3(1), dim3(kDecBlock), 0, s, st, h, p + 1);
+        else
+            prev = h;
     }
-    hipLaunchKernelGGL(k_split_count, dim3((unsigned)nb), dim3(kDecBlock), 0, s, dp, n, st, counts, sums);
-    hipLaunchKernelGGL(k_split_scan, dim3(1), dim3(1024), 0, s, counts, sums, (int)nb, n, st, offsets, n_dynamic,
-                       lam_s, loss);
-    hipLaunchKernelGGL(k_split_write, dim3((unsigned)nb), dim3(kDecBlock), 0, s, dp, n, st, offsets, lam_s, dyn_idx,
-                       is_dyn, d_dp);
+    hipLaunchKernelGGL(k_split_count, dim3((unsigned)pl.blocks), dim3(kDecBlock), 0, s, dp, n, pl.per, st, prev, counts,
+                       sums);
+    hipLaunchKernelGGL(k_split_write, dim3((unsigned)pl.blocks), dim3(kDecBlock), 0, s, dp, n, pl.per, st, counts, sums,
+                       lam_s, dyn_idx, n_dynamic, is_dyn, loss, d_dp);
     return hipGetLastError();
 }
 

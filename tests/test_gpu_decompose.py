@@ -111,3 +111,23 @@ def test_front_end_chain():
     idx, _, _, _ = run(dph, 10.0)
     assert np.array_equal(idx.astype(np.int64), O.decompose(dph, 10.0)[0])
     assert len(idx) == 5000
+
+
+# The sizes at which the workspace starts to hold one histogram per digit (65281), the
+# workgroups cover more than one run of 256 (98305), the counts move behind the histograms
+# (196353) and the workgroups grow again (524289); the magnitudes share their leading
+# digits, so that the threshold is decided in the last ones.
+@pytest.mark.parametrize("n", [65_280, 65_281, 98_304, 98_305, 196_352, 196_353, 524_289])
+@pytest.mark.parametrize("k", [0.0, 37.0, 100.0])
+def test_split_at_the_plan_edges(n, k):
+    rng = np.random.default_rng(n)
+    dp = (1.0 + 2e-4 * rng.random((n, 3))).astype(np.float32)
+    dp[n // 3:n // 2] = dp[n // 3]
+    idx, flag, loss, grad = run(dp, k, 0.7)
+    ridx, rloss, rgrad = O.decompose(dp, k, 0.7)
+    assert np.array_equal(idx.astype(np.int64), ridx)
+    want = np.zeros(n, np.uint8)
+    want[ridx] = 1
+    assert np.array_equal(flag, want)
+    assert abs(loss - rloss) <= RTOL_F32 * abs(rloss)
+    scaled_close(grad, rgrad, 0.7 / max(n - len(ridx), 1) * np.ones_like(rgrad), RTOL_F32, "d_dp")
