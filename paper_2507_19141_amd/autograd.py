@@ -37,6 +37,14 @@ class DeformField:
         return lo
 
 
+def _written(shape, count, dtype, device) -> torch.Tensor:
+    """A tensor whose first `count` elements the caller writes; any others are zero."""
+    t = torch.empty(shape, dtype=dtype, device=device)
+    if t.numel() > count:
+        t.zero_()
+    return t
+
+
 class Hash4DDeform(torch.autograd.Function):
     @staticmethod
     def forward(ctx, xyzt, table, params, field: DeformField, scaler=None):
@@ -60,10 +68,10 @@ class Hash4DDeform(torch.autograd.Function):
         n = xyzt.shape[0]
         dev = xyzt.device
         S = scaler.scale if scaler is not None else 1.0
-        d_table = torch.zeros(ctx.table_shape, dtype=field.torch_dtype, device=dev)
-        d_params = torch.zeros(ctx.n_params, dtype=field.torch_dtype, device=dev)
         d_delta = d_delta.to(field.torch_dtype).contiguous()
         if not ctx.needs_input_grad[0]:
+            d_table = torch.zeros(ctx.table_shape, dtype=field.torch_dtype, device=dev)
+            d_params = torch.zeros(ctx.n_params, dtype=field.torch_dtype, device=dev)
             ws_bytes = _lib.hash4d_deform_workspace_bytes(g, m, field.dtype, n)
             ws = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=dev)
             _lib.hash4d_deform_backward(g, m, field.dtype, p_used, xyzt, n, feat, d_delta, S, 1.0 / S, d_table,
@@ -72,17 +80,22 @@ class Hash4DDeform(torch.autograd.Function):
         else:
             # the positions need their gradient too (the derivative of Eq. 9 with
             # respect to x): decoder backward, then the table scatter and the input
-            # gradient from the same (unscaled) feature gradient
-            LM = _lib.LEVEL_MAJOR
+            # gradient from the same (unscaled) feature gradient.  Both parameter gradients
+            # are written, not added to, so nothing is cleared first (11 us of fills, and
+            # the scatter's reads of what they wrote, for a 30 MB table and 50k queries);
+            # a table or parameter tensor with elements past the field's own keeps zeros there
+            LM, OW = _lib.LEVEL_MAJOR, _lib.LEVEL_MAJOR | _lib.GRAD_OVERWRITE
+            d_table = _written(ctx.table_shape, g.E * g.F, field.torch_dtype, dev)
+            d_params = _written(ctx.n_params, m.in_ * 64 + 64 + 64 * 64 + 64 + m.out * 65, field.torch_dtype, dev)
             d_feat = torch.empty((g.L, n, g.F), dtype=field.torch_dtype, device=dev)
             wb = _lib.deform_mlp_workspace_bytes(m, field.dtype, n)
             ws = torch.empty(max(wb, 1), dtype=torch.uint8, device=dev)
             _lib.deform_mlp_backward(m, field.dtype, p_used, feat, n, d_delta, S, 1.0 / S, d_feat, d_params, ws, wb,
-                                     LM, g.F)
+                                     OW, g.F)
             grad_dt = _lib.F64 if field.dtype == _lib.F64 else _lib.F32
             wb = _lib.hash4d_encode_backward_workspace_bytes(g, n)
             ws = torch.empty(max(wb, 1), dtype=torch.uint8, device=dev)
-            _lib.hash4d_encode_backward(g, grad_dt, xyzt, n, d_feat, 1.0, d_table, ws, wb, LM)
+            _lib.hash4d_encode_backward(g, grad_dt, xyzt, n, d_feat, 1.0, d_table, ws, wb, OW)
             d_xyzt = torch.zeros((n, 4), dtype=field.torch_dtype, device=dev)
             wb = _lib.hash4d_encode_backward_input_workspace_bytes(g, field.dtype, n)
             ws = torch.empty(max(wb, 1), dtype=torch.uint8, device=dev) if wb else None

@@ -252,3 +252,29 @@ def test_autograd_position_gradient_matches_oracle_chain():
     scaled_close(host(t.grad), O.encode_backward(x, rf, og), O.encode_backward(x, sf, og), RTOL_GRAD,
                  "autograd d_table (position path)")
     scaled_close(host(p.grad), rp, sp, RTOL_GRAD, "autograd d_params (position path)")
+
+
+@pytest.mark.parametrize("n", [0, 1, 517])
+def test_position_path_writes_every_gradient_element(n):
+    # the parameter gradients of the position path are written, not added to: elements
+    # past the field's own table and parameters, and all of them without a query, are zero
+    import torch
+    from paper_2507_19141_amd.autograd import Hash4DDeform
+    w, og, lg, x, table, params, gd, _ = smooth_case(max(n, 1), 204)
+    more_t = np.concatenate([table, np.ones((3, w.F), np.float32)])
+    more_p = np.concatenate([params, np.ones(5, np.float32)])
+    for _ in range(2):   # the second time in memory that held gradients
+        xd, t, p = (dev(a).requires_grad_(True) for a in (x[:n], more_t, more_p))
+        delta = Hash4DDeform.apply(xd, t, p, field(lg, w.n_in, _lib.F32), None)
+        gx, gt, gp = torch.autograd.grad(delta, (xd, t, p), dev(gd[:n]))
+        assert gx.shape == (n, 4)
+        assert not host(gt)[og.E:].any() and not host(gp)[params.size:].any()
+        gt, gp = host(gt)[:og.E], host(gp)[:params.size]
+        if n == 0:
+            assert not gt.any() and not gp.any()
+            continue
+        f_ref = O.encode(x, table, og)
+        rf, rp = O.mlp_backward(params, f_ref, gd)
+        sf, sp = mlp_backward_scale(params, f_ref, gd)
+        scaled_close(gt, O.encode_backward(x, rf, og), O.encode_backward(x, sf, og), RTOL_GRAD, "d_table")
+        scaled_close(gp, rp, sp, RTOL_GRAD, "d_params")
