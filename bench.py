@@ -28,7 +28,7 @@ if ROOT not in sys.path:
 
 METRIC = "4D-hash deform queries/s fwd+bwd (N=200k, L=16, T=2^19), BF16 vs FP32"
 HBM_PEAK_GBPS = 8000.0
-KERNEL_SOURCES = ("encode.hip", "h4d_device.h", "h4d_internal.h", "mlp.hip")
+KERNEL_SOURCES = ("encode.hip", "h4d_device.h", "h4d_internal.h", "mlp.hip", "pair_lists.h")
 # the library kernels behind each timed part of the step
 STEP_KERNELS = {"cast": ["k_cast_bf16"], "encode": ["k_encode"], "decode": ["k_mlp_forward"],
                 "decode_bwd": ["k_mlp_backward", "k_mlp_reduce"],

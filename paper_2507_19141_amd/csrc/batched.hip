@@ -137,7 +137,12 @@ struct BQuery {
     uint32_t e;
 };
 
-constexpr int kBatchScatterBlock = 1024;  // one workgroup per CU (128 KiB tile), 16 wavefronts
+// One workgroup per CU (128 KiB tile), 16 wavefronts.  The lists of a scene cover all its
+// timestamps, so a tile is cleared and written once per step.  5 scenes x 4 timestamps, 6.2M
+// queries: scatter 8.8 -> 5.1 ms, pre-pass 0.36 -> 0.86 ms.  Per query it takes longer than
+// the plain scatter at random times: with one timestamp per segment the coarse levels'
+// updates crowd into a few rows, whose adds retry.
+constexpr int kBatchScatterBlock = 1024;
 
 // XCD placement of the scatter tiles: the tile list is eight runs of about equal work, run
 // x going to XCD x (workgroup b runs on XCD b % 8), whole levels at a time, so each XCD's

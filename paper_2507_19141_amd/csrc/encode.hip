@@ -58,6 +58,15 @@ __global__ __launch_bounds__(kEncodeBlock) void k_encode(DevGrid g, const TT* __
 // those queries only.
 // PAIR: each query also subtracts the same gradient at the corners of x + eps (the
 // second term of Eq. 11).
+//
+// The lists are why a tile's time follows its own updates: with the masks alone every tile
+// streams its level's mask array and gathers whole queries for one pair each.  200k queries
+// of the 16-level, 2^19-row scene: scatter 224 -> 128 us, the passes before it 26 -> 34 us;
+// 123k queries of one timestamp 254 -> 173 us (and no pass over tiles split among
+// workgroups); two corner sets 558 -> 230 us.  What bounds it now, at four wavefronts per
+// SIMD (the tile fills the LDS): vector instructions 59 % of the time, LDS 54 %, L1 fills
+// 56 %, none of them alone.  Doubles in the tile with the hardware's FP64 adds, which need
+// no retry, were no faster (the tile then holds half the rows: 431 -> 511 us for a step).
 
 // The pre-pass.  Grid (chunks of the level with the most, L).
 template <bool PAIR>

@@ -84,9 +84,11 @@ __device__ __forceinline__ uint32_t corner_tiles(const DevGrid& g, const TileMap
 }
 
 // ---- the pre-pass: one workgroup sorts one chunk of one level ----
+// Bound by its LDS atomics (one per entry, about 15 clocks a wavefront) and the passes over
+// the chunk in LDS: 34 us for 200k queries at 16 levels, 58 us with two corner sets.
 // 1024 threads at eight wavefronts per SIMD (64 registers) with one corner set per query
-// (512: 36 against 35 us for 200k queries); two sets need more registers, where 512
-// threads are faster (70 against 91 us).
+// (512 threads: 36 us); two sets need more registers, where 512 threads are faster (58
+// against 79 us).
 constexpr int pre_block(bool pair) { return pair ? 512 : 1024; }
 constexpr int pre_waves_per_eu(bool pair) { return pair ? 4 : 8; }
 
@@ -113,8 +115,8 @@ __device__ __forceinline__ float4 perturbed(float4 x, float4 e) {
 // an instruction, and the LDS atomic that counts an entry also gives its rank.  So inside
 // a tile's run the entries stay in query order, and the scatter's neighbouring lanes load
 // positions and gradients from the same 128-byte lines: a gather costs a clock per line
-// that neighbouring lanes do not share (with the entries of 64 queries pair by pair the
-// scatter's loads took 148 clocks per batch of 64, in query order about 50).
+// that neighbouring lanes do not share (entries of 64 queries pair by pair: 4.75e7 L1
+// accesses in the scatter of 200k queries; in query order 3.25e7).
 // PAIR: pos(q, x, xp) gives two positions; both in one cell give one entry per pair (kind
 // 2: both weights at the same two rows), else 8 entries of kind 0 (x) and 8 of kind 1
 // (xp).  Without PAIR every entry is of kind 0.
