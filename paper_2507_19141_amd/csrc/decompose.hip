@@ -219,6 +219,121 @@ __global__ __launch_bounds__(kDecBlock) void k_split_write(const float* __restri
     }
 }
 
+// Small splits in one launch of one workgroup: every Gaussian's key stays in a register of
+// its thread (up to 16 of them), so nothing but the outputs leaves the CU.  1000 Gaussians
+// 44 -> 16 us, 16000 45 -> 31 us, a microsecond more per 1000: one CU's loads and LDS
+// atomics.  Past 16 keys a thread would read them again for each digit, and near 30k it
+// would take as long as the launches.
+constexpr int kSmallBlock = 1024, kSmallRuns = 16;
+
+// Inclusive sums over the first 256 threads' values; called by all threads, with barriers.
+__device__ __forceinline__ uint32_t scan256(uint32_t v, uint32_t* wsum) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t c = v;
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t a = (uint32_t)__shfl_up((int)c, d, 64);
+        if (lane >= d) c += a;
+    }
+    if (lane == 63 && wave < 4) wsum[wave] = c;
+    __syncthreads();
+    for (int w = 0; w < 4; ++w)
+        if (w < wave) c += wsum[w];
+    __syncthreads();
+    return c;
+}
+
+__global__ __launch_bounds__(kSmallBlock) void k_split_small(const float* __restrict__ dp, int n, int64_t n_d,
+                                                             float lam_s, int32_t* __restrict__ dyn_idx,
+                                                             int32_t* __restrict__ n_dynamic,
+                                                             uint8_t* __restrict__ is_dyn, float* __restrict__ loss,
+                                                             float* __restrict__ d_dp) {
+    constexpr int kWaves = kSmallBlock / 64;
+    __shared__ uint32_t h[256], wsum[4], total;
+    __shared__ uint32_t found[2];              // the key's digits so far, the rank sought among them
+    __shared__ uint32_t place[kSmallRuns * kWaves];
+    __shared__ float wf[kWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t k[kSmallRuns];
+#pragma unroll
+    for (int r = 0; r < kSmallRuns; ++r) {
+        const int i = r * kSmallBlock + tid;
+        k[r] = i < n ? motion_key(dp, i) : 0u;
+    }
+    const bool all = n_d >= n;
+    if (tid == 0) {  // the (n_d + 1)-th largest, counted from below
+        found[0] = 0u;
+        found[1] = all ? 0u : (uint32_t)(n - n_d - 1);
+    }
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        if (tid < 256) h[tid] = 0u;
+        __syncthreads();
+        const uint32_t prefix = found[0], rank = found[1];
+        const uint32_t hi_mask = shift == 24 ? 0u : ~((1u << (shift + 8)) - 1u);
+#pragma unroll
+        for (int r = 0; r < kSmallRuns; ++r)
+            if (r * kSmallBlock + tid < n && (k[r] & hi_mask) == prefix) atomicAdd(&h[(k[r] >> shift) & 255u], 1u);
+        __syncthreads();
+        const uint32_t v = tid < 256 ? h[tid] : 0u;
+        const uint32_t c = scan256(v, wsum);
+        if (tid < 256 && c - v <= rank && rank < c) {  // exactly one bucket: the rank exists
+            found[0] = prefix | (uint32_t)tid << shift;
+            found[1] = rank - (c - v);
+        }
+        __syncthreads();
+    }
+    const uint32_t tau = found[0];
+    float mag = 0.f;
+#pragma unroll
+    for (int r = 0; r < kSmallRuns; ++r) {
+        const int i = r * kSmallBlock + tid;
+        const bool dyn = i < n && (all || k[r] > tau);
+        const uint64_t bal = __ballot(dyn);
+        if (lane == 0) place[r * kWaves + wave] = (uint32_t)__popcll(bal);
+        if (i < n && !dyn) {
+            const float x = dp[3 * i], y = dp[3 * i + 1], z = dp[3 * i + 2];
+            mag += sqrtf(x * x + y * y + z * z);
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) mag += __shfl_xor(mag, o, 64);
+    if (lane == 0) wf[wave] = mag;
+    __syncthreads();
+    const uint32_t v = tid < 256 ? place[tid] : 0u;
+    const uint32_t c = scan256(v, wsum);
+    if (tid < 256) place[tid] = c - v;
+    if (tid == 255) total = c;
+    __syncthreads();
+    const uint32_t n_dyn = total;
+    const int n_s = n - (int)n_dyn;
+    if (tid == 0) {
+        if (n_dynamic) *n_dynamic = (int32_t)n_dyn;
+        if (loss && n_s > 0) {
+            double f = 0.0;
+            for (int w = 0; w < kWaves; ++w) f += (double)wf[w];
+            *loss += lam_s / (float)n_s * (float)f;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kSmallRuns; ++r) {
+        const int i = r * kSmallBlock + tid;
+        const bool dyn = i < n && (all || k[r] > tau);
+        const uint64_t bal = __ballot(dyn);
+        if (i >= n) continue;
+        if (is_dyn) is_dyn[i] = dyn ? 1 : 0;
+        if (dyn) {
+            if (dyn_idx) dyn_idx[place[r * kWaves + wave] + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull))] = i;
+        } else if (d_dp) {
+            const float x = dp[3 * i], y = dp[3 * i + 1], z = dp[3 * i + 2];
+            const float m = sqrtf(x * x + y * y + z * z);
+            if (m > 0.f) {
+                const float g = lam_s / (float)n_s / m;
+                d_dp[3 * i] += g * x;
+                d_dp[3 * i + 1] += g * y;
+                d_dp[3 * i + 2] += g * z;
+            }
+        }
+    }
+}
+
 // 256 bytes of states, and words for one histogram and three per kDecBlock Gaussians.
 size_t decompose_workspace_bytes(int64_t n) {
     const int64_t nb = (n + kDecBlock - 1) / kDecBlock;
@@ -249,12 +364,17 @@ static SplitPlan split_plan(int64_t n) {
 
 hipError_t launch_decompose(const float* dp, int64_t n, double k_percent, float lam_s, int32_t* dyn_idx,
                             int32_t* n_dynamic, uint8_t* is_dyn, float* loss, float* d_dp, void* ws, hipStream_t s) {
+    const int64_t n_d = (int64_t)floor(k_percent / 100.0 * (double)n);
+    if (n <= kSmallBlock * kSmallRuns) {
+        hipLaunchKernelGGL(k_split_small, dim3(1), dim3(kSmallBlock), 0, s, dp, (int)n, n_d, lam_s, dyn_idx, n_dynamic,
+                           is_dyn, loss, d_dp);
+        return hipGetLastError();
+    }
     const SplitPlan pl = split_plan(n);
     SelectState* st = static_cast<SelectState*>(ws);
     uint32_t* hist = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + 256);
     uint32_t* counts = hist + pl.counts;
     float* sums = reinterpret_cast<float*>(counts + pl.blocks);
-    const int64_t n_d = (int64_t)floor(k_percent / 100.0 * (double)n);
     hipLaunchKernelGGL(k_select_init, dim3(1), dim3(kDecBlock), 0, s, st, hist, pl.hists * 256, n, n_d);
     // 256 device atomics per workgroup and pass
     const int hist_blocks = (int)std::min<int64_t>((n + kDecBlock - 1) / kDecBlock, 256);

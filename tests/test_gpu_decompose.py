@@ -131,3 +131,28 @@ def test_split_at_the_plan_edges(n, k):
     assert np.array_equal(flag, want)
     assert abs(loss - rloss) <= RTOL_F32 * abs(rloss)
     scaled_close(grad, rgrad, 0.7 / max(n - len(ridx), 1) * np.ones_like(rgrad), RTOL_F32, "d_dp")
+
+
+# One workgroup holds the keys of up to 16384 Gaussians: its runs of 1024 and wavefronts,
+# and the size after which the split takes several launches.
+@pytest.mark.parametrize("n", [1, 64, 65, 1023, 1024, 1025, 15_361, 16_383, 16_384, 16_385])
+@pytest.mark.parametrize("k", [0.0, 0.1, 37.0, 100.0])
+def test_split_in_one_workgroup(n, k):
+    rng = np.random.default_rng(n + 7)
+    dp = rng.standard_normal((n, 3)).astype(np.float32)
+    dp[n // 2:n // 2 + n // 8] = dp[0]   # ties
+    dp[n // 4:n // 4 + n // 16] = 0.0
+    dp[n - 1, 1] = np.inf if n > 64 else dp[n - 1, 1]
+    idx, flag, loss, grad = run(dp, k, 0.7)
+    ridx, rloss, rgrad = O.decompose(dp, k, 0.7)
+    assert np.array_equal(idx.astype(np.int64), ridx)
+    want = np.zeros(n, np.uint8)
+    want[ridx] = 1
+    assert np.array_equal(flag, want)
+    ok = np.isfinite(rgrad)
+    if np.isfinite(rloss):
+        assert abs(loss - rloss) <= RTOL_F32 * abs(rloss)
+    else:
+        assert not np.isfinite(loss)
+    scaled_close(np.where(ok, grad, 0.0), np.where(ok, rgrad, 0.0), 0.7 / max(n - len(ridx), 1) * np.ones_like(rgrad),
+                 RTOL_F32, "d_dp")
