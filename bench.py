@@ -295,9 +295,10 @@ def probe_sweep(torch, _lib, E, n_loads, reps=5):
 def achievable(torch, _lib, synth, per, pr, n):
     """Each kernel's time against the probe ceiling that matches its access pattern
     (each fraction at most 1 when the kernel runs at that ceiling):
-    encode: its corner-row requests (one per x-pair whose rows are an aligned pair,
-    two otherwise, counted from the corner rows) at the random-gather request rate of
-    a 4 MiB, L2-resident footprint (the level slice each XCD holds);
+    encode: its line requests (one per x-pair whose rows share a 128-byte line, two
+    otherwise, counted from the corner rows: neighbouring lanes read a pair together) at
+    the random-gather request rate of a 4 MiB, L2-resident footprint (the level slice
+    each XCD holds);
     scatter: the larger of the time to write and read the sorted corner pairs (2 bytes
     for each of the 8 pairs of a query and level) at the copy rate and the time for the
     corner updates at the LDS compare-and-swap rate (the queries' own loads taken as
@@ -309,7 +310,8 @@ def achievable(torch, _lib, synth, per, pr, n):
     rows = torch.empty((n, w.L, 16), dtype=torch.int32, device="cuda")
     _lib.hash4d_corner_indices(g, torch.from_numpy(x).cuda(), n, rows, None)
     r0, r1 = rows[..., 0::2], rows[..., 1::2]
-    paired = (r1 == (r0 ^ 1)) & ((r0 | 1) < g.E)
+    per_line = 128 // (4 * w.F)
+    paired = r0 // per_line == r1 // per_line
     requests = int(n * w.L * 8 + (~paired).sum().item())
     del rows, r0, r1, paired
     t_enc = requests / (pr["gather8_4MiB_Gloads_per_s"] * 1e9)
