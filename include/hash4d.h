@@ -349,7 +349,8 @@ h4d_status h4d_count_nonfinite(const float* p, int64_t count, int32_t* counter, 
 
 /* Bytes of workspace deform_mlp_backward needs for n queries (split-N partial
  * weight gradients: one row of P parameters per persistent block).  0 if *m is
- * invalid. */
+ * invalid.  Calls also take a workspace with a row per 128 queries only (at most 256
+ * rows), and then run on fewer blocks. */
 size_t deform_mlp_workspace_bytes(const h4d_mlp* m, h4d_dtype dt, int64_t n);
 
 /* Decoder forward (Section 4.2: the trunk phi_d of Eq. 9, then the position,

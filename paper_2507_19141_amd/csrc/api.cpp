@@ -172,9 +172,15 @@ static size_t scatter_ws(const h4d_grid* g, int64_t n, bool pair = false) {
 }
 
 // Deformation backward workspace: [decoder partials | d_feat [L, n, F] | pair lists].
-static size_t deform_ws(const h4d_grid* g, const h4d_mlp* m, h4d_dtype dt, int64_t n) {
+// least: with the fewest decoder partials that a call takes.
+static size_t mlp_part(const h4d_mlp* m, h4d_dtype dt, int64_t n, bool least) {
+    const size_t bytes = least ? mlp_workspace_least(dt, m->in, m->out, (int)n)
+                               : mlp_workspace_bytes(dt, m->in, m->out, (int)n);
+    return (bytes + 255) / 256 * 256;
+}
+static size_t deform_ws(const h4d_grid* g, const h4d_mlp* m, h4d_dtype dt, int64_t n, bool least = false) {
     const size_t el = dt == H4D_F64 ? sizeof(double) : sizeof(float);
-    const size_t a = (mlp_workspace_bytes(dt, m->in, m->out, (int)n) + 255) / 256 * 256;
+    const size_t a = mlp_part(m, dt, n, least);
     const size_t b = ((size_t)n * g->L * g->F * el + 255) / 256 * 256;
     return a + b + scatter_ws(g, n);
 }
@@ -744,13 +750,13 @@ static h4d_status mlp_backward_call(const h4d_mlp* m, h4d_dtype dt, const void* 
                           "deform_mlp_backward");
     }
     if (!params || !feat || !d_out || !d_feat || !d_params) return fail(H4D_EINVAL, "NULL data pointer");
-    const size_t need = mlp_workspace_bytes(dt, m->in, m->out, (int)n);
+    const size_t need = mlp_workspace_least(dt, m->in, m->out, (int)n);
     if (!workspace || ws_bytes < need)
         return fail(H4D_EINVAL, "workspace of %zu bytes, %zu needed", workspace ? ws_bytes : (size_t)0, need);
     if (((uintptr_t)workspace) & 15u) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");
     return hip_status(launch_mlp_backward(dt, m->in, m->out, params, feat, Fk, ls, qs, (int)n, d_out, loss_scale,
                                           grad_scale, grad_scale, d_feat, ls, qs, d_params, workspace,
-                                          (hipStream_t)stream, overwrite, nonfinite),
+                                          ws_bytes, (hipStream_t)stream, overwrite, nonfinite),
                       "deform_mlp_backward");
 }
 
@@ -826,21 +832,23 @@ h4d_status hash4d_deform_backward(const h4d_grid* g, const h4d_mlp* m, h4d_dtype
     if ((st = check_deform(g, m, dt, xyzt, n))) return st;
     if (n == 0) return H4D_OK;
     if (!params || !feat || !d_delta || !d_table || !d_params) return fail(H4D_EINVAL, "NULL data pointer");
-    const size_t need = deform_ws(g, m, dt, n);
+    const size_t need = deform_ws(g, m, dt, n, true);
     if (!workspace || ws_bytes < need)
         return fail(H4D_EINVAL, "workspace of %zu bytes, %zu needed", workspace ? ws_bytes : (size_t)0, need);
     if (((uintptr_t)workspace) & 15u) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");
+    const bool least = ws_bytes < deform_ws(g, m, dt, n);
     const DevGrid d = to_device(*g);
     const hipStream_t s = (hipStream_t)stream;
     const int64_t ls = n * g->F, qs = g->F;
     char* ws = static_cast<char*>(workspace);
     const size_t el = dt == H4D_F64 ? sizeof(double) : sizeof(float);
-    const size_t part = (mlp_workspace_bytes(dt, m->in, m->out, (int)n) + 255) / 256 * 256;
+    const size_t part = mlp_part(m, dt, n, least);
     void* d_feat = ws + part;
     void* lists = ws + part + ((size_t)n * g->L * g->F * el + 255) / 256 * 256;
     // decoder backward: d_feat keeps the loss scale, d_params gets grad_scale
     if ((st = hip_status(launch_mlp_backward(dt, m->in, m->out, params, feat, g->F, ls, qs, (int)n, d_delta,
-                                             loss_scale, 1.0, grad_scale, d_feat, ls, qs, d_params, ws, s),
+                                             loss_scale, 1.0, grad_scale, d_feat, ls, qs, d_params, ws, part,
+                                             s),
                          "hash4d_deform_backward/decode")))
         return st;
     int64_t rows[H4D_MAX_LEVELS];

@@ -179,7 +179,9 @@ hipError_t launch_mlp_forward_batch(h4d_dtype dt, int in, int out, const MlpBatc
 hipError_t launch_mlp_backward_batch(h4d_dtype dt, int in, int out, const MlpBatch& b, int blocks, double in_scale,
                                      double feat_scale, double param_scale, void* ws, hipStream_t s);
 // Features / feature gradients are addressed as feat[(k / F) lstride + q qstride + k % F].
+// Workspace of the backward: what its grid of choice takes, and the least it runs with.
 size_t mlp_workspace_bytes(h4d_dtype dt, int in, int out, int n);
+size_t mlp_workspace_least(h4d_dtype dt, int in, int out, int n);
 hipError_t launch_mlp_forward(h4d_dtype dt, int in, int out, const void* params, const void* feat, int F,
                               int64_t lstride, int64_t qstride, int n, void* delta, hipStream_t s);
 // d_out is multiplied by in_scale on load; d_feat is written times feat_scale;
@@ -187,8 +189,8 @@ hipError_t launch_mlp_forward(h4d_dtype dt, int in, int out, const void* params,
 hipError_t launch_mlp_backward(h4d_dtype dt, int in, int out, const void* params, const void* feat, int F,
                                int64_t lstride, int64_t qstride, int n, const void* d_out, double in_scale,
                                double feat_scale, double param_scale, void* d_feat, int64_t dlstride,
-                               int64_t dqstride, void* d_params, void* ws, hipStream_t s, bool overwrite = false,
-                               int32_t* nonfinite = nullptr);
+                               int64_t dqstride, void* d_params, void* ws, size_t ws_bytes, hipStream_t s,
+                               bool overwrite = false, int32_t* nonfinite = nullptr);
 
 // ---- precision helpers (precision.hip) ----
 hipError_t launch_cast_bf16(const float* src, uint16_t* dst, int64_t count, hipStream_t s);

@@ -972,10 +972,19 @@ constexpr int kMlpFwdMaxBlocks = 1024;
 constexpr int kMlpBwdMaxBlocks = 256;
 constexpr int kMlpF64MaxBlocks = 64;   // the FP64 check path spills to scratch: keep its grid small
 
-// One workgroup per `waves` tiles of 16 queries, at most `cap`.
-static int mlp_blocks(int n, int waves, int cap) {
+// Tiles per workgroup of the backward while the grid is below its cap.  With a tile for each
+// of the eight wavefronts a few thousand queries leave most CUs idle and each CU's one
+// iteration is a chain of latencies; two tiles halve the SIMDs' sharing in the layer chain
+// and quarter the contractions, for four times the partial rows.  Steps of 4096 queries, in
+// us with 8 / 4 / 2 / 1 tiles: 8 features 49.5 / 46 / 45.2 / 46.6, 32 features 80 / 75 / 75 /
+// 76; 16000 queries 62.9 / 60 / 58.0 / 57.4 and 104 / 101 / 100 / 100; from 8 * 256 tiles on
+// there is no difference.
+constexpr int kMlpBwdTiles = 2, kMlpBwdTilesLeast = 8;
+
+// One workgroup per `each` tiles of 16 queries, at most `cap`.
+static int mlp_blocks(int n, int each, int cap) {
     const int ntiles = (n + 15) / 16;
-    const int want = (ntiles + waves - 1) / waves;
+    const int want = (ntiles + each - 1) / each;
     return want < cap ? (want > 0 ? want : 1) : cap;
 }
 
@@ -987,6 +996,14 @@ static size_t lds_forward(int out) {
 
 size_t mlp_workspace_bytes(h4d_dtype dt, int in, int out, int n) {
     return mlp_partial_bytes(dt, in, out, mlp_blocks_for(dt, true, n), 1);
+}
+
+static int mlp_blocks_least(h4d_dtype dt, int n) {
+    return mlp_blocks(n, kMlpBwdTilesLeast, dt == H4D_F64 ? kMlpF64MaxBlocks : kMlpBwdMaxBlocks);
+}
+
+size_t mlp_workspace_least(h4d_dtype dt, int in, int out, int n) {
+    return mlp_partial_bytes(dt, in, out, mlp_blocks_least(dt, n), 1);
 }
 
 template <class Pol, int IN>
@@ -1055,7 +1072,10 @@ static int log2i(int F) { return F == 1 ? 0 : F == 2 ? 1 : F == 4 ? 2 : 3; }
 
 int mlp_blocks_for(h4d_dtype dt, bool backward, int64_t queries) {
     const int cap = dt == H4D_F64 ? kMlpF64MaxBlocks : backward ? kMlpBwdMaxBlocks : kMlpFwdMaxBlocks;
-    return mlp_blocks((int)(queries < 2147483647 ? queries : 2147483647), backward ? 8 : 4, cap);
+    return mlp_blocks((int)(queries < 2147483647 ? queries : 2147483647), !backward             ? 4
+                                                                                : dt == H4D_F64 ? kMlpBwdTilesLeast
+                                                                                                : kMlpBwdTiles,
+                      cap);
 }
 
 size_t mlp_partial_bytes(h4d_dtype dt, int in, int out, int blocks, int) {
@@ -1096,9 +1116,11 @@ hipError_t launch_mlp_forward(h4d_dtype dt, int in, int out, const void* params,
 hipError_t launch_mlp_backward(h4d_dtype dt, int in, int out, const void* params, const void* feat, int F,
                                int64_t lstride, int64_t qstride, int n, const void* d_out, double in_scale,
                                double feat_scale, double param_scale, void* d_feat, int64_t dlstride, int64_t dqstride,
-                               void* d_params, void* ws, hipStream_t s, bool overwrite, int32_t* nonfinite) {
+                               void* d_params, void* ws, size_t ws_bytes, hipStream_t s, bool overwrite,
+                               int32_t* nonfinite) {
     if (dlstride != lstride || dqstride != qstride) return hipErrorInvalidValue;  // d_feat shares feat's layout
-    const int blocks = mlp_blocks_for(dt, true, n);
+    int blocks = mlp_blocks_for(dt, true, n);
+    if (mlp_partial_bytes(dt, in, out, blocks, 1) > ws_bytes) blocks = mlp_blocks_least(dt, n);
     MlpBatch b = single(params, feat, nullptr, d_out, d_feat, d_params, F, lstride, qstride, n, blocks);
     b.overwrite = overwrite ? 1 : 0;
     b.nonfinite = nonfinite;

@@ -368,3 +368,31 @@ def test_deform_apply_eq10_bit_exact():
     xd = dev(x)
     _lib.hash4d_deform_apply(dev(delta), n, 10, xd, dev(r), dev(s), xd, ro, so)
     assert np.array_equal(host(xd), ref[0].astype(np.float32))
+
+
+def least_rows(n):
+    """Rows of the smallest workspace that the backward takes: one per 128 queries."""
+    return min(256, max(1, ((n + 15) // 16 + 7) // 8))
+
+
+# Two tiles of 16 queries per workgroup below 512 tiles, and the same call on the smallest
+# workspace (eight tiles per workgroup): both against the oracle.
+@pytest.mark.parametrize("n", [1, 16, 17, 32, 33, 129, 2001, 8176, 8193])
+@pytest.mark.parametrize("n_in", [8, 32])
+def test_mlp_backward_grids_f32(n_in, n):
+    import torch
+    params, f, g = decoder_case(n_in, n, 97)
+    m = _lib.mlp_shape(n_in)
+    P = O.param_count(n_in)
+    rf, rp = O.mlp_backward(params, f, g)
+    sf, sp = mlp_backward_scale(params, f, g)
+    least = (least_rows(n) * P * 4 + 255) // 256 * 256
+    full = _lib.deform_mlp_workspace_bytes(m, _lib.F32, n)
+    assert full >= least
+    for wb in (full, least):
+        ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
+        d_feat, d_params = nan_tensor((n, n_in), torch.float32), nan_tensor((P,), torch.float32)
+        _lib.deform_mlp_backward(m, _lib.F32, dev(params), dev(f), n, dev(g), 1.0, 1.0, d_feat, d_params, ws, wb,
+                                 _lib.QUERY_MAJOR | _lib.GRAD_OVERWRITE)
+        scaled_close(host(d_feat), rf, sf, RTOL_GRAD, f"d_feat {wb}")
+        scaled_close(host(d_params), rp, sp, RTOL_GRAD, f"d_params {wb}")
