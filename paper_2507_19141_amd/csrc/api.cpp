@@ -381,6 +381,7 @@ static h4d_status encode_backward_call(const h4d_grid* g, h4d_dtype grad_dt, con
     if (!d_feat || !d_table) return fail(H4D_EINVAL, "d_feat or d_table is NULL");
     const size_t need = scatter_ws(g, n);
     if (static_ws) {
+        ws_bytes = kStaticScratchBytes;
         if (need > kStaticScratchBytes)
             return fail(H4D_EINVAL, "n=%lld, L=%d need %zu bytes of workspace; the static workspace holds %zu",
                         (long long)n, g->L, need, kStaticScratchBytes);
@@ -394,8 +395,8 @@ static h4d_status encode_backward_call(const h4d_grid* g, h4d_dtype grad_dt, con
     int64_t rows[H4D_MAX_LEVELS];
     rows_of(*g, rows);
     return hip_status(launch_scatter_tiled(d, rows, grad_dt, xyzt, nullptr, (int)n, d_feat, ls, qs,
-                                           (double)grad_scale, d_table, workspace, (hipStream_t)stream, overwrite,
-                                           MainGradArg{}, nonfinite),
+                                           (double)grad_scale, d_table, workspace, ws_bytes, (hipStream_t)stream,
+                                           overwrite, MainGradArg{}, nonfinite),
                       where);
 }
 
@@ -510,7 +511,7 @@ h4d_status smoothness_reg(const h4d_grid* g, h4d_dtype table_dt, const void* tab
         ((size_t)n * g->L * g->F * (table_dt == H4D_F64 ? sizeof(double) : sizeof(float)) + 255) / 256 * 256;
     return hip_status(launch_scatter_tiled(d, rows, table_dt == H4D_F64 ? H4D_F64 : H4D_F32, xyzt, eps, (int)n,
                                            workspace, n * g->F, g->F, 2.0 * (double)lambda / (double)n, d_table,
-                                           static_cast<char*>(workspace) + dbytes, s),
+                                           static_cast<char*>(workspace) + dbytes, ws_bytes - dbytes, s),
                       "smoothness_reg/scatter");
 }
 
@@ -558,7 +559,8 @@ h4d_status hash4d_encode_backward_smooth(const h4d_grid* g, h4d_dtype table_dt, 
     main.scale = (double)grad_scale;
     return hip_status(launch_scatter_tiled(d, rows, table_dt == H4D_F64 ? H4D_F64 : H4D_F32, xyzt, eps, (int)n,
                                            workspace, n * g->F, g->F, 2.0 * (double)lambda / (double)n, d_table,
-                                           static_cast<char*>(workspace) + dbytes, s, overwrite, main),
+                                           static_cast<char*>(workspace) + dbytes, ws_bytes - dbytes, s, overwrite,
+                                           main),
                       "hash4d_encode_backward_smooth/scatter");
 }
 
@@ -844,7 +846,7 @@ h4d_status hash4d_deform_backward(const h4d_grid* g, const h4d_mlp* m, h4d_dtype
     const size_t el = dt == H4D_F64 ? sizeof(double) : sizeof(float);
     const size_t part = mlp_part(m, dt, n, least);
     void* d_feat = ws + part;
-    void* lists = ws + part + ((size_t)n * g->L * g->F * el + 255) / 256 * 256;
+    const size_t lists = part + ((size_t)n * g->L * g->F * el + 255) / 256 * 256;
     // decoder backward: d_feat keeps the loss scale, d_params gets grad_scale
     if ((st = hip_status(launch_mlp_backward(dt, m->in, m->out, params, feat, g->F, ls, qs, (int)n, d_delta,
                                              loss_scale, 1.0, grad_scale, d_feat, ls, qs, d_params, ws, part,
@@ -854,7 +856,7 @@ h4d_status hash4d_deform_backward(const h4d_grid* g, const h4d_mlp* m, h4d_dtype
     int64_t rows[H4D_MAX_LEVELS];
     rows_of(*g, rows);
     return hip_status(launch_scatter_tiled(d, rows, dt == H4D_F64 ? H4D_F64 : H4D_F32, xyzt, nullptr, (int)n, d_feat,
-                                           ls, qs, grad_scale, d_table, lists, s),
+                                           ls, qs, grad_scale, d_table, ws + lists, ws_bytes - lists, s),
                       "hash4d_deform_backward/encode");
 }
 

@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kBatchScatterBlock) void k_bscatter(const BSeg* __r
     batch_flush<F>(g, tm, l, tr, tile, sc.d_table, overwrite);
 }
 
-// Tiles of the levels without lists.
+// Tiles of the levels with masks.
 template <int F>
 __global__ __launch_bounds__(kBatchScatterBlock) void k_bscatter_masked(const BSeg* __restrict__ segs,
                                                                         const DevGrid* __restrict__ grids,
@@ -262,10 +262,10 @@ __global__ __launch_bounds__(kBatchScatterBlock) void k_bscatter_masked(const BS
     const DevGrid& g = grids[tl.scene];
     const TileMap& tm = tms[tl.scene];
     const int l = tl.level;
-    if ((tm.lists >> l) & 1u) return;
+    if (!((tm.masks >> l) & 1u)) return;
     const BScene sc = scenes[tl.scene];
     const TileRows tr = tile_rows(g, tm, l, tl.tile);
-    const int ml = __popc(~tm.lists & ((1u << l) - 1u));
+    const int ml = __popc(tm.masks & ((1u << l) - 1u));
     zero_tile<kBatchScatterBlock>(tile, tr.cnt * F);
     __syncthreads();
     for (int sgi = sc.seg0; sgi < sc.seg0 + sc.nseg; ++sgi) {
@@ -663,10 +663,10 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
         int64_t lrows[H4D_MAX_LEVELS];
         for (int l = 0; l < d.grid.L; ++l) lrows[l] = d.grid.offset[l + 1] - d.grid.offset[l];
         const TileMap tm = make_tile_map(p->grids_h[s], lrows, d.grid.F, (int)sizeof(float), (int)d.n, d.n_times, false,
-                                         d.grid.L);
+                                         level_bits(d.grid.L), level_bits(d.grid.L));
         tms.push_back(tm);
         bscenes.push_back(BScene{seg0, d.n_times, (int)d.n, nullptr, nullptr, d.d_table});
-        const int masked = d.grid.L - __builtin_popcount(tm.lists);
+        const int masked = __builtin_popcount(tm.masks);
         mask_elems += (int64_t)d.n_times * masked * mask_stride(d.n);
         region_count += tm.list_region[d.grid.L];
         head_count += tm.list_head[d.grid.L];
@@ -708,7 +708,7 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
             b.d_table = d.d_table;
             b.mask = p->masks + mo;
             b.index = k;
-            mo += (int64_t)(d.grid.L - __builtin_popcount(tms[s].lists)) * mask_stride(d.n);
+            mo += (int64_t)__builtin_popcount(tms[s].masks) * mask_stride(d.n);
             segs.push_back(b);
         }
         dfo += d.n_times * seg_elems;

@@ -4,6 +4,7 @@
 // placed on XCDs level by level (xcd_item), so each XCD's L2 holds mostly one
 // level's slice of the table (4 MiB FP32 / 2 MiB BF16 for a 2^19-row, F = 2 level)
 // instead of every XCD streaming the whole table through its L2.
+#include <limits.h>
 #include <string.h>
 
 #include <algorithm>
@@ -51,8 +52,8 @@ __global__ __launch_bounds__(kEncodeBlock) void k_encode(DevGrid g, const TT* __
 // workgroup owns those rows).
 //
 // A pre-pass tells each tile which queries reach it: pair lists (pair_lists.h), or, on
-// levels of more than kListTiles tiles (and where a workspace bounds the lists), a 32-bit
-// mask per (query, level) of the tiles the query's corners touch (tile t sets bit t >>
+// levels of more than kListTiles tiles (and where the workspace does not hold one level's
+// lists), a 32-bit mask per (query, level) of the tiles the query's corners touch (tile t sets bit t >>
 // bit_shift); a tile workgroup reads the masks of its level, compacts the queries whose
 // bit is set into per-wavefront LDS queues and runs the corner work on full wavefronts of
 // those queries only.
@@ -68,7 +69,8 @@ __global__ __launch_bounds__(kEncodeBlock) void k_encode(DevGrid g, const TT* __
 // 56 %, none of them alone.  Doubles in the tile with the hardware's FP64 adds, which need
 // no retry, were no faster (the tile then holds half the rows: 431 -> 511 us for a step).
 
-// The pre-pass.  Grid (chunks of the level with the most, L).
+// The pre-pass.  Grid (chunks of the level with the most, L); levels without tiles belong
+// to another pass (scatter_plan).
 template <bool PAIR>
 __global__ __launch_bounds__(pre_block(PAIR)) __attribute__((amdgpu_waves_per_eu(pre_waves_per_eu(PAIR)))) void k_tile_pre(DevGrid g, TileMap tm, const float4* __restrict__ xyzt,
                                                         const float4* __restrict__ eps, int n,
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(pre_block(PAIR)) __attribute__((amdgpu_waves_per_eu
                                                         uint32_t* __restrict__ heads) {
     __shared__ __align__(16) PreShared<PAIR> sh;
     const int l = blockIdx.y, nchunks = pre_chunks(n, pre_chunk_log(tm, l, PAIR));
-    if ((int)blockIdx.x >= nchunks) return;
+    if ((int)blockIdx.x >= nchunks || !(((tm.lists | tm.masks) >> l) & 1u)) return;
     tile_pre<PAIR>(g, tm, l, (int)blockIdx.x, 0, nchunks, n,
                    [&](int q, float4& x, float4& xp) {
                        x = xyzt[q];
@@ -319,7 +321,7 @@ __global__ __launch_bounds__(kScatterBlock) void k_scatter_tiled(DevGrid g, Tile
     flush_tile<G, F>(g, tm, l, tr, tile, d_table, overwrite, nonfinite);
 }
 
-// Tiles of the levels without lists.
+// Tiles of the levels with masks.
 template <typename G, int F, bool PAIR>
 __global__ __launch_bounds__(kScatterBlock) void k_scatter_masked(DevGrid g, TileMap tm, const float4* __restrict__ xyzt,
                                                                  const float4* __restrict__ eps, int n,
@@ -333,12 +335,12 @@ __global__ __launch_bounds__(kScatterBlock) void k_scatter_masked(DevGrid g, Til
     G* tile = reinterpret_cast<G*>(smem);
     int l;
     uint32_t t;
-    if (!scatter_tile(g, tm, l, t) || ((tm.lists >> l) & 1u)) return;
+    if (!scatter_tile(g, tm, l, t) || !((tm.masks >> l) & 1u)) return;
     const TileRows tr = tile_rows(g, tm, l, t);
     zero_tile<kScatterBlock>(tile, tr.cnt * F);
     __syncthreads();
     masked_queue_loop<kScatterBlock>(
-        n, mask + (int64_t)__popc(~tm.lists & ((1u << l) - 1u)) * mask_stride(n), tile_bit(tm, l, tr.first), queue,
+        n, mask + (int64_t)__popc(tm.masks & ((1u << l) - 1u)) * mask_stride(n), tile_bit(tm, l, tr.first), queue,
         [&](int q) { return tile_load<G, F, PAIR>(l, xyzt, eps, src, lstride, qstride, mg, q, 0u); },
         [&](const TileQuery<G, F, PAIR>& q) {
             tile_run<G, F, PAIR>(g, tm, l, q, scale, mg, g.off[l] + tr.first, tr.cnt, tile);
@@ -407,7 +409,7 @@ hipError_t launch_encode(const DevGrid& g, h4d_dtype dt, const void* table, cons
 
 // Tiles of at most 128 KiB of LDS; tile_start is the first tile of each level.
 TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gbytes, int n, int segs, bool pair,
-                      int list_levels) {
+                      uint32_t levels, uint32_t listed) {
     TileMap tm;
     memset(&tm, 0, sizeof tm);
     tm.max_rows = kTileBytes / (F * gbytes);  // a power of two: F and gbytes are
@@ -436,15 +438,14 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
             if (tiles[l] <= kListTiles) can |= 1u << l;
         }
     }
-    for (int dense = 1; dense >= 0; --dense)
-        for (int l = 0; l < g.L; ++l)
-            if (((can >> l) & 1u) && (int)((g.dense_bits >> l) & 1u) == dense &&
-                __builtin_popcount(tm.lists) < list_levels)
-                tm.lists |= 1u << l;
+    tm.lists = levels & listed & can;
+    tm.masks = levels & ~tm.lists;
     int t = 0, region = 0;
     int64_t head = 0;
     for (int l = 0; l < g.L; ++l) {
-        if ((tm.lists >> l) & 1u) {
+        if (!((levels >> l) & 1u)) {
+            tiles[l] = 0;
+        } else if ((tm.lists >> l) & 1u) {
             if ((g.dense_bits >> l) & 1u) {
                 tm.tile_shift[l] = line_shift[l];
                 tiles[l] = 1 << line_shift[l];
@@ -459,7 +460,7 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
             const int chunks = segs * pre_chunks(n, pre_chunk_log(tm, l, pair));
             region += chunks;
             head += (int64_t)chunks * tiles[l];
-        } else {
+        } else if ((tm.masks >> l) & 1u) {
             while (((tiles[l] - 1) >> tm.bit_shift[l]) >= 32) ++tm.bit_shift[l];
         }
         t += tiles[l];
@@ -470,35 +471,83 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
     return tm;
 }
 
-// Workspace of the tiled scatter, each part 256-byte aligned: pair list regions | list
-// heads | masks [mask level][stride] u32.
-struct ScatterWs {
+// One pass of the tiled scatter (a pre-pass and a launch over some of the levels), and what
+// it takes of the workspace, each part 256-byte aligned: pair list regions | list heads |
+// masks [mask level][stride] u32.
+struct ScatterPass {
     size_t heads, masks, total;
     TileMap tm;
 };
 
 static size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
-static ScatterWs scatter_ws_for(const DevGrid& g, const int64_t* level_rows, int n, int gbytes, bool pair,
-                                int list_levels) {
-    ScatterWs w;
-    w.tm = make_tile_map(g, level_rows, g.F, gbytes, n, 1, pair, list_levels);
+static ScatterPass scatter_pass(const DevGrid& g, const int64_t* level_rows, int n, int gbytes, bool pair,
+                                uint32_t levels, uint32_t listed) {
+    ScatterPass w;
+    w.tm = make_tile_map(g, level_rows, g.F, gbytes, n, 1, pair, levels, listed);
     w.heads = (size_t)w.tm.list_region[g.L] * kListEntries * sizeof(uint16_t);
     w.masks = w.heads + align256((size_t)w.tm.list_head[g.L] * sizeof(uint32_t));
-    w.total = w.masks + align256((size_t)mask_stride(n) * (g.L - __builtin_popcount(w.tm.lists)) * sizeof(uint32_t));
+    w.total = w.masks + align256((size_t)mask_stride(n) * __builtin_popcount(w.tm.masks) * sizeof(uint32_t));
     return w;
+}
+
+// How a workspace of `avail` bytes is used: one pass over all levels if their lists fit,
+// else passes over runs of levels, one after the other in the same memory.  The runs have
+// equal numbers of levels or about equal bytes, whichever fits with fewer rounds of
+// workgroups over the CUs (a tile fills one): 16 levels of 2^14 rows at 200k queries take
+// 173 us in passes of 256 tiles, 217 us where one has 11 levels.  Masks on the levels that
+// do not fit cost far more (250k queries: 203 us in two passes, 336 us with masks), so only
+// a level whose own lists do not fit has them.
+struct ScatterPlan {
+    int passes;
+    uint32_t listed;
+    uint32_t levels[H4D_MAX_LEVELS];  // of each pass
+};
+constexpr int kCus = 256;
+
+static ScatterPlan scatter_plan(const DevGrid& g, const int64_t* level_rows, int n, int gbytes, bool pair,
+                                size_t avail) {
+    ScatterPlan best;
+    memset(&best, 0, sizeof best);
+    best.passes = 1;
+    best.listed = best.levels[0] = level_bits(g.L);
+    auto pass = [&](uint32_t levels) { return scatter_pass(g, level_rows, n, gbytes, pair, levels, best.listed); };
+    if (pass(best.listed).total <= avail) return best;
+    size_t level[H4D_MAX_LEVELS], total = 0;
+    for (int l = 0; l < g.L; ++l) {
+        if (pass(1u << l).total > avail) best.listed &= ~(1u << l);
+        total += level[l] = pass(1u << l).total;
+    }
+    int least = INT_MAX;  // rounds; the last try, a level each, always fits
+    for (int passes = 1; passes <= g.L && passes < least; ++passes)
+        for (int by_bytes = 0; by_bytes < 2; ++by_bytes) {
+            ScatterPlan p = best;
+            memset(p.levels, 0, sizeof p.levels);
+            p.passes = passes;
+            size_t before = 0;
+            for (int l = 0; l < g.L; before += level[l++])  // by the middle of the level's bytes
+                p.levels[by_bytes ? (before + level[l] / 2) * passes / total : (size_t)(l * passes / g.L)] |= 1u << l;
+            int rounds = 0;
+            for (int i = 0; i < passes && rounds < least; ++i) {
+                const ScatterPass w = pass(p.levels[i]);
+                rounds = w.total <= avail ? rounds + (w.tm.tile_start[g.L] + kCus - 1) / kCus : least;
+            }
+            if (rounds < least) {
+                best = p;
+                least = rounds;
+            }
+        }
+    return best;
 }
 
 // The size rule behind hash4d_encode_backward_noalloc: 12 bytes per (query, level), the
 // queries per tile of each chunk of 1024, and two partial tiles for each of up to 96
-// workgroups.  Every call within the static workspace by this rule is taken, so
-// scatter_ws gives lists to no more levels than fit there in such a call (the others use
-// masks, 4 bytes per query).
+// workgroups.  Every call within the static workspace by this rule is taken.
 static size_t noalloc_rule_bytes(const DevGrid& g, const int64_t* level_rows, int n) {
     size_t slot = 0;
     int tiles = 0;
     for (int gbytes = 4; gbytes <= 8; gbytes += 4) {
-        const TileMap tm = make_tile_map(g, level_rows, g.F, gbytes, n, 1, false, 0);
+        const TileMap tm = make_tile_map(g, level_rows, g.F, gbytes, n, 1, false, level_bits(g.L), 0u);
         tiles = std::max(tiles, tm.tile_start[g.L]);
         for (int l = 0; l < g.L; ++l)
             slot = std::max(slot, (size_t)std::min((int64_t)1 << tm.tile_shift[l], level_rows[l]) * g.F * gbytes);
@@ -509,16 +558,17 @@ static size_t noalloc_rule_bytes(const DevGrid& g, const int64_t* level_rows, in
            2 * extra * slot;
 }
 
-static ScatterWs scatter_ws(const DevGrid& g, const int64_t* level_rows, int n, int gbytes, bool pair) {
-    ScatterWs w = scatter_ws_for(g, level_rows, n, gbytes, pair, g.L);
-    if (!pair && w.total > kStaticScratchBytes && noalloc_rule_bytes(g, level_rows, n) <= kStaticScratchBytes)
-        for (int levels = __builtin_popcount(w.tm.lists) - 1; levels >= 0 && w.total > kStaticScratchBytes; --levels)
-            w = scatter_ws_for(g, level_rows, n, gbytes, pair, levels);
-    return w;
-}
-
+// All levels in one pass.  One corner set: the static workspace's size where that is less
+// and its entry point takes the call, since that takes exactly the calls for which no more
+// is reported; such a call runs in two passes or more, with a workspace of its own too
+// unless it brings more.  Never less for more queries: either size and the rule only grow.
 size_t scatter_ws_bytes(const DevGrid& g, const int64_t* level_rows, int n, bool pair) {
-    return std::max(scatter_ws(g, level_rows, n, 4, pair).total, scatter_ws(g, level_rows, n, 8, pair).total);
+    const uint32_t all = level_bits(g.L);
+    const size_t bytes = std::max(scatter_pass(g, level_rows, n, 4, pair, all, all).total,
+                                  scatter_pass(g, level_rows, n, 8, pair, all, all).total);
+    return !pair && bytes > kStaticScratchBytes && noalloc_rule_bytes(g, level_rows, n) <= kStaticScratchBytes
+               ? kStaticScratchBytes
+               : bytes;
 }
 
 struct ScatterBufs {
@@ -538,7 +588,6 @@ static hipError_t tiled_f(const DevGrid& g, const TileMap& tm, const float* xyzt
     const G* gr = static_cast<const G*>(src);
     G* out = static_cast<G*>(d_table);
     const MainGrad<G> mg{static_cast<const G*>(main.src), main.lstride, main.qstride, (G)main.scale};
-    const uint32_t all = g.L >= 32 ? 0xffffffffu : (1u << g.L) - 1u;
     hipError_t e = hipSuccess;
     if (tm.lists) {
         auto kern = k_scatter_tiled<G, F, PAIR>;
@@ -548,7 +597,7 @@ static hipError_t tiled_f(const DevGrid& g, const TileMap& tm, const float* xyzt
                            overwrite ? 1 : 0, mg, nonfinite);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (~tm.lists & all) {
+    if (tm.masks) {
         auto kern = k_scatter_masked<G, F, PAIR>;
         e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -561,44 +610,50 @@ static hipError_t tiled_f(const DevGrid& g, const TileMap& tm, const float* xyzt
 
 template <typename G, bool PAIR>
 static hipError_t tiled_g(const DevGrid& g, const int64_t* level_rows, const float* xyzt, const float* eps, int n,
-                          const void* src, int64_t ls, int64_t qs, double scale, void* d_table, void* mask_ws,
-                          bool overwrite, const MainGradArg& main, int32_t* nonfinite, hipStream_t s) {
-    const ScatterWs w = scatter_ws(g, level_rows, n, (int)sizeof(G), PAIR);
-    const TileMap& tm = w.tm;
-    char* ws = static_cast<char*>(mask_ws);
-    const ScatterBufs b{reinterpret_cast<uint16_t*>(ws), reinterpret_cast<uint32_t*>(ws + w.heads),
-                        reinterpret_cast<uint32_t*>(ws + w.masks)};
-    int chunks = 0;
-    for (int l = 0; l < g.L; ++l) chunks = std::max(chunks, pre_chunks(n, pre_chunk_log(tm, l, PAIR)));
-    hipLaunchKernelGGL(k_tile_pre<PAIR>, dim3((unsigned)chunks, (unsigned)g.L), dim3(pre_block(PAIR)), 0, s, g, tm,
-                       reinterpret_cast<const float4*>(xyzt), reinterpret_cast<const float4*>(eps), n, b.mask,
-                       b.lists, b.heads);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    switch (g.F) {
-        case 1: return tiled_f<G, 1, PAIR>(g, tm, xyzt, eps, n, b, src, ls, qs, scale, d_table, overwrite, main, nonfinite, s);
-        case 2: return tiled_f<G, 2, PAIR>(g, tm, xyzt, eps, n, b, src, ls, qs, scale, d_table, overwrite, main, nonfinite, s);
-        case 4: return tiled_f<G, 4, PAIR>(g, tm, xyzt, eps, n, b, src, ls, qs, scale, d_table, overwrite, main, nonfinite, s);
-        case 8: return tiled_f<G, 8, PAIR>(g, tm, xyzt, eps, n, b, src, ls, qs, scale, d_table, overwrite, main, nonfinite, s);
+                          const void* src, int64_t ls, int64_t qs, double scale, void* d_table, void* ws,
+                          size_t ws_bytes, bool overwrite, const MainGradArg& main, int32_t* nonfinite,
+                          hipStream_t s) {
+    const ScatterPlan plan = scatter_plan(g, level_rows, n, (int)sizeof(G), PAIR, ws_bytes);
+    for (int i = 0; i < plan.passes; ++i) {
+        const uint32_t levels = plan.levels[i];
+        if (!levels) continue;
+        const ScatterPass w = scatter_pass(g, level_rows, n, (int)sizeof(G), PAIR, levels, plan.listed);
+        const TileMap& tm = w.tm;
+        char* at = static_cast<char*>(ws);
+        const ScatterBufs b{reinterpret_cast<uint16_t*>(at), reinterpret_cast<uint32_t*>(at + w.heads),
+                            reinterpret_cast<uint32_t*>(at + w.masks)};
+        int chunks = 0;
+        for (int l = 0; l < g.L; ++l)
+            if ((levels >> l) & 1u) chunks = std::max(chunks, pre_chunks(n, pre_chunk_log(tm, l, PAIR)));
+        hipLaunchKernelGGL(k_tile_pre<PAIR>, dim3((unsigned)chunks, (unsigned)g.L), dim3(pre_block(PAIR)), 0, s, g, tm,
+                           reinterpret_cast<const float4*>(xyzt), reinterpret_cast<const float4*>(eps), n, b.mask,
+                           b.lists, b.heads);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+#define H4D_SCATTER(FF) tiled_f<G, FF, PAIR>(g, tm, xyzt, eps, n, b, src, ls, qs, scale, d_table, overwrite, main, nonfinite, s)
+        switch (g.F) {
+            case 1: e = H4D_SCATTER(1); break;
+            case 2: e = H4D_SCATTER(2); break;
+            case 4: e = H4D_SCATTER(4); break;
+            case 8: e = H4D_SCATTER(8); break;
+            default: e = hipErrorInvalidValue;
+        }
+#undef H4D_SCATTER
+        if (e != hipSuccess) return e;
     }
-    return hipErrorInvalidValue;
+    return hipSuccess;
 }
 
 hipError_t launch_scatter_tiled(const DevGrid& g, const int64_t* level_rows, h4d_dtype grad_dt, const float* xyzt,
                                 const float* eps, int n, const void* src, int64_t ls, int64_t qs, double scale,
-                                void* d_table, void* mask_ws, hipStream_t s, bool overwrite,
+                                void* d_table, void* ws, size_t ws_bytes, hipStream_t s, bool overwrite,
                                 const MainGradArg& main, int32_t* nonfinite) {
     if (main.src && !eps) return hipErrorInvalidValue;  // the second gradient rides on the pair form only
-    if (grad_dt == H4D_F64) {
-        return eps ? tiled_g<double, true>(g, level_rows, xyzt, eps, n, src, ls, qs, scale, d_table, mask_ws,
-                                           overwrite, main, nonfinite, s)
-                   : tiled_g<double, false>(g, level_rows, xyzt, eps, n, src, ls, qs, scale, d_table, mask_ws,
-                                            overwrite, main, nonfinite, s);
-    }
-    return eps ? tiled_g<float, true>(g, level_rows, xyzt, eps, n, src, ls, qs, scale, d_table, mask_ws, overwrite,
-                                      main, nonfinite, s)
-               : tiled_g<float, false>(g, level_rows, xyzt, eps, n, src, ls, qs, scale, d_table, mask_ws, overwrite,
-                                       main, nonfinite, s);
+#define H4D_SCATTER(GG, PP) \
+    tiled_g<GG, PP>(g, level_rows, xyzt, eps, n, src, ls, qs, scale, d_table, ws, ws_bytes, overwrite, main, nonfinite, s)
+    if (grad_dt == H4D_F64) return eps ? H4D_SCATTER(double, true) : H4D_SCATTER(double, false);
+    return eps ? H4D_SCATTER(float, true) : H4D_SCATTER(float, false);
+#undef H4D_SCATTER
 }
 
 // ------------------------------------------ static workspace (no allocation) ----

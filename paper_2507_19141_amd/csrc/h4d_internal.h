@@ -72,11 +72,12 @@ struct TileMap {
     // (hashed, T a power of two of at least one tile, pi_1 = 1 and 2 N_s <= tile
     // rows: the pair's hashes differ only in bits below log2(2 N_s)).
     uint32_t pair_cotiled;
-    // Bit l set: the level's updates reach its tiles through pair lists (pair_lists.h),
-    // else through tile masks.  loose: its pairs may straddle two tiles.  On a dense list
-    // level tile_shift is the log2 of its tiles.  list_region / list_head: the level's
-    // first region of entries and first head.
-    uint32_t lists, loose;
+    // Bit l set: the level's updates reach its tiles through pair lists (pair_lists.h), or
+    // through tile masks; a level with neither bit has no tiles (another launch's levels).
+    // loose: its pairs may straddle two tiles.  On a dense list level tile_shift is the
+    // log2 of its tiles.  list_region / list_head: the level's first region of entries and
+    // first head.
+    uint32_t lists, masks, loose;
     int32_t list_region[H4D_MAX_LEVELS + 1];
     int64_t list_head[H4D_MAX_LEVELS + 1];
 };
@@ -87,15 +88,17 @@ constexpr int kListEntries = 16384;
 constexpr int kListTiles = 256;
 constexpr int list_chunk_log(bool pair, bool loose) { return 11 - (pair ? 1 : 0) - (loose ? 1 : 0); }
 constexpr int kMaskChunkLog = 11, kMaskChunk = 1 << kMaskChunkLog;
-// Tiles and lists for `segs` runs of n queries each (pair: two corner sets per query).  At
-// most list_levels levels get lists, dense levels first.
+constexpr uint32_t level_bits(int L) { return L >= 32 ? 0xffffffffu : (1u << L) - 1u; }
+// Tiles of the levels in `levels`, for `segs` runs of n queries each (pair: two corner sets
+// per query); those also in `listed` get lists where they can have them, the others masks.
 TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gbytes, int n, int segs, bool pair,
-                      int list_levels);
-// The scatter's tile masks: one 32-bit mask per (query, level) of the levels without
-// lists, level-major with the query count padded to a multiple of four so that every
-// level starts on a 16-byte boundary (the scan reads four masks per load).
+                      uint32_t levels, uint32_t listed);
+// The scatter's tile masks: one 32-bit mask per (query, level) of the levels with masks,
+// level-major with the query count padded to a multiple of four so that every level starts
+// on a 16-byte boundary (the scan reads four masks per load).
 constexpr int64_t mask_stride(int64_t n) { return (n + 3) & ~(int64_t)3; }
-// Workspace for n queries; pair: of the form with eps (two corner sets per query).
+// Workspace that the size query reports for n queries; pair: of the form with eps (two
+// corner sets per query).
 size_t scatter_ws_bytes(const DevGrid& g, const int64_t* level_rows, int n, bool pair);
 // A second feature gradient for the pair form (eps set): added, times scale, at x's
 // corners only.  src == nullptr: none.
@@ -106,8 +109,9 @@ struct MainGradArg {
 };
 hipError_t launch_scatter_tiled(const DevGrid& g, const int64_t* level_rows, h4d_dtype grad_dt, const float* xyzt,
                                 const float* eps, int n, const void* src, int64_t lstride, int64_t qstride,
-                                double scale, void* d_table, void* mask_ws, hipStream_t s, bool overwrite = false,
-                                const MainGradArg& main = MainGradArg{}, int32_t* nonfinite = nullptr);
+                                double scale, void* d_table, void* ws, size_t ws_bytes, hipStream_t s,
+                                bool overwrite = false, const MainGradArg& main = MainGradArg{},
+                                int32_t* nonfinite = nullptr);
 // The static workspace of hash4d_encode_backward_noalloc: kStaticScratchBytes of
 // device memory per GPU (a file-scope array), its address on the current device.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;

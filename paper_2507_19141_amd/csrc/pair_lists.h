@@ -235,8 +235,8 @@ __device__ __forceinline__ void tile_pre_lists(const DevGrid& g, const TileMap& 
     for (int i = threadIdx.x; i < quads; i += kPreBlock) dst[i] = src[i];
 }
 
-// One workgroup of the pre-pass: chunk `chunk` of level l, its lists or (levels without
-// lists, chunks of kMaskChunk queries) its tile masks.  tm's list offsets count chunk0 +
+// One workgroup of the pre-pass: chunk `chunk` of level l, its lists or (levels with masks,
+// chunks of kMaskChunk queries) its tile masks.  tm's list offsets count chunk0 +
 // chunk as the chunk of a longer run (segments of one scene); heads and regions are the
 // run's.
 template <bool PAIR, typename Pos>
@@ -250,7 +250,7 @@ __device__ __forceinline__ void tile_pre(const DevGrid& g, const TileMap& tm, in
         else tile_pre_lists<PAIR, false>(g, tm, l, chunk, n, pos, region, h, nchunks, sh);
         return;
     }
-    uint32_t* lm = mask + (int64_t)__popc(~tm.lists & ((1u << l) - 1u)) * mask_stride(n);
+    uint32_t* lm = mask + (int64_t)__popc(tm.masks & ((1u << l) - 1u)) * mask_stride(n);
     for (int i = 0; i < kMaskChunk / pre_block(PAIR); ++i) {
         const int q = chunk * kMaskChunk + i * pre_block(PAIR) + (int)threadIdx.x;
         if (q >= n) return;

@@ -201,3 +201,70 @@ def test_batched_scatter_over_segments(F, names, ns, zero):
             scale += O.encode_backward(xt, sf, s["og"])
         scaled_close(s["d_table"].cpu().numpy(), ref, scale, RTOL_GRAD, f"scene {i}")
     plan.destroy()
+
+
+# ---- workspace and passes ----
+WS_GRIDS = {  # L, F, space, time, T
+    "small_T": (16, 2, (16, 2048), (16, 150), 1 << 14),
+    "paper": (16, 2, (16, 2048), (16, 150), 1 << 19),
+    "loose": (8, 1, (300, 2048), (9, 20), 1 << 12),
+    "many_levels": (32, 1, (4, 2048), (4, 64), 1 << 13),
+    "one_level": (1, 2, (30, 30), (16, 16), 1 << 19),
+    "masks": (1, 8, (512, 512), (40, 40), 1 << 21),
+}
+
+
+def _ws_grid(name):
+    L, F, sp, tm, T = WS_GRIDS[name]
+    return _lib.h4d_grid_init(L, F, O.level_resolutions(*sp, L), O.level_resolutions(*tm, L), T)
+
+
+@pytest.mark.parametrize("name", WS_GRIDS)
+def test_workspace_never_shrinks(name):
+    # a workspace sized for the largest cloud serves every smaller one
+    lg = _ws_grid(name)
+    m = _lib.mlp_shape(lg.L * lg.F) if lg.L * lg.F in (8, 16, 32, 64) else None
+    ns = sorted({1, 2, 5, 7, 511, 512, 513, 2047, 2048, 2049} | set(range(1000, 600_000, 499)) | {1 << 21, 6_000_000})
+    for ws in (lambda n: _lib.hash4d_encode_backward_workspace_bytes(lg, n),
+               lambda n: _lib.smoothness_workspace_bytes(lg, _lib.F32, n),
+               lambda n: _lib.hash4d_deform_workspace_bytes(lg, m, _lib.F32, n) if m else 0):
+        sizes = [ws(n) for n in ns]
+        drops = [(a, b) for a, b, x, y in zip(ns, ns[1:], sizes, sizes[1:]) if y < x]
+        assert not drops, drops[:3]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", ["noalloc", "workspace"])
+@pytest.mark.parametrize("overwrite", [False, True], ids=["accumulate", "overwrite"])
+def test_scatter_in_several_passes(form, overwrite):
+    # lists of all levels past the bytes at hand: shares of the levels one after the other,
+    # every row and every non-finite value written once
+    needs_gpu()
+    import torch
+    L, F, sp, tm, T = WS_GRIDS["many_levels"]
+    rs, rt = O.level_resolutions(*sp, L), O.level_resolutions(*tm, L)
+    og, lg = O.make_grid(L, F, rs, rt, T), _ws_grid("many_levels")
+    n = 140_001
+    rng, x = _inputs(n, 61, False)
+    gf = synth.upstream(n, L * F, rng)
+    base = synth.table_init(og.E, F, rng, scale=1e-3)
+    d_table = _dev(np.full_like(base, np.nan) if overwrite else base)
+    layout = _lib.QUERY_MAJOR | (_lib.GRAD_OVERWRITE if overwrite else 0)
+    ref, scale = O.encode_backward(x, gf, og, 0.5), O.encode_backward(x, np.abs(gf), og, 0.5)
+    wb = _lib.hash4d_encode_backward_workspace_bytes(lg, n)
+    assert wb == 64 << 20   # what the static workspace holds, less than all lists take
+    if form == "noalloc":
+        _lib.hash4d_encode_backward_noalloc(lg, _lib.F32, _dev(x), n, _dev(gf), 0.5, d_table, layout)
+    else:
+        ws = torch.full((wb,), 0xA5, dtype=torch.uint8, device="cuda")
+        bad = torch.zeros(1, dtype=torch.int32, device="cuda")
+        gbad = gf.copy()
+        gbad[777, 5], gbad[778, 30] = np.nan, np.inf
+        d2 = d_table.clone()
+        _lib.hash4d_encode_backward_checked(lg, _lib.F32, _dev(x), n, _dev(gbad), 0.5, d2, ws, wb, bad, layout)
+        assert int(bad.item()) == int((~torch.isfinite(d2)).sum().item()) > 0
+        _lib.hash4d_encode_backward(lg, _lib.F32, _dev(x), n, _dev(gf), 0.5, d_table, ws, wb, layout)
+    torch.cuda.synchronize()
+    if not overwrite:
+        ref, scale = ref + base, scale + np.abs(base)
+    scaled_close(d_table.cpu().numpy(), ref, scale, RTOL_GRAD, f"{form} n={n}")
