@@ -268,3 +268,45 @@ def test_scatter_in_several_passes(form, overwrite):
     if not overwrite:
         ref, scale = ref + base, scale + np.abs(base)
     scaled_close(d_table.cpu().numpy(), ref, scale, RTOL_GRAD, f"{form} n={n}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", [_lib.F32, _lib.F64], ids=["f32", "f64"])
+@pytest.mark.parametrize("pair", [False, True], ids=["one_set", "two_sets"])
+@pytest.mark.parametrize("overwrite", [False, True], ids=["accumulate", "overwrite"])
+def test_lists_beside_masks(dt, pair, overwrite):
+    # a dense and a tight level with lists around two levels with more tiles than lists
+    # have: each kernel skips the other's tiles, the second mask level has the second masks
+    needs_gpu()
+    import torch
+    L, F, T, n = 5, 8, 1 << 21, 3000
+    rs, rt = [512, 3, 600, 31, 24], [40, 4, 30, 7, 19]
+    og, lg = O.make_grid(L, F, rs, rt, T), _lib.h4d_grid_init(L, F, rs, rt, T)
+    assert lg.dense_list() == [False, True, False, True, True]
+    rng, x = _inputs(n, 71, False)
+    real = np.float64 if dt == _lib.F64 else np.float32
+    gf = synth.upstream(n, L * F, rng)
+    base = synth.table_init(og.E, F, rng, scale=1e-3)
+    d_table = _dev(np.full(base.shape, np.nan, real) if overwrite else base.astype(real))
+    layout = _lib.QUERY_MAJOR | (_lib.GRAD_OVERWRITE if overwrite else 0)
+    ref, scale = O.encode_backward(x, gf, og, 0.5), O.encode_backward(x, np.abs(gf), og, 0.5)
+    if pair:
+        table, eps = synth.table_init(og.E, F, rng), synth.perturbation(n, rng, 1e-3)
+        loss = torch.zeros(1, dtype=torch.float64 if dt == _lib.F64 else torch.float32, device="cuda")
+        wb = _lib.smoothness_workspace_bytes(lg, dt, n)
+        ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
+        _lib.hash4d_encode_backward_smooth(lg, dt, _dev(table.astype(real)), _dev(x), _dev(eps), n,
+                                           _dev(gf.astype(real)), 0.5, 2.0, loss, d_table, ws, wb, layout)
+        xp = O.perturbed(x, eps)
+        d = np.abs(O.encode(x, table, og) - O.encode(xp, table, og))
+        s = 4.0 / n * (d + O.encode(x, np.abs(table), og) + O.encode(xp, np.abs(table), og))
+        scale = O.encode_backward(x, s + 0.5 * np.abs(gf), og) + O.encode_backward(xp, s, og)
+        ref = ref + O.smoothness(x, eps, table, og, 2.0)[1]
+    else:
+        wb = _lib.hash4d_encode_backward_workspace_bytes(lg, n)
+        ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
+        _lib.hash4d_encode_backward(lg, dt, _dev(x), n, _dev(gf.astype(real)), 0.5, d_table, ws, wb, layout)
+    torch.cuda.synchronize()
+    if not overwrite:
+        ref, scale = ref + base, scale + np.abs(base)
+    scaled_close(d_table.cpu().numpy(), ref, scale, 1e-12 if dt == _lib.F64 else RTOL_GRAD, f"pair={pair}")
