@@ -173,8 +173,13 @@ h4d_status hash3d_encode(const h4d_grid3* g, h4d_dtype table_dt, const void* tab
  * sums its rows' updates in LDS and adds them to d_table; no device-wide atomics.
  * A pre-pass sorts the corner pairs of every (query, level) by tile into `workspace`
  * (device, 16-byte aligned, at least hash4d_encode_backward_workspace_bytes) so that each
- * tile only works on the updates that reach it.  The LDS adds (one FP32 rounding each)
- * make the summation order, hence the last bits, vary run to run. */
+ * tile only works on the updates that reach it.  The reported size never falls as n grows.
+ * A workspace that does not hold the sorted pairs of all levels is used in passes over the
+ * levels: where 64 MiB is reported because hash4d_encode_backward_noalloc takes the call
+ * (a larger one then saves passes), and for callers that still bring the smaller size
+ * which versions without sorted pairs reported (all calls with this scatter take it).
+ * The LDS adds (one FP32 rounding each) make the summation order, hence the last bits,
+ * vary run to run. */
 size_t hash4d_encode_backward_workspace_bytes(const h4d_grid* g, int64_t n);
 h4d_status hash4d_encode_backward(const h4d_grid* g, h4d_dtype grad_dt, const float* xyzt, int64_t n,
                                   h4d_layout layout, const void* d_feat, float grad_scale, void* d_table,

@@ -164,15 +164,16 @@ static h4d_status check_mlp(const h4d_mlp* m, h4d_dtype dt) {
     return check_dtype(dt);
 }
 
-// Workspace of the tiled scatter for grid g and n queries.
-static size_t scatter_ws(const h4d_grid* g, int64_t n, bool pair = false) {
+// Workspace of the tiled scatter for grid g and n queries (least: the least it takes).
+static size_t scatter_ws(const h4d_grid* g, int64_t n, bool pair = false, bool least = false) {
     int64_t rows[H4D_MAX_LEVELS];
     rows_of(*g, rows);
-    return scatter_ws_bytes(to_device(*g), rows, (int)n, pair);
+    return least ? scatter_ws_least(to_device(*g), rows, (int)n, pair)
+                 : scatter_ws_bytes(to_device(*g), rows, (int)n, pair);
 }
 
 // Deformation backward workspace: [decoder partials | d_feat [L, n, F] | pair lists].
-// least: with the fewest decoder partials that a call takes.
+// least: the least that a call takes.
 static size_t mlp_part(const h4d_mlp* m, h4d_dtype dt, int64_t n, bool least) {
     const size_t bytes = least ? mlp_workspace_least(dt, m->in, m->out, (int)n)
                                : mlp_workspace_bytes(dt, m->in, m->out, (int)n);
@@ -182,7 +183,7 @@ static size_t deform_ws(const h4d_grid* g, const h4d_mlp* m, h4d_dtype dt, int64
     const size_t el = dt == H4D_F64 ? sizeof(double) : sizeof(float);
     const size_t a = mlp_part(m, dt, n, least);
     const size_t b = ((size_t)n * g->L * g->F * el + 255) / 256 * 256;
-    return a + b + scatter_ws(g, n);
+    return a + b + scatter_ws(g, n, false, least);
 }
 
 h4d_status validate_grid(const h4d_grid* g) { return check_grid(g); }
@@ -379,7 +380,7 @@ static h4d_status encode_backward_call(const h4d_grid* g, h4d_dtype grad_dt, con
         return hip_status(launch_zero_words(d_table, words, (hipStream_t)stream), where);
     }
     if (!d_feat || !d_table) return fail(H4D_EINVAL, "d_feat or d_table is NULL");
-    const size_t need = scatter_ws(g, n);
+    const size_t need = scatter_ws(g, n, false, !static_ws);
     if (static_ws) {
         ws_bytes = kStaticScratchBytes;
         if (need > kStaticScratchBytes)
@@ -470,9 +471,9 @@ h4d_status hash4d_corner_indices(const h4d_grid* g, const float* xyzt, int64_t n
 }
 
 // Smoothness workspace: [d = G(x) - G(x + eps), level-major | pair lists].
-static size_t smooth_ws(const h4d_grid* g, h4d_dtype table_dt, int64_t n) {
+static size_t smooth_ws(const h4d_grid* g, h4d_dtype table_dt, int64_t n, bool least = false) {
     const size_t d = ((size_t)n * g->L * g->F * (table_dt == H4D_F64 ? sizeof(double) : sizeof(float)) + 255) / 256 * 256;
-    return d + scatter_ws(g, n, true);
+    return d + scatter_ws(g, n, true, least);
 }
 
 size_t smoothness_workspace_bytes(const h4d_grid* g, h4d_dtype table_dt, int64_t n) {
@@ -492,7 +493,7 @@ h4d_status smoothness_reg(const h4d_grid* g, h4d_dtype table_dt, const void* tab
     if ((st = check_table_alignment(table, table_dt, g->F))) return st;
     if (((uintptr_t)eps) & 15u) return fail(H4D_EINVAL, "eps is not 16-byte aligned");
     if (n * (int64_t)g->L * g->F > kMaxN) return fail(H4D_EINVAL, "n L F exceeds 2^31-1 features");
-    const size_t need = smooth_ws(g, table_dt, n);
+    const size_t need = smooth_ws(g, table_dt, n, true);
     if (d_table && (!workspace || ws_bytes < need))
         return fail(H4D_EINVAL, "workspace of %zu bytes, %zu needed", workspace ? ws_bytes : (size_t)0, need);
     if (workspace && (((uintptr_t)workspace) & 15u)) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");
@@ -537,7 +538,7 @@ h4d_status hash4d_encode_backward_smooth(const h4d_grid* g, h4d_dtype table_dt, 
     if ((st = check_table_alignment(table, table_dt, g->F))) return st;
     if (((uintptr_t)eps) & 15u) return fail(H4D_EINVAL, "eps is not 16-byte aligned");
     if (n * (int64_t)g->L * g->F > kMaxN) return fail(H4D_EINVAL, "n L F exceeds 2^31-1 features");
-    const size_t need = smooth_ws(g, table_dt, n);
+    const size_t need = smooth_ws(g, table_dt, n, true);
     if (!workspace || ws_bytes < need)
         return fail(H4D_EINVAL, "workspace of %zu bytes, %zu needed", workspace ? ws_bytes : (size_t)0, need);
     if (((uintptr_t)workspace) & 15u) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");

@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kBatchScatterBlock) void k_bscatter(const BSeg* __r
             constexpr bool kLoose = decltype(loose)::value;
             walk_pair_lists<kBatchScatterBlock>(
                 nchunks, log, sc.heads + tm.list_head[l] + (int64_t)tl.tile * nchunks,
-                sc.lists + (int64_t)tm.list_region[l] * kListEntries, walk,
+                sc.lists + tm.list_entry[l], walk,
                 [&](int round, uint32_t cq, uint32_t e) {
                     const uint32_t c = (uint32_t)round + (cq >> log);
                     uint32_t seg = __umulhi(c, inv);
@@ -657,7 +657,7 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
     // tiles and pair lists of every scene
     std::vector<TileMap> tms;
     std::vector<BScene> bscenes;
-    int64_t mask_elems = 0, region_count = 0, head_count = 0;
+    int64_t mask_elems = 0, entry_count = 0, head_count = 0;
     for (int s = 0, seg0 = 0; s < n_scenes; ++s) {
         const h4d_scene_desc& d = scenes[s];
         int64_t lrows[H4D_MAX_LEVELS];
@@ -668,7 +668,7 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
         bscenes.push_back(BScene{seg0, d.n_times, (int)d.n, nullptr, nullptr, d.d_table});
         const int masked = __builtin_popcount(tm.masks);
         mask_elems += (int64_t)d.n_times * masked * mask_stride(d.n);
-        region_count += tm.list_region[d.grid.L];
+        entry_count += tm.list_entry[d.grid.L];
         head_count += tm.list_head[d.grid.L];
         p->any_masks = p->any_masks || masked > 0;
         p->any_lists = p->any_lists || tm.lists != 0u;
@@ -677,7 +677,7 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
         seg0 += d.n_times;
     }
     if ((e = hipMalloc((void**)&p->masks, std::max<int64_t>(mask_elems, 1) * sizeof(uint32_t))) != hipSuccess ||
-        (e = hipMalloc((void**)&p->lists, std::max<int64_t>(region_count, 1) * kListEntries * sizeof(uint16_t))) !=
+        (e = hipMalloc((void**)&p->lists, std::max<int64_t>(entry_count, 1) * sizeof(uint16_t))) !=
             hipSuccess ||
         (e = hipMalloc((void**)&p->heads, std::max<int64_t>(head_count, 1) * sizeof(uint32_t))) != hipSuccess)
         return bail(plan_hip(e, "plan masks"));
@@ -687,7 +687,7 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
         for (int s = 0; s < n_scenes; ++s) {
             bscenes[s].lists = lists;
             bscenes[s].heads = heads;
-            lists += (int64_t)tms[s].list_region[scenes[s].grid.L] * kListEntries;
+            lists += tms[s].list_entry[scenes[s].grid.L];
             heads += tms[s].list_head[scenes[s].grid.L];
         }
     }

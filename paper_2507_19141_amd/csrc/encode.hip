@@ -183,7 +183,7 @@ __device__ __forceinline__ void scatter_lists(const DevGrid& g, const TileMap& t
         constexpr bool kLoose = decltype(loose)::value;
         walk_pair_lists<kScatterBlock>(
             nchunks, log, heads + tm.list_head[l] + (int64_t)tr.tile * nchunks,
-            lists + (int64_t)tm.list_region[l] * kListEntries, lds,
+            lists + tm.list_entry[l], lds,
             [&](int round, uint32_t cq, uint32_t e) {
                 ListQuery<G, F, PAIR> q;
                 q.t = tile_load<G, F, PAIR>(l, xyzt, eps, src, lstride, qstride, mg, round << log,
@@ -440,8 +440,8 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
     }
     tm.lists = levels & listed & can;
     tm.masks = levels & ~tm.lists;
-    int t = 0, region = 0;
-    int64_t head = 0;
+    int t = 0;
+    int64_t entry = 0, head = 0;
     for (int l = 0; l < g.L; ++l) {
         if (!((levels >> l) & 1u)) {
             tiles[l] = 0;
@@ -454,25 +454,27 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
             }
         }
         tm.tile_start[l] = t;
-        tm.list_region[l] = region;
+        tm.list_entry[l] = entry;
         tm.list_head[l] = head;
         if ((tm.lists >> l) & 1u) {
-            const int chunks = segs * pre_chunks(n, pre_chunk_log(tm, l, pair));
-            region += chunks;
-            head += (int64_t)chunks * tiles[l];
+            const int log = pre_chunk_log(tm, l, pair), per_seg = pre_chunks(n, log);
+            if (n > 0)  // whole regions, then the last segment's last chunk
+                entry += (int64_t)kListEntries * ((int64_t)segs * per_seg - 1) +
+                         (int64_t)(kListEntries >> log) * (n - ((int64_t)(per_seg - 1) << log));
+            head += (int64_t)segs * per_seg * tiles[l];
         } else if ((tm.masks >> l) & 1u) {
             while (((tiles[l] - 1) >> tm.bit_shift[l]) >= 32) ++tm.bit_shift[l];
         }
         t += tiles[l];
     }
     tm.tile_start[g.L] = t;
-    tm.list_region[g.L] = region;
+    tm.list_entry[g.L] = entry;
     tm.list_head[g.L] = head;
     return tm;
 }
 
 // One pass of the tiled scatter (a pre-pass and a launch over some of the levels), and what
-// it takes of the workspace, each part 256-byte aligned: pair list regions | list heads |
+// it takes of the workspace, each part 256-byte aligned: pair lists | list heads |
 // masks [mask level][stride] u32.
 struct ScatterPass {
     size_t heads, masks, total;
@@ -485,7 +487,7 @@ static ScatterPass scatter_pass(const DevGrid& g, const int64_t* level_rows, int
                                 uint32_t levels, uint32_t listed) {
     ScatterPass w;
     w.tm = make_tile_map(g, level_rows, g.F, gbytes, n, 1, pair, levels, listed);
-    w.heads = (size_t)w.tm.list_region[g.L] * kListEntries * sizeof(uint16_t);
+    w.heads = align256((size_t)w.tm.list_entry[g.L] * sizeof(uint16_t));
     w.masks = w.heads + align256((size_t)w.tm.list_head[g.L] * sizeof(uint32_t));
     w.total = w.masks + align256((size_t)mask_stride(n) * __builtin_popcount(w.tm.masks) * sizeof(uint32_t));
     return w;
@@ -540,10 +542,11 @@ static ScatterPlan scatter_plan(const DevGrid& g, const int64_t* level_rows, int
     return best;
 }
 
-// The size rule behind hash4d_encode_backward_noalloc: 12 bytes per (query, level), the
+// The size that versions without pair lists reported: 12 bytes per (query, level), the
 // queries per tile of each chunk of 1024, and two partial tiles for each of up to 96
-// workgroups.  Every call within the static workspace by this rule is taken.
-static size_t noalloc_rule_bytes(const DevGrid& g, const int64_t* level_rows, int n) {
+// workgroups.  A caller may hold a workspace of that size, and the calls that
+// hash4d_encode_backward_noalloc takes were settled by it: both are still taken.
+static size_t former_ws_bytes(const DevGrid& g, const int64_t* level_rows, int n) {
     size_t slot = 0;
     int tiles = 0;
     for (int gbytes = 4; gbytes <= 8; gbytes += 4) {
@@ -566,9 +569,13 @@ size_t scatter_ws_bytes(const DevGrid& g, const int64_t* level_rows, int n, bool
     const uint32_t all = level_bits(g.L);
     const size_t bytes = std::max(scatter_pass(g, level_rows, n, 4, pair, all, all).total,
                                   scatter_pass(g, level_rows, n, 8, pair, all, all).total);
-    return !pair && bytes > kStaticScratchBytes && noalloc_rule_bytes(g, level_rows, n) <= kStaticScratchBytes
+    return !pair && bytes > kStaticScratchBytes && former_ws_bytes(g, level_rows, n) <= kStaticScratchBytes
                ? kStaticScratchBytes
                : bytes;
+}
+
+size_t scatter_ws_least(const DevGrid& g, const int64_t* level_rows, int n, bool pair) {
+    return std::min(scatter_ws_bytes(g, level_rows, n, pair), former_ws_bytes(g, level_rows, n));
 }
 
 struct ScatterBufs {

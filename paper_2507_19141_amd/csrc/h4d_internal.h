@@ -75,10 +75,9 @@ struct TileMap {
     // Bit l set: the level's updates reach its tiles through pair lists (pair_lists.h), or
     // through tile masks; a level with neither bit has no tiles (another launch's levels).
     // loose: its pairs may straddle two tiles.  On a dense list level tile_shift is the
-    // log2 of its tiles.  list_region / list_head: the level's first region of entries and
-    // first head.
+    // log2 of its tiles.  list_entry / list_head: the level's first entry and first head.
     uint32_t lists, masks, loose;
-    int32_t list_region[H4D_MAX_LEVELS + 1];
+    int64_t list_entry[H4D_MAX_LEVELS + 1];
     int64_t list_head[H4D_MAX_LEVELS + 1];
 };
 // Pair lists: entries of one region, tiles of a list level at most, and the log2 of the
@@ -98,8 +97,9 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
 // on a 16-byte boundary (the scan reads four masks per load).
 constexpr int64_t mask_stride(int64_t n) { return (n + 3) & ~(int64_t)3; }
 // Workspace that the size query reports for n queries; pair: of the form with eps (two
-// corner sets per query).
+// corner sets per query); and the least that a call takes.
 size_t scatter_ws_bytes(const DevGrid& g, const int64_t* level_rows, int n, bool pair);
+size_t scatter_ws_least(const DevGrid& g, const int64_t* level_rows, int n, bool pair);
 // A second feature gradient for the pair form (eps set): added, times scale, at x's
 // corners only.  src == nullptr: none.
 struct MainGradArg {

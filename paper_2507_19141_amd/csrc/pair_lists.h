@@ -7,8 +7,9 @@
 // reads exactly its own pairs, one per lane, in query order, so that neighbouring lanes'
 // loads of positions and gradients share cache lines.
 //
-// A chunk's entries fill at most one region of kListEntries; chunk c of list level l is
-// region list_region[l] + c, and heads[list_head[l] + tile * chunks + c] holds the first
+// A chunk's entries fill at most one region of kListEntries (the last chunk's is as short as
+// its queries allow); chunk c of list level l starts at entry list_entry[l] + c
+// kListEntries, and heads[list_head[l] + tile * chunks + c] holds the first
 // entry and the count of the tile's run in it.
 //
 // Tiles of a list level (make_tile_map):
@@ -244,7 +245,7 @@ __device__ __forceinline__ void tile_pre(const DevGrid& g, const TileMap& tm, in
                                          int nchunks, int n, Pos pos, uint32_t* __restrict__ mask,
                                          uint16_t* __restrict__ lists, uint32_t* __restrict__ heads, PreShared<PAIR>& sh) {
     if ((tm.lists >> l) & 1u) {
-        uint16_t* region = lists + (int64_t)(tm.list_region[l] + chunk0 + chunk) * kListEntries;
+        uint16_t* region = lists + tm.list_entry[l] + (int64_t)(chunk0 + chunk) * kListEntries;
         uint32_t* h = heads + tm.list_head[l] + chunk0;
         if ((tm.loose >> l) & 1u) tile_pre_lists<PAIR, true>(g, tm, l, chunk, n, pos, region, h, nchunks, sh);
         else tile_pre_lists<PAIR, false>(g, tm, l, chunk, n, pos, region, h, nchunks, sh);

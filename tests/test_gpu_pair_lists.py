@@ -310,3 +310,69 @@ def test_lists_beside_masks(dt, pair, overwrite):
     if not overwrite:
         ref, scale = ref + base, scale + np.abs(base)
     scaled_close(d_table.cpu().numpy(), ref, scale, 1e-12 if dt == _lib.F64 else RTOL_GRAD, f"pair={pair}")
+
+
+@pytest.mark.parametrize("name", WS_GRIDS)
+@pytest.mark.parametrize("n", [5, 100, 1000])
+def test_workspace_of_few_queries(name, n):
+    # the lists take what the queries can fill: 16 bytes per (query, level), twice that for
+    # two corner sets or pairs that straddle tiles, and a head per tile
+    lg = _ws_grid(name)
+    tiles = 4 * 256 * lg.L + 512
+    assert _lib.hash4d_encode_backward_workspace_bytes(lg, n) <= 32 * n * lg.L + tiles
+    d = (4 * n * lg.L * lg.F + 255) // 256 * 256
+    assert _lib.smoothness_workspace_bytes(lg, _lib.F32, n) - d <= 64 * n * lg.L + 2 * tiles
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("entry", ["encode", "smooth", "encode_smooth", "deform"])
+def test_workspace_of_the_former_size(entry):
+    # the size reported before the scatter sorted pairs is still taken, one byte less is not
+    needs_gpu()
+    import torch
+    L, F, sp, tm, T = WS_GRIDS["many_levels"]
+    rs, rt = O.level_resolutions(*sp, L), O.level_resolutions(*tm, L)
+    og, lg = O.make_grid(L, F, rs, rt, T), _ws_grid("many_levels")
+    n = 9_001
+    rng, x = _inputs(n, 83, False)
+    gf, table = synth.upstream(n, L * F, rng), synth.table_init(og.E, F, rng)
+    eps = synth.perturbation(n, rng, 1e-3)
+    former = _static_rule(L, F, rs, rt, T, n)
+    al = lambda b: (b + 255) // 256 * 256  # noqa: E731
+    xd, loss, d_table = _dev(x), torch.zeros(1, device="cuda"), torch.zeros((og.E, F), device="cuda")
+    xp = O.perturbed(x, eps)
+    s = 4.0 / n * (np.abs(O.encode(x, table, og) - O.encode(xp, table, og)) + O.encode(x, np.abs(table), og)
+                   + O.encode(xp, np.abs(table), og))
+    if entry == "encode":
+        assert _lib.hash4d_encode_backward_workspace_bytes(lg, n) > former
+        wb, call = former, lambda ws, b: _lib.hash4d_encode_backward(lg, _lib.F32, xd, n, _dev(gf), 1.0, d_table, ws, b)
+        ref, scale = O.encode_backward(x, gf, og), O.encode_backward(x, np.abs(gf), og)
+    elif entry == "deform":
+        m, params = _lib.mlp_shape(L * F), synth.decoder_params(L * F, rng)
+        gd, feat, delta = synth.upstream(n, 10, rng), torch.empty((L, n, F), device="cuda"), torch.empty((n, 10), device="cuda")
+        pd, d_params = _dev(params), torch.zeros(params.size, device="cuda")
+        _lib.hash4d_deform_forward(lg, m, _lib.F32, _dev(table), pd, xd, n, feat, delta)
+        rows = min(256, ((n + 15) // 16 + 7) // 8)      # decoder partials of eight tiles each
+        wb = al(rows * params.size * 4) + al(4 * n * L * F) + former
+        call = lambda ws, b: _lib.hash4d_deform_backward(lg, m, _lib.F32, pd, xd, n, feat, _dev(gd), 1.0, 1.0,  # noqa: E731
+                                                         d_table, d_params, ws, b)
+        ref = O.deform_backward(x, table, og, params, gd)[0]
+        scale = O.encode_backward(x, mlp_backward_scale(params, O.encode(x, table, og), gd)[0], og)
+    else:
+        wb = al(4 * n * L * F) + former
+        assert _lib.smoothness_workspace_bytes(lg, _lib.F32, n) > wb
+        ref = O.smoothness(x, eps, table, og, 2.0)[1]
+        scale = O.encode_backward(x, s, og) + O.encode_backward(xp, s, og)
+        if entry == "smooth":
+            call = lambda ws, b: _lib.smoothness_reg(lg, _lib.F32, _dev(table), xd, _dev(eps), n, 2.0, loss, d_table,  # noqa: E731
+                                                     ws, b)
+        else:
+            call = lambda ws, b: _lib.hash4d_encode_backward_smooth(lg, _lib.F32, _dev(table), xd, _dev(eps), n,  # noqa: E731
+                                                                    _dev(gf), 1.0, 2.0, loss, d_table, ws, b)
+            ref, scale = ref + O.encode_backward(x, gf, og), scale + O.encode_backward(x, np.abs(gf), og)
+    ws = torch.full((wb,), 0xA5, dtype=torch.uint8, device="cuda")
+    with pytest.raises(_lib.H4DError, match="workspace"):
+        call(ws, wb - 1)
+    call(ws, wb)
+    torch.cuda.synchronize()
+    scaled_close(d_table.cpu().numpy(), ref, scale, RTOL_GRAD, entry)
