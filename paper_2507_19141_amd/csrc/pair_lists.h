@@ -474,6 +474,23 @@ __device__ __forceinline__ void add_pair(G* tile, uint32_t cnt, uint32_t r0, con
 // (below 2^21); the first round's queries start at query 0 of the run.
 constexpr int kWalkChunks = 1024;
 constexpr int kWalkLds = 2 * kWalkChunks + 16;
+
+// A wavefront holds the descriptions of batches base .. base + 63 of its range, which ends
+// before batch b1.  It reads on for up to three batches past the end (the last batch again)
+// and describes no batch there, so that the lane it reads from stays one of its 64.
+__host__ __device__ constexpr bool walk_describes(int next, int base, int b1) { return next < b1 && next - base >= 64; }
+__host__ __device__ constexpr int walk_lane(int next, int base, int b1) { return (next < b1 ? next : b1 - 1) - base; }
+constexpr bool walk_lanes_exist(int b1) {
+    for (int next = 0, base = 0; next < b1 + 6; ++next) {
+        if (walk_describes(next, base, b1)) base = next;
+        if (walk_lane(next, base, b1) < 0 || walk_lane(next, base, b1) > 63) return false;
+    }
+    return true;
+}
+static_assert(walk_lanes_exist(1) && walk_lanes_exist(2) && walk_lanes_exist(62) && walk_lanes_exist(63) &&
+                  walk_lanes_exist(64) && walk_lanes_exist(65) && walk_lanes_exist(127) && walk_lanes_exist(128),
+              "ranges of whole sets of 64 batches and next to them");
+
 template <int BLOCK, typename Load, typename Run>
 __device__ __forceinline__ void walk_pair_lists(int nchunks, int chunk_log, const uint32_t* __restrict__ heads,
                                                 const uint16_t* __restrict__ lists, int* lds, Load load, Run run) {
@@ -533,8 +550,8 @@ __device__ __forceinline__ void walk_pair_lists(int nchunks, int chunk_log, cons
         };
         int next = b0;
         auto fetch = [&](Batch& b) {  // the next batch of the range, none past its end
-            if (next - dbase >= 64) describe(next);
-            const int i = min(next, b1 - 1) - dbase;
+            if (walk_describes(next, dbase, b1)) describe(next);
+            const int i = walk_lane(next, dbase, b1);
             b.cn = (uint32_t)__builtin_amdgcn_readlane((int)dcn, i);
             const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)doff, i);
             b.e = *reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(rl) +

@@ -376,3 +376,23 @@ def test_workspace_of_the_former_size(entry):
     call(ws, wb)
     torch.cuda.synchronize()
     scaled_close(d_table.cpu().numpy(), ref, scale, RTOL_GRAD, entry)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batches", [1, 2, 3, 63, 64, 65, 128])
+def test_walk_ranges_of_whole_descriptions(batches):
+    # eight tiles that every query reaches once: `batches` batches of 64 entries for each of
+    # a tile's 16 wavefronts, up to the end of what a wavefront describes at a time
+    needs_gpu()
+    import torch
+    og, lg = O.make_grid(1, 2, [1], [1], 16), _lib.h4d_grid_init(1, 2, [1], [1], 16)
+    n = 64 * 16 * batches
+    rng = np.random.default_rng(batches)
+    x = synth.uniform_xyzt(n, rng)
+    gf = synth.upstream(n, 2, rng)
+    wb = _lib.hash4d_encode_backward_workspace_bytes(lg, n)
+    ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
+    d_table = torch.full((og.E, 2), float("nan"), device="cuda")
+    _lib.hash4d_encode_backward(lg, _lib.F32, _dev(x), n, _dev(gf), 1.0, d_table, ws, wb, _lib.GRAD_OVERWRITE)
+    torch.cuda.synchronize()
+    scaled_close(d_table.cpu().numpy(), O.encode_backward(x, gf, og), O.encode_backward(x, np.abs(gf), og), RTOL_GRAD)
