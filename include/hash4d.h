@@ -251,9 +251,11 @@ h4d_status hash4d_deform_apply(const float* delta, int64_t n, int32_t out, const
  *   *loss   += lambda / n * sum_q ||d_q||^2
  *   d_table += (2 lambda / n) (d w at x's corners - d w~ at x~'s corners)
  * Both encodes are recomputed per query and level, nothing is kept between calls.
- * d_table may be NULL (loss only, no workspace needed).  Otherwise `workspace`
- * (device, smoothness_workspace_bytes) receives d and the scatter's sorted pairs, and
- * the gradient is added by the tiled scatter.  table_dt as hash4d_encode; loss and d_table are FP32 (FP64
+ * d_table may be NULL (loss only, no workspace needed; the FP32 partial sums of 256 queries
+ * of a level are then added in order of arrival).  Otherwise `workspace`
+ * (device, smoothness_workspace_bytes) receives d, the loss's partial sums (added in a fixed
+ * order and in 64 bits) and the scatter's sorted pairs, and the gradient is added by the
+ * tiled scatter.  table_dt as hash4d_encode; loss and d_table are FP32 (FP64
  * for F64).  eps: FP32 [n, 4], 16-byte aligned. */
 size_t smoothness_workspace_bytes(const h4d_grid* g, h4d_dtype table_dt, int64_t n);
 h4d_status smoothness_reg(const h4d_grid* g, h4d_dtype table_dt, const void* table, const float* xyzt,

@@ -471,9 +471,11 @@ h4d_status hash4d_corner_indices(const h4d_grid* g, const float* xyzt, int64_t n
 }
 
 // Smoothness workspace: [d = G(x) - G(x + eps), level-major | pair lists].
+static size_t smooth_d_bytes(const h4d_grid* g, h4d_dtype table_dt, int64_t n) {
+    return ((size_t)n * g->L * g->F * (table_dt == H4D_F64 ? sizeof(double) : sizeof(float)) + 255) / 256 * 256;
+}
 static size_t smooth_ws(const h4d_grid* g, h4d_dtype table_dt, int64_t n, bool least = false) {
-    const size_t d = ((size_t)n * g->L * g->F * (table_dt == H4D_F64 ? sizeof(double) : sizeof(float)) + 255) / 256 * 256;
-    return d + scatter_ws(g, n, true, least);
+    return smooth_d_bytes(g, table_dt, n) + scatter_ws(g, n, true, least);
 }
 
 size_t smoothness_workspace_bytes(const h4d_grid* g, h4d_dtype table_dt, int64_t n) {
@@ -499,17 +501,18 @@ h4d_status smoothness_reg(const h4d_grid* g, h4d_dtype table_dt, const void* tab
     if (workspace && (((uintptr_t)workspace) & 15u)) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");
     const DevGrid d = to_device(*g);
     const hipStream_t s = (hipStream_t)stream;
-    // pass 1: loss and the feature difference d = G(x) - G(x + eps), level-major [L, n, F]
+    const size_t dbytes = smooth_d_bytes(g, table_dt, n);
+    // pass 1: loss and the feature difference d = G(x) - G(x + eps), level-major [L, n, F];
+    // the loss's partial sums lie where pass 2 puts its pair lists
     if ((st = hip_status(launch_smoothness(d, table_dt, table, xyzt, eps, (int)n, (double)lambda, loss,
-                                           d_table ? workspace : nullptr, s),
+                                           d_table ? workspace : nullptr,
+                                           d_table ? static_cast<char*>(workspace) + dbytes : nullptr, s),
                          "smoothness_reg/diff")))
         return st;
     if (!d_table) return H4D_OK;
     // pass 2: d_table += (2 lambda / n) (d at x's corners - d at x~'s corners)
     int64_t rows[H4D_MAX_LEVELS];
     rows_of(*g, rows);
-    const size_t dbytes =
-        ((size_t)n * g->L * g->F * (table_dt == H4D_F64 ? sizeof(double) : sizeof(float)) + 255) / 256 * 256;
     return hip_status(launch_scatter_tiled(d, rows, table_dt == H4D_F64 ? H4D_F64 : H4D_F32, xyzt, eps, (int)n,
                                            workspace, n * g->F, g->F, 2.0 * (double)lambda / (double)n, d_table,
                                            static_cast<char*>(workspace) + dbytes, ws_bytes - dbytes, s),
@@ -543,16 +546,16 @@ h4d_status hash4d_encode_backward_smooth(const h4d_grid* g, h4d_dtype table_dt, 
         return fail(H4D_EINVAL, "workspace of %zu bytes, %zu needed", workspace ? ws_bytes : (size_t)0, need);
     if (((uintptr_t)workspace) & 15u) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");
     const DevGrid d = to_device(*g);
-    // pass 1: loss and d = G(x) - G(x + eps), level-major [L, n, F]
-    if ((st = hip_status(launch_smoothness(d, table_dt, table, xyzt, eps, (int)n, (double)lambda, loss, workspace, s),
+    const size_t dbytes = smooth_d_bytes(g, table_dt, n);
+    // pass 1: loss and d = G(x) - G(x + eps), level-major [L, n, F], as in smoothness_reg
+    if ((st = hip_status(launch_smoothness(d, table_dt, table, xyzt, eps, (int)n, (double)lambda, loss, workspace,
+                                           static_cast<char*>(workspace) + dbytes, s),
                          "hash4d_encode_backward_smooth/diff")))
         return st;
     // pass 2: one scatter over both corner sets: x's corners get (2 lambda / n) d +
     // grad_scale d_feat, x~'s corners get -(2 lambda / n) d
     int64_t rows[H4D_MAX_LEVELS];
     rows_of(*g, rows);
-    const size_t dbytes =
-        ((size_t)n * g->L * g->F * (table_dt == H4D_F64 ? sizeof(double) : sizeof(float)) + 255) / 256 * 256;
     MainGradArg main;
     main.src = d_feat;
     main.lstride = ls;

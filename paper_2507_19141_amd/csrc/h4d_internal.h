@@ -205,9 +205,11 @@ hipError_t launch_deform_apply(const float* delta, int n, int out, const float* 
                                float* xo, float* ro, float* so, hipStream_t st);
 
 // ---- smoothness regulariser (smooth.hip) ----
-// Loss (+=) and, if d_out != NULL, the level-major difference G(x) - G(x + eps).
+// Loss (+=) and, if d_out != NULL, the level-major difference G(x) - G(x + eps).  sums:
+// NULL, or at least 8 bytes per level and (started) 256 queries, used until the loss is
+// added; with it the loss is summed in a fixed order and in 64 bits.
 hipError_t launch_smoothness(const DevGrid& g, h4d_dtype dt, const void* table, const float* xyzt, const float* eps,
-                             int n, double lam, void* loss, void* d_out, hipStream_t s);
+                             int n, double lam, void* loss, void* d_out, void* sums, hipStream_t s);
 
 // ---- roofline probes (probe.hip) ----
 hipError_t launch_probe_gather(const void* table, uint32_t rows, int row_bytes, int64_t n_loads, uint32_t seed,

@@ -278,3 +278,30 @@ def test_position_path_writes_every_gradient_element(n):
         sf, sp = mlp_backward_scale(params, f_ref, gd)
         scaled_close(gt, O.encode_backward(x, rf, og), O.encode_backward(x, sf, og), RTOL_GRAD, "d_table")
         scaled_close(gp, rp, sp, RTOL_GRAD, "d_params")
+
+
+@pytest.mark.parametrize("dt", [_lib.F32, _lib.F64], ids=["f32", "f64"])
+@pytest.mark.parametrize("n", [1, 257, 200_001])
+def test_smoothness_loss_is_summed_in_one_order(dt, n):
+    # against the 64-bit sum of the squares of the differences that the call itself wrote:
+    # a square, F - 1 adds, 6 + 3 adds of a workgroup's sum and the result are rounded
+    needs_gpu()
+    import torch
+    L, F, T = 16, 2, 1 << 16
+    lg = _lib.h4d_grid_init(L, F, _lib.h4d_grid_schedule(L, 16, 2048), _lib.h4d_grid_schedule(L, 16, 150), T)
+    real = torch.float64 if dt == _lib.F64 else torch.float32
+    rng = np.random.default_rng(17 + n)
+    x, eps = synth.uniform_xyzt(n, rng), synth.perturbation(n, rng, 1e-2)
+    table = torch.from_numpy(synth.table_init(lg.E, F, rng)).cuda().to(real)
+    xd, ed = torch.from_numpy(x).cuda(), torch.from_numpy(eps).cuda()
+    wb = _lib.smoothness_workspace_bytes(lg, dt, n)
+    got = []
+    for _ in range(2):
+        loss, d_table = torch.zeros(1, dtype=real, device="cuda"), torch.zeros((lg.E, F), dtype=real, device="cuda")
+        ws = torch.zeros(wb, dtype=torch.uint8, device="cuda")
+        _lib.smoothness_reg(lg, dt, table, xd, ed, n, 0.5, loss, d_table, ws, wb)
+        d = ws[: n * L * F * loss.element_size()].view(real).double()
+        ref = 0.5 / n * float((d * d).sum().item())
+        got.append(float(loss.item()))
+    assert got[0] == got[1]
+    assert ref > 0 and abs(got[0] - ref) <= (F + 10) * (2.0**-53 if dt == _lib.F64 else 2.0**-24) * ref + 1e-15 * ref
