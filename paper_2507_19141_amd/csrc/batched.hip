@@ -21,8 +21,6 @@
 
 namespace h4d {
 
-constexpr int kBatchBlock = 256;
-
 struct BSeg {
     const float4* xyz;   // scene positions [n, 4]; the 4th value is replaced by t
     float t;
@@ -374,16 +372,18 @@ static hipError_t upload_ranges(BRange** dst, const std::vector<BRange>& r) {
     return e;
 }
 
-// Workgroups of a schedule: whole rounds of the XCDs, no more than the items need.
-static int encode_grid(const BSchedule& s, int items) {
-    const int all = (items + kXcds - 1) / kXcds * kXcds;
-    return s.grid > 0 ? std::min(s.grid, all) : all;
+// A launch has fewer than 2^32 threads in a dimension, and a plan may have more (query,
+// timestamp, level) triples than that; a smaller grid walks the list.
+int batch_encode_grid(int want, int items) {
+    constexpr int64_t kMost = ((int64_t)1 << 32) / kBatchBlock - kXcds;
+    const int all = (int)std::min(((int64_t)items + kXcds - 1) / kXcds * kXcds, kMost);
+    return want > 0 ? std::min(want, all) : all;
 }
 
 static hipError_t launch_bencode(const h4d_batched_plan& p, const BSchedule& s, hipStream_t st) {
     if (p.total_enc == 0) return hipSuccess;
     const int F = p.scenes[0].grid.F;
-    const dim3 grid(encode_grid(s, p.total_enc)), block(kBatchBlock);
+    const dim3 grid(batch_encode_grid(s.grid, p.total_enc)), block(kBatchBlock);
     // the wide form needs every scene's table to allow it
     bool wide = true;
     for (int i = 0; i < p.n_scenes; ++i) {
@@ -574,7 +574,8 @@ static hipError_t autotune(h4d_batched_plan& p, const std::vector<BSeg>& segs, h
             for (int gsz : grids) {
                 if (e != hipSuccess) continue;
                 const BSchedule cand{qpt, lpb, gsz};
-                if ((e = install(cand)) != hipSuccess || (e = launch_bencode(p, cand, st)) != hipSuccess) continue;
+                if ((e = install(cand)) != hipSuccess) continue;
+                if (launch_bencode(p, cand, st) != hipSuccess) continue;  // not launched: no candidate
                 hipEventRecord(a, st);
                 for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) e = launch_bencode(p, cand, st);
                 hipEventRecord(b, st);
@@ -583,7 +584,7 @@ static hipError_t autotune(h4d_batched_plan& p, const std::vector<BSeg>& segs, h
                 if (e == hipSuccess) e = hipEventElapsedTime(&ms, a, b);
                 if (e != hipSuccess) continue;
                 ms /= 3.f;
-                p.tuned.push_back(h4d_tune_result{0, qpt, lpb, encode_grid(cand, p.total_enc), ms});
+                p.tuned.push_back(h4d_tune_result{0, qpt, lpb, batch_encode_grid(cand.grid, p.total_enc), ms});
                 if (ms < best) {
                     best = ms;
                     best_s = cand;
@@ -835,7 +836,7 @@ h4d_status hash4d_batched_plan_info(const h4d_batched_plan* p, h4d_batched_info*
     info->segments = p->nseg;
     info->encode_qpt = p->enc.qpt;
     info->encode_lpb = p->enc.lpb;
-    info->encode_grid = encode_grid(p->enc, p->total_enc);
+    info->encode_grid = batch_encode_grid(p->enc.grid, p->total_enc);
     info->scatter_tiles = p->ntiles;
     info->scatter_rows_per_tile = kTileBytes / (p->scenes[0].grid.F * (int)sizeof(float));
     info->graph = p->exec != nullptr;

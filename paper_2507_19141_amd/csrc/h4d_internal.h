@@ -138,6 +138,12 @@ hipError_t launch_encode_input_grad(const DevGrid& g, h4d_dtype dt, const void* 
                                     hipStream_t s, void* ws = nullptr);
 size_t input_grad_workspace_bytes(int L, int n);
 
+// ---- batched plan (batched.hip) ----
+// Workgroups of the batched encode over `items` work items: whole rounds of the XCDs, no
+// more than the items need, than `want` (0: any number) and than a launch can have.
+constexpr int kBatchBlock = 256;
+int batch_encode_grid(int want, int items);
+
 // ---- decoder launchers (mlp.hip) ----
 constexpr int kMaxMlpSpans = 16;
 

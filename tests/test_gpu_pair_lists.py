@@ -396,3 +396,14 @@ def test_walk_ranges_of_whole_descriptions(batches):
     _lib.hash4d_encode_backward(lg, _lib.F32, _dev(x), n, _dev(gf), 1.0, d_table, ws, wb, _lib.GRAD_OVERWRITE)
     torch.cuda.synchronize()
     scaled_close(d_table.cpu().numpy(), O.encode_backward(x, gf, og), O.encode_backward(x, np.abs(gf), og), RTOL_GRAD)
+
+
+def test_batched_encode_grid_can_be_launched():
+    # one workgroup of 256 threads per item up to the largest launch (below 2^32 threads),
+    # whole rounds of the eight XCDs; a smaller grid where one is asked for
+    grid = _lib.load()["_ZN3h4d17batch_encode_gridEii"]
+    for items in (1, 7, 8, 9, 1000, (1 << 24) - 9, (1 << 24) - 8, 1 << 24, (1 << 24) + 1, (1 << 30) + 5, (1 << 31) - 1):
+        g = grid(0, items)
+        assert g % 8 == 0 and 0 < g * 256 < 1 << 32
+        assert g == min((items + 7) // 8 * 8, (1 << 24) - 8)
+        assert grid(1024, items) == min(1024, g)
