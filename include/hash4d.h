@@ -475,7 +475,9 @@ typedef struct {
 
 /* Build a plan for n_scenes (1..16) scenes sharing F and the decoder shape m, in
  * dt F32 or BF16.  The plan owns device memory of its own (work lists, per-segment
- * feature gradients, decoder partials; freed by destroy).  With AUTOTUNE the
+ * feature gradients, decoder partials, and the scatter's sorted pairs: 16 to 33 bytes per
+ * query, timestamp and level, or 4 where that much cannot be allocated and the scatter
+ * scans tile masks instead, which is slower; freed by destroy).  With AUTOTUNE the
  * candidate schedules (queries per thread x levels per item x grid size) of the
  * batched encode kernel are timed on `stream` with the scenes' own data (they
  * write `feat`).  The scatter runs one workgroup per (scene, level, tile of table

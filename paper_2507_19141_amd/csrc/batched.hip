@@ -601,11 +601,13 @@ static hipError_t autotune(h4d_batched_plan& p, const std::vector<BSeg>& segs, h
 
 }  // namespace h4d
 
-extern "C" {
-
-h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_desc* scenes, int32_t n_scenes,
-                                      const h4d_mlp* m, h4d_dtype dt, float loss_scale, int32_t flags, void* stream) {
+// lists: pair lists where the levels can have them, else masks on every level.  err: the
+// HIP error behind H4D_EHIP.
+static h4d_status create_plan(h4d_batched_plan** out, const h4d_scene_desc* scenes, int32_t n_scenes, const h4d_mlp* m,
+                              h4d_dtype dt, float loss_scale, int32_t flags, void* stream, bool lists,
+                              hipError_t* err) {
     clear_error();
+    *err = hipSuccess;
     if (!out) return plan_fail(H4D_EINVAL, "plan output pointer is NULL");
     *out = nullptr;
     if (!scenes || n_scenes < 1 || n_scenes > H4D_MAX_SCENES)
@@ -641,8 +643,10 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
     p->scenes.assign(scenes, scenes + n_scenes);
     p->queries = queries;
     const hipStream_t st = (hipStream_t)stream;
+    hipError_t e;
     auto bail = [&](h4d_status s2) {
         hash4d_batched_plan_destroy(p);
+        *err = e;
         return s2;
     };
     // grids and segments
@@ -653,7 +657,7 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
         p->grids_h.push_back(to_device(d.grid));
         dfeat_elems += (int64_t)d.n_times * d.grid.L * d.n * d.grid.F;
     }
-    hipError_t e = hipMalloc((void**)&p->d_feat, std::max<int64_t>(dfeat_elems, 1) * sizeof(float));
+    e = hipMalloc((void**)&p->d_feat, std::max<int64_t>(dfeat_elems, 1) * sizeof(float));
     if (e != hipSuccess) return bail(plan_hip(e, "plan d_feat"));
     // tiles and pair lists of every scene
     std::vector<TileMap> tms;
@@ -664,7 +668,7 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
         int64_t lrows[H4D_MAX_LEVELS];
         for (int l = 0; l < d.grid.L; ++l) lrows[l] = d.grid.offset[l + 1] - d.grid.offset[l];
         const TileMap tm = make_tile_map(p->grids_h[s], lrows, d.grid.F, (int)sizeof(float), (int)d.n, d.n_times, false,
-                                         level_bits(d.grid.L), level_bits(d.grid.L));
+                                         level_bits(d.grid.L), lists ? level_bits(d.grid.L) : 0u);
         tms.push_back(tm);
         bscenes.push_back(BScene{seg0, d.n_times, (int)d.n, nullptr, nullptr, d.d_table});
         const int masked = __builtin_popcount(tm.masks);
@@ -683,12 +687,12 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
         (e = hipMalloc((void**)&p->heads, std::max<int64_t>(head_count, 1) * sizeof(uint32_t))) != hipSuccess)
         return bail(plan_hip(e, "plan masks"));
     {
-        uint16_t* lists = p->lists;
+        uint16_t* entries = p->lists;
         uint32_t* heads = p->heads;
         for (int s = 0; s < n_scenes; ++s) {
-            bscenes[s].lists = lists;
+            bscenes[s].lists = entries;
             bscenes[s].heads = heads;
-            lists += tms[s].list_entry[scenes[s].grid.L];
+            entries += tms[s].list_entry[scenes[s].grid.L];
             heads += tms[s].list_head[scenes[s].grid.L];
         }
     }
@@ -802,6 +806,19 @@ h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_de
     }
     *out = p;
     return H4D_OK;
+}
+
+extern "C" {
+
+// The lists take 16 to 33 bytes per (query, timestamp, level), masks 4: a plan whose lists
+// do not fit in the card's memory is made without.
+h4d_status hash4d_batched_plan_create(h4d_batched_plan** out, const h4d_scene_desc* scenes, int32_t n_scenes,
+                                      const h4d_mlp* m, h4d_dtype dt, float loss_scale, int32_t flags, void* stream) {
+    hipError_t e;
+    h4d_status st = create_plan(out, scenes, n_scenes, m, dt, loss_scale, flags, stream, true, &e);
+    if (e != hipErrorOutOfMemory) return st;
+    (void)hipGetLastError();
+    return create_plan(out, scenes, n_scenes, m, dt, loss_scale, flags, stream, false, &e);
 }
 
 h4d_status hash4d_batched_forward(h4d_batched_plan* p, void* stream) {

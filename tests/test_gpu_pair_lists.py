@@ -407,3 +407,19 @@ def test_batched_encode_grid_can_be_launched():
         assert g % 8 == 0 and 0 < g * 256 < 1 << 32
         assert g == min((items + 7) // 8 * 8, (1 << 24) - 8)
         assert grid(1024, items) == min(1024, g)
+
+
+@pytest.mark.gpu
+def test_batched_plan_whose_lists_do_not_fit():
+    # 9.6e9 (query, timestamp, level) triples: lists of 307 GB are more than the card has,
+    # so the plan is made with masks (38 GB, and 38 GB of feature gradients); it is not run,
+    # and its buffers are never touched
+    needs_gpu()
+    import torch
+    L, n, times = 8, 240_000_000, [0.0, 0.25, 0.5, 0.75, 1.0]
+    lg = _lib.h4d_grid_init(L, 1, [2047] * L, [3] * L, 1 << 11)
+    one = torch.zeros(64, device="cuda")
+    plan = _lib.BatchedPlan([_lib.scene_desc(lg, n, one, times, *[one] * 7)], _lib.mlp_shape(L), _lib.F32)
+    info = plan.info()
+    assert info.queries == n * len(times) and info.encode_grid * 256 < 1 << 32
+    plan.destroy()
