@@ -281,8 +281,24 @@ __device__ __forceinline__ void gather_pairs(const TT* __restrict__ table, uint3
     }
 }
 
-// Rows x and y of gather_pairs for the 8 pairs of a cell of the 4D grid.
-__device__ __forceinline__ void pair_rows_xy(const DevGrid& g, int l, const Cell& c, uint32_t (&x)[8], uint32_t (&y)[8]) {
+// Quadrilinear weights along the axes, and of the corners of x-pair p: the products of
+// level_weights in its order.
+template <typename W>
+struct AxisWeights {
+    W x[2], y[2], z[2], t[2];
+    __device__ __forceinline__ explicit AxisWeights(const Cell& c)
+        : x{W(1) - W(c.fx), W(c.fx)}, y{W(1) - W(c.fy), W(c.fy)}, z{W(1) - W(c.fz), W(c.fz)}, t{W(1) - W(c.ft), W(c.ft)} {}
+    __device__ __forceinline__ void pair(int p, W& lo, W& hi) const {
+        const W wy = p & 1 ? y[1] : y[0], wz = p & 2 ? z[1] : z[0], wt = p & 4 ? t[1] : t[0];
+        lo = ((x[0] * wy) * wz) * wt;
+        hi = ((x[1] * wy) * wz) * wt;
+    }
+};
+
+// Rows x and y of gather_pairs for N pairs p0, p0 + 1, .. of a cell of the 4D grid.
+template <int N>
+__device__ __forceinline__ void pair_rows_xy(const DevGrid& g, int l, const Cell& c, int p0, uint32_t (&x)[N],
+                                             uint32_t (&y)[N]) {
     const uint32_t odd = threadIdx.x & 1u;
     const uint32_t off = g.off[l], ix = (uint32_t)c.ix + odd, iy = (uint32_t)c.ix + (odd ^ 1u);
     if ((g.dense_bits >> l) & 1u) {
@@ -290,10 +306,11 @@ __device__ __forceinline__ void pair_rows_xy(const DevGrid& g, int l, const Cell
         const uint32_t S2 = S * S, S3 = S2 * S;
         const uint32_t base = off + S * ((uint32_t)c.iy + S * ((uint32_t)c.iz + S * (uint32_t)c.it));
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
+        for (int j = 0; j < N; ++j) {
+            const int p = p0 + j;
             const uint32_t line = base + (p & 1) * S + ((p >> 1) & 1) * S2 + (p >> 2) * S3;
-            x[p] = line + ix;
-            y[p] = line + iy;
+            x[j] = line + ix;
+            y[j] = line + iy;
         }
     } else {
         const uint32_t hx = ix * g.prime[0], hy = iy * g.prime[0];
@@ -301,23 +318,33 @@ __device__ __forceinline__ void pair_rows_xy(const DevGrid& g, int l, const Cell
         const uint32_t hz0 = (uint32_t)c.iz * g.prime[2], hz1 = hz0 + g.prime[2];
         const uint32_t ht0 = (uint32_t)c.it * g.prime[3], ht1 = ht0 + g.prime[3];
 #pragma unroll
-        for (int p = 0; p < 8; ++p) {
+        for (int j = 0; j < N; ++j) {
+            const int p = p0 + j;
             const uint32_t h = ((p & 1) ? hy1 : hy0) ^ ((p & 2) ? hz1 : hz0) ^ ((p & 4) ? ht1 : ht0);
             if (g.tmask) {
-                x[p] = off + ((hx ^ h) & g.tmask);
-                y[p] = off + ((hy ^ h) & g.tmask);
+                x[j] = off + ((hx ^ h) & g.tmask);
+                y[j] = off + ((hy ^ h) & g.tmask);
             } else {
-                x[p] = off + (hx ^ h) % g.T;
-                y[p] = off + (hy ^ h) % g.T;
+                x[j] = off + (hx ^ h) % g.T;
+                y[j] = off + (hy ^ h) % g.T;
             }
         }
     }
 }
 
 // each(p, lo, hi) with the rows of the lower and upper corner of every x-pair p = 0 .. 7 of
-// a cell, in order (corner k of level_rows: pair k / 2).  The pairs are gathered in groups
-// that keep the rows in flight within the registers.  FP32 and BF16 tables: called by both
-// lanes of every even/odd pair.
+// a cell, in order (corner k of level_rows: pair k / 2).  FP32 and BF16 tables: called by
+// both lanes of every even/odd pair.
+//
+// Up to four features all 8 pairs are gathered at once: their latencies overlap, and groups
+// of 4 cost up to 2 % (input gradient of 16 levels, 200k queries: 171 -> 175 us).  Eight
+// features would then take 256 registers, one wavefront per SIMD (an unrolled loop of groups
+// too: the compiler gathers them all first), so their groups are smaller and the loop stays
+// rolled.  200k queries, 8 levels of 2^18 rows, all at once -> in groups: smoothness pass
+// FP32 408 -> 346 us, BF16 219 -> 150, input gradient FP32 223 -> 200, encode 192 -> 187.
+template <typename TT, int F>
+constexpr int kPairGroup = F < 8 ? 8 : sizeof(TT) == 4 ? 2 : 4;
+
 template <typename TT, int F, bool WIDE, typename Each>
 __device__ __forceinline__ void each_pair(const DevGrid& g, int l, const TT* __restrict__ table, const Cell& c, Each each) {
     using A = typename AccOf<TT>::type;
@@ -330,19 +357,13 @@ __device__ __forceinline__ void each_pair(const DevGrid& g, int l, const TT* __r
 #pragma unroll
         for (int p = 0; p < 8; ++p) each(p, v[2 * p], v[2 * p + 1]);
     } else {
-        constexpr int kGroup = F <= 2 ? 8 : F == 4 ? 4 : 2;
-        uint32_t x[8], y[8];
-        pair_rows_xy(g, l, c, x, y);
-#pragma unroll
+        constexpr int kGroup = kPairGroup<TT, F>;
+#pragma unroll 1
         for (int p0 = 0; p0 < 8; p0 += kGroup) {
-            uint32_t gx[kGroup], gy[kGroup];
-#pragma unroll
-            for (int j = 0; j < kGroup; ++j) {
-                gx[j] = x[p0 + j];
-                gy[j] = y[p0 + j];
-            }
+            uint32_t x[kGroup], y[kGroup];
+            pair_rows_xy<kGroup>(g, l, c, p0, x, y);
             A v[2 * kGroup][F];
-            gather_pairs<TT, F, WIDE, kGroup>(table, g.rows, gx, gy, v);
+            gather_pairs<TT, F, WIDE, kGroup>(table, g.rows, x, y, v);
 #pragma unroll
             for (int j = 0; j < kGroup; ++j) each(p0 + j, v[2 * j], v[2 * j + 1]);
         }
@@ -353,15 +374,16 @@ __device__ __forceinline__ void each_pair(const DevGrid& g, int l, const TT* __r
 template <typename TT, int F, bool WIDE, typename A>
 __device__ __forceinline__ void interpolate(const DevGrid& g, int l, const TT* __restrict__ table, const Cell& c,
                                             A (&acc)[F]) {
-    A w[16];
-    level_weights<A>(c, w);
+    const AxisWeights<A> w(c);
 #pragma unroll
     for (int f = 0; f < F; ++f) acc[f] = A(0);
     each_pair<TT, F, WIDE>(g, l, table, c, [&](int p, const A (&lo)[F], const A (&hi)[F]) {
+        A wl, wh;
+        w.pair(p, wl, wh);
 #pragma unroll
-        for (int f = 0; f < F; ++f) acc[f] += w[2 * p] * lo[f];
+        for (int f = 0; f < F; ++f) acc[f] += wl * lo[f];
 #pragma unroll
-        for (int f = 0; f < F; ++f) acc[f] += w[2 * p + 1] * hi[f];
+        for (int f = 0; f < F; ++f) acc[f] += wh * hi[f];
     });
 }
 

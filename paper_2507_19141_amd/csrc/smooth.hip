@@ -35,23 +35,24 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth(DevGrid g, const TT* __
         const Cell c0 = level_cell(g, l, x);
         const Cell c1 = level_cell(g, l, xp);
         const bool same = c0.ix == c1.ix && c0.iy == c1.iy && c0.iz == c1.iz && c0.it == c1.it;
-        A w0[16], w1[16];
-        level_weights<A>(c0, w0);
-        level_weights<A>(c1, w1);
+        const AxisWeights<A> w0(c0), w1(c1);
         A d[F], a0[F];
 #pragma unroll
         for (int f = 0; f < F; ++f) d[f] = a0[f] = A(0);
         each_pair<TT, F, WIDE>(g, l, table, c0, [&](int p, const A (&lo)[F], const A (&hi)[F]) {
-            const A dl = w0[2 * p] - w1[2 * p], dh = w0[2 * p + 1] - w1[2 * p + 1];
+            A l0, h0, l1, h1;
+            w0.pair(p, l0, h0);
+            w1.pair(p, l1, h1);
+            const A dl = l0 - l1, dh = h0 - h1;
 #pragma unroll
             for (int f = 0; f < F; ++f) {
                 d[f] += dl * lo[f];
-                a0[f] += w0[2 * p] * lo[f];
+                a0[f] += l0 * lo[f];
             }
 #pragma unroll
             for (int f = 0; f < F; ++f) {
                 d[f] += dh * hi[f];
-                a0[f] += w0[2 * p + 1] * hi[f];
+                a0[f] += h0 * hi[f];
             }
         });
         // the second cell's corners, where it differs in either lane of the pair
