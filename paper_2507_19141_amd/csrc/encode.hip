@@ -458,10 +458,9 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
         tm.list_head[l] = head;
         if ((tm.lists >> l) & 1u) {
             const int log = pre_chunk_log(tm, l, pair), per_seg = pre_chunks(n, log);
-            if (n > 0)  // whole regions, then the last segment's last chunk
-                entry += (int64_t)kListEntries * ((int64_t)segs * per_seg - 1) +
-                         (int64_t)(kListEntries >> log) * (n - ((int64_t)(per_seg - 1) << log));
-            head += (int64_t)segs * per_seg * tiles[l];
+            const int64_t chunks = (int64_t)segs * per_seg;
+            entry += chunks == 1 ? (int64_t)(kListEntries >> log) * n : chunks * kListEntries;
+            head += chunks * tiles[l];
         } else if ((tm.masks >> l) & 1u) {
             while (((tiles[l] - 1) >> tm.bit_shift[l]) >= 32) ++tm.bit_shift[l];
         }
