@@ -7,8 +7,8 @@
 // reads exactly its own pairs, one per lane, in query order, so that neighbouring lanes'
 // loads of positions and gradients share cache lines.
 //
-// A chunk's entries fill at most one region of kListEntries (the last chunk's is as short as
-// its queries allow); chunk c of list level l starts at entry list_entry[l] + c
+// A chunk's entries fill at most one region of kListEntries (a level's only chunk's is as short
+// as its queries allow); chunk c of list level l starts at entry list_entry[l] + c
 // kListEntries, and heads[list_head[l] + tile * chunks + c] holds the first
 // entry and the count of the tile's run in it.
 //
@@ -476,14 +476,18 @@ constexpr int kWalkChunks = 1024;
 constexpr int kWalkLds = 2 * kWalkChunks + 16;
 
 // A wavefront holds the descriptions of batches base .. base + 63 of its range, which ends
-// before batch b1.  It reads on for up to three batches past the end (the last batch again)
-// and describes no batch there, so that the lane it reads from stays one of its 64.
-__host__ __device__ constexpr bool walk_describes(int next, int base, int b1) { return next < b1 && next - base >= 64; }
-__host__ __device__ constexpr int walk_lane(int next, int base, int b1) { return (next < b1 ? next : b1 - 1) - base; }
+// before batch b1.  It reads on past the end; base may then lie there too, and every lane
+// describes the last batch.
+__host__ __device__ constexpr int walk_lane(int next, int base, int b1) {
+    const int i = (next < b1 ? next : b1 - 1) - base;
+    return i > 0 ? i : 0;
+}
 constexpr bool walk_lanes_exist(int b1) {
     for (int next = 0, base = 0; next < b1 + 6; ++next) {
-        if (walk_describes(next, base, b1)) base = next;
-        if (walk_lane(next, base, b1) < 0 || walk_lane(next, base, b1) > 63) return false;
+        if (next - base >= 64) base = next;
+        const int batch = base + walk_lane(next, base, b1), want = next < b1 ? next : b1 - 1;
+        if (walk_lane(next, base, b1) < 0 || walk_lane(next, base, b1) > 63 || (batch < b1 ? batch : b1 - 1) != want)
+            return false;
     }
     return true;
 }
@@ -550,7 +554,7 @@ __device__ __forceinline__ void walk_pair_lists(int nchunks, int chunk_log, cons
         };
         int next = b0;
         auto fetch = [&](Batch& b) {  // the next batch of the range, none past its end
-            if (walk_describes(next, dbase, b1)) describe(next);
+            if (next - dbase >= 64) describe(next);
             const int i = walk_lane(next, dbase, b1);
             b.cn = (uint32_t)__builtin_amdgcn_readlane((int)dcn, i);
             const uint32_t off = (uint32_t)__builtin_amdgcn_readlane((int)doff, i);
