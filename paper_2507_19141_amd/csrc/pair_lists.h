@@ -570,6 +570,21 @@ __device__ __forceinline__ void walk_pair_lists(int nchunks, int chunk_log, cons
         };
         auto data = [&](const Batch& b) { return Item{load(cb, (b.cn >> 8) << chunk_log, b.e), b.cn & 0xffu}; };
         describe(b0);
+        if constexpr (sizeof(Data) > 128) {
+            // two corner sets of eight FP64 features: three batches in flight spill 338
+            // registers (50k queries of 8 levels: 718 us, one at a time 590)
+            Batch q[2];
+            fetch(q[0]);
+            for (int b = b0; b < b1; b += 2) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const Item d = data(q[j]);
+                    fetch(q[1 - j]);
+                    if ((uint32_t)lane < d.n) run(d.d);
+                }
+            }
+            continue;
+        }
         Batch q[3];
         Item d[3];
         fetch(q[0]);
