@@ -36,11 +36,6 @@ __device__ __forceinline__ float clamp_unit(float x) {
     return __builtin_amdgcn_fmed3f(__builtin_canonicalizef(x), 0.0f, 1.0f);
 }
 
-// Rank of this lane among the lanes set in a ballot below it (lanes 0 .. lane - 1).
-__device__ __forceinline__ int lane_rank(uint64_t bal) {
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-}
-
 // Lower vertex and fractional offset along one dimension: pos = x * N rounded once
 // in FP32, i = min(floor(pos), N - 1), frac = pos - i, which is exact in FP32.
 // Contraction is off in this block: the compiler would otherwise fuse the product
@@ -209,7 +204,11 @@ __device__ __forceinline__ uint32_t lane_swap(uint32_t v) {
 // One table row as raw 32-bit words.  Wide: rows of 4 bytes are read as the aligned 8-byte
 // row pair they lie in (a 4-byte gather costs a clock per lane whatever lines it touches,
 // an 8-byte one a clock per line), so the table has to be aligned to 8 bytes and have at
-// least two rows; the last row of an odd table is read together with the one before it.
+// least two rows; the last row of an odd table is read together with the one before it,
+// from an address that is aligned to 4 bytes only.
+struct __attribute__((packed, aligned(4))) RowPair {
+    uint32_t x, y;
+};
 template <typename TT, int F>
 struct RawRow {
     static constexpr int kBytes = (int)sizeof(TT) * F;
@@ -222,7 +221,7 @@ struct RawRow {
         const char* base = reinterpret_cast<const char*>(t);
         if constexpr (WIDE && kCanWiden) {
             const uint32_t a = min(row & ~1u, rows - 2u);
-            const uint2 v = *reinterpret_cast<const uint2*>(base + (size_t)a * 4u);
+            const RowPair v = *reinterpret_cast<const RowPair*>(base + (size_t)a * 4u);
             w[0] = row != a ? v.y : v.x;
         } else if constexpr (kBytes == 2) {
             w[0] = *reinterpret_cast<const uint16_t*>(base + (size_t)row * 2u);
@@ -459,7 +458,7 @@ __device__ __forceinline__ void lds_add2_two(float* p, float a0, float a1, float
     if (rv != sv) lds_add2_retry(q, b0, b1, rv);
 }
 
-// Add F values (times w) to one tile row.
+// Add F values to one tile row; lds_add_row: times w.
 template <typename G, int F>
 __device__ __forceinline__ void lds_add_values(G* p, const G (&v)[F]) {
     if constexpr (sizeof(G) == 4 && F % 2 == 0) {
