@@ -200,10 +200,10 @@ __global__ __launch_bounds__(kBatchScatterBlock) void k_bscatter(const BSeg* __r
         const float* __restrict__ d_feat = segs[sc.seg0].d_feat + (int64_t)l * sc.n * F;
         const int64_t seg_stride = (int64_t)g.L * sc.n * F;
         float* mine = tile + (threadIdx.x & (tr.copies - 1u)) * tr.stride;
-        auto go = [&](auto loose) {
-            constexpr bool kLoose = decltype(loose)::value;
+        auto go = [&](auto own) {
+            constexpr bool kOwn = decltype(own)::value;
             walk_pair_lists<kBatchScatterBlock>(
-                nchunks, log, sc.heads + tm.list_head[l] + (int64_t)tl.tile * nchunks,
+                nchunks, log, sc.heads + tm.list_head[l] + (int64_t)(tl.tile >> tm.share_shift[l]) * nchunks,
                 sc.lists + tm.list_entry[l], walk,
                 [&](int round, uint32_t cq, uint32_t e) {
                     const uint32_t c = (uint32_t)round + (cq >> log);
@@ -232,11 +232,11 @@ __global__ __launch_bounds__(kBatchScatterBlock) void k_bscatter(const BSeg* __r
                         hi[f] = w.w1 * b.gv[f];
                     }
                     uint32_t r0, r1;
-                    pair_rows<kLoose>(lv, c, m, r0, r1);
-                    add_pair<float, F, kLoose>(mine, tr.cnt, r0, lo, r1, hi);
+                    pair_rows<kOwn>(lv, c, m, r0, r1);
+                    add_pair<float, F, kOwn>(mine, tr.cnt, r0, lo, r1, hi);
                 });
         };
-        if (lv.loose) go(std::true_type{});
+        if (lv.own) go(std::true_type{});
         else go(std::false_type{});
     }
     __syncthreads();

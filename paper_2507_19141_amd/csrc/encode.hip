@@ -52,13 +52,19 @@ __global__ __launch_bounds__(kEncodeBlock) void k_encode(DevGrid g, const TT* __
 // workgroup owns those rows).
 //
 // A pre-pass tells each tile which queries reach it: pair lists (pair_lists.h), or, on
-// levels of more than kListTiles tiles (and where the workspace does not hold one level's
+// hashed levels of more than kListTiles tiles (and where the workspace does not hold one level's
 // lists), a 32-bit mask per (query, level) of the tiles the query's corners touch (tile t sets bit t >>
 // bit_shift); a tile workgroup reads the masks of its level, compacts the queries whose
 // bit is set into per-wavefront LDS queues and runs the corner work on full wavefronts of
 // those queries only.
 // PAIR: each query also subtracts the same gradient at the corners of x + eps (the
 // second term of Eq. 11).
+//
+// Dense levels of more than kListTiles tiles share lists among neighbouring tiles rather
+// than scan masks: where queries crowd (one timestamp), a mask form's tiles of consecutive
+// rows get most of a level's updates.  200k queries at one timestamp, one level: 1.1M rows
+// of 4 features 698 -> 127 us, 2M of 8 1076 -> 213, 32M of 2 (2048 tiles) 1505 -> 187; at
+// random times 195 -> 87, 258 -> 115, 500 -> 203.
 //
 // The lists are why a tile's time follows its own updates: with the masks alone every tile
 // streams its level's mask array and gathers whole queries for one pair each.  200k queries
@@ -179,10 +185,10 @@ __device__ __forceinline__ void scatter_lists(const DevGrid& g, const TileMap& t
                                               const MainGrad<G>& mg, int* lds, G* tile) {
     const int log = pre_chunk_log(tm, l, PAIR), nchunks = pre_chunks(n, log);
     const ListLevel lv = list_level(g, tm, l, tr);
-    auto walk = [&](auto loose) {
-        constexpr bool kLoose = decltype(loose)::value;
+    auto walk = [&](auto own) {
+        constexpr bool kOwn = decltype(own)::value;
         walk_pair_lists<kScatterBlock>(
-            nchunks, log, heads + tm.list_head[l] + (int64_t)tr.tile * nchunks,
+            nchunks, log, heads + tm.list_head[l] + (int64_t)(tr.tile >> tm.share_shift[l]) * nchunks,
             lists + tm.list_entry[l], lds,
             [&](int round, uint32_t cq, uint32_t e) {
                 ListQuery<G, F, PAIR> q;
@@ -203,7 +209,7 @@ __device__ __forceinline__ void scatter_lists(const DevGrid& g, const TileMap& t
                         a[f] = w.w0 * q.t.gv[f];
                         b[f] = w.w1 * q.t.gv[f];
                     }
-                    pair_rows<kLoose>(lv, c, m, r0, r1);
+                    pair_rows<kOwn>(lv, c, m, r0, r1);
                 } else {
                     // kind 0: x's pair, +(gradients); kind 1: xp's pair, -(smoothness
                     // gradient); kind 2: both at the same rows
@@ -226,12 +232,12 @@ __device__ __forceinline__ void scatter_lists(const DevGrid& g, const TileMap& t
                             b[f] -= wp.w1 * q.t.gv[f];
                         }
                     }
-                    pair_rows<kLoose>(lv, c, m, r0, r1);
+                    pair_rows<kOwn>(lv, c, m, r0, r1);
                 }
-                add_pair<G, F, kLoose>(tile, tr.cnt, r0, a, r1, b);
+                add_pair<G, F, kOwn>(tile, tr.cnt, r0, a, r1, b);
             });
     };
-    if (lv.loose) walk(std::true_type{});
+    if (lv.own) walk(std::true_type{});
     else walk(std::false_type{});
 }
 
@@ -428,7 +434,7 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
             const int64_t S = (int64_t)g.res_s[l] + 1, lines = rows / S;
             int b = 5;
             while (b > 0 && ((int64_t)1 << b) > lines) --b;
-            while ((1 << b) < kListTiles && ((lines + (1 << b) - 1) >> b) * S > tm.max_rows) ++b;
+            while (((int64_t)1 << b) < lines && ((lines + (1 << b) - 1) >> b) * S > tm.max_rows) ++b;
             line_shift[l] = b;
             if (((lines + (1 << b) - 1) >> b) * S <= tm.max_rows) can |= 1u << l;
         } else {
@@ -449,6 +455,7 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
             if ((g.dense_bits >> l) & 1u) {
                 tm.tile_shift[l] = line_shift[l];
                 tiles[l] = 1 << line_shift[l];
+                while ((tiles[l] >> tm.share_shift[l]) > kListTiles) ++tm.share_shift[l];
             } else if (!((tm.pair_cotiled >> l) & 1u)) {
                 tm.loose |= 1u << l;
             }
@@ -460,7 +467,7 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
             const int log = pre_chunk_log(tm, l, pair), per_seg = pre_chunks(n, log);
             const int64_t chunks = (int64_t)segs * per_seg;
             entry += chunks == 1 ? (int64_t)(kListEntries >> log) * n : chunks * kListEntries;
-            head += chunks * tiles[l];
+            head += chunks * (tiles[l] >> tm.share_shift[l]);
         } else if ((tm.masks >> l) & 1u) {
             while (((tiles[l] - 1) >> tm.bit_shift[l]) >= 32) ++tm.bit_shift[l];
         }

@@ -75,12 +75,13 @@ struct TileMap {
     // Bit l set: the level's updates reach its tiles through pair lists (pair_lists.h), or
     // through tile masks; a level with neither bit has no tiles (another launch's levels).
     // loose: its pairs may straddle two tiles.  On a dense list level tile_shift is the
-    // log2 of its tiles.  list_entry / list_head: the level's first entry and first head.
+    // log2 of its tiles, 2^share_shift of which share a list.  list_entry / list_head: the level's first entry and first head.
     uint32_t lists, masks, loose;
+    int32_t share_shift[H4D_MAX_LEVELS];
     int64_t list_entry[H4D_MAX_LEVELS + 1];
     int64_t list_head[H4D_MAX_LEVELS + 1];
 };
-// Pair lists: entries of one region, tiles of a list level at most, and the log2 of the
+// Pair lists: entries of one region, lists of a level at most, and the log2 of the
 // queries of a chunk, whose 8 pairs have up to one entry per corner set (pair: two) and
 // tile (loose: two).
 constexpr int kListEntries = 16384;

@@ -9,8 +9,8 @@
 //
 // A chunk's entries fill at most one region of kListEntries (a level's only chunk's is as short
 // as its queries allow); chunk c of list level l starts at entry list_entry[l] + c
-// kListEntries, and heads[list_head[l] + tile * chunks + c] holds the first
-// entry and the count of the tile's run in it.
+// kListEntries, and heads[list_head[l] + list * chunks + c] holds the first
+// entry and the count of the list's run in it (one list per tile, but see dense).
 //
 // Tiles of a list level (make_tile_map):
 //  - hashed, tight: 2^tile_shift consecutive rows.  pi_1 = 1 and T a power of two keep the
@@ -18,7 +18,9 @@
 //  - dense: the level's x-lines (runs of N_s + 1 rows, same y, z, t) are dealt to
 //    2^tile_shift tiles in turn, line h P + k of P lines going to tile k + 11 h mod P, so
 //    that queries crowded into a few cells (every query at one timestamp, a clustered
-//    cloud) still spread over all tiles.  A pair lies in one line, hence in one tile.
+//    cloud) still spread over all tiles.  A pair lies in one line, hence in one tile.  A
+//    level of more than kListTiles tiles has kListTiles lists, each for 2^share_shift
+//    neighbouring tiles, which walk it and add the rows of their own lines.
 //  - loose (hashed, T no power of two or 2 N_s above the tile's rows): consecutive rows,
 //    but a pair may straddle two tiles.  Such a pair has an entry in both, and the
 //    scatter adds the rows that lie in its own tile.
@@ -32,26 +34,30 @@ constexpr uint32_t kListQMask = 2047;  // bits 0..10: query in its chunk
 constexpr int kListPShift = 11;        // bits 11..13: pair
 constexpr int kListKShift = 14;        // bits 14..15: kind (corner sets, see tile_pre_lists)
 
-// Tile of x-line `line` of a dense list level with 2^b tiles, and its inverse: the line
-// in slot h of tile t.
+// Tile of x-line `line` of a dense list level with 2^b tiles; its inverse: the line in slot
+// h of tile t; and the line's list where 2^share tiles have one (line_tile >> share).
 __device__ __forceinline__ uint32_t line_tile(uint32_t line, int b) { return (line + 11u * (line >> b)) & ((1u << b) - 1u); }
 __device__ __forceinline__ uint32_t tile_line(uint32_t h, uint32_t t, int b) {
     return (h << b) + ((t - 11u * h) & ((1u << b) - 1u));
+}
+__device__ __forceinline__ uint32_t line_list(uint32_t line, int b, int share) {
+    return __builtin_amdgcn_ubfe(line + 11u * (line >> b), (uint32_t)share, (uint32_t)(b - share));
 }
 
 __device__ __forceinline__ uint32_t cell_line(const Cell& c, uint32_t S, uint32_t p) {
     return ((uint32_t)c.iy + (p & 1u)) + S * (((uint32_t)c.iz + ((p >> 1) & 1u)) + S * ((uint32_t)c.it + ((p >> 2) & 1u)));
 }
 
-// Tiles of the 8 pairs (one byte each, pairs 0-3 in t[0]); tight and dense levels.
+// Lists of the 8 pairs (one byte each, pairs 0-3 in t[0]); tight and dense levels.
 __device__ __forceinline__ void pair_tiles(const DevGrid& g, const TileMap& tm, int l, const Cell& c, uint32_t (&t)[2]) {
     uint32_t b[8];
     const int sh = tm.tile_shift[l];
     if ((g.dense_bits >> l) & 1u) {
         const uint32_t S = (uint32_t)g.res_s[l] + 1u;
         const uint32_t line = cell_line(c, S, 0u);
+        const int share = tm.share_shift[l];
 #pragma unroll
-        for (int p = 0; p < 8; ++p) b[p] = line_tile(line + (p & 1) + ((p >> 1) & 1) * S + (p >> 2) * S * S, sh);
+        for (int p = 0; p < 8; ++p) b[p] = line_list(line + (p & 1) + ((p >> 1) & 1) * S + (p >> 2) * S * S, sh, share);
     } else {  // the x term lies below the tile's row bits
         const uint32_t hy0 = (uint32_t)c.iy * g.prime[1], hy1 = hy0 + g.prime[1];
         const uint32_t hz0 = (uint32_t)c.iz * g.prime[2], hz1 = hz0 + g.prime[2];
@@ -82,6 +88,10 @@ __device__ __forceinline__ uint32_t corner_tiles(const DevGrid& g, const TileMap
         apart |= (uint32_t)(a != b) << p;
     }
     return apart;
+}
+
+__device__ __forceinline__ int level_lists(const TileMap& tm, int l) {
+    return (tm.tile_start[l + 1] - tm.tile_start[l]) >> tm.share_shift[l];
 }
 
 // ---- the pre-pass: one workgroup sorts one chunk of one level ----
@@ -132,7 +142,7 @@ __device__ __forceinline__ void tile_pre_lists(const DevGrid& g, const TileMap& 
     static_assert(kPer >= 1 && kChunk * 8 * kSets == kListEntries, "a chunk's entries fill its region");
     constexpr int kWaveEntries = kListEntries / kPreWaves, kEach = kWaveEntries / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int P = tm.tile_start[l + 1] - tm.tile_start[l];
+    const int P = level_lists(tm, l);
     const int q0 = chunk << list_chunk_log(PAIR, LOOSE);
     for (int i = threadIdx.x; i < kPreWaves * P; i += kPreBlock) sh.cnt[i] = 0u;
     float4 xs[kPer], xp[kPer];  // every load in flight before the first use
@@ -343,7 +353,8 @@ struct ListLevel {
     int shift;            // dense: log2 of the tiles
     uint32_t rmask, tmask, T, px;
     uint32_t first, cnt;
-    bool dense, loose;
+    uint32_t tile;        // dense
+    bool dense, own;      // own: only the rows in the tile are added (loose, or a shared list)
 };
 
 __device__ __forceinline__ ListLevel list_level(const DevGrid& g, const TileMap& tm, int l, const TileRows& tr) {
@@ -362,7 +373,8 @@ __device__ __forceinline__ ListLevel list_level(const DevGrid& g, const TileMap&
     c.first = tr.first;
     c.cnt = tr.cnt;
     c.dense = tr.dense;
-    c.loose = (tm.loose >> l) & 1u;
+    c.tile = tr.tile;
+    c.own = ((tm.loose >> l) & 1u) || tm.share_shift[l] > 0;
     return c;
 }
 
@@ -416,13 +428,17 @@ __device__ __forceinline__ PairWeights<G> pair_weights(const FCell& c, const Pai
     return PairWeights<G>{(G(1) - G(c.fx)) * w, G(c.fx) * w};
 }
 
-// Rows of a pair of cell c in the tile.
-template <bool LOOSE>
+// Rows of a pair of cell c in the tile.  OWN: a row outside the tile is at or above cnt.
+template <bool OWN>
 __device__ __forceinline__ void pair_rows(const ListLevel& lv, const FCell& c, const PairMask& m, uint32_t& r0,
                                           uint32_t& r1) {
     const uint32_t ix = (uint32_t)c.ix, iy = (uint32_t)((int)c.iy - m.y), iz = (uint32_t)((int)c.iz - m.z),
                    it = (uint32_t)((int)c.it - m.t);
-    if constexpr (LOOSE) {
+    if (OWN && lv.dense) {
+        const uint32_t line = iy + lv.S * (iz + lv.S * it);
+        r0 = line_tile(line, lv.shift) == lv.tile ? (line >> lv.shift) * lv.S + ix : ~1u;
+        r1 = r0 + 1u;
+    } else if constexpr (OWN) {
         const uint32_t H = (iy * lv.py) ^ (iz * lv.pz) ^ (it * lv.pt), hx = ix * lv.px;
         const uint32_t h0 = hx ^ H, h1 = (hx + lv.px) ^ H;
         r0 = (lv.tmask ? h0 & lv.tmask : h0 % lv.T) - lv.first;
@@ -439,11 +455,10 @@ __device__ __forceinline__ void pair_rows(const ListLevel& lv, const FCell& c, c
     }
 }
 
-// Add a at the lower and b at the upper corner of a pair.  On a loose level a corner
-// outside the tile has its row at or above cnt.
-template <typename G, int F, bool LOOSE>
+// Add a at the lower and b at the upper corner of a pair (OWN: where they lie in the tile).
+template <typename G, int F, bool OWN>
 __device__ __forceinline__ void add_pair(G* tile, uint32_t cnt, uint32_t r0, const G (&a)[F], uint32_t r1, const G (&b)[F]) {
-    if constexpr (LOOSE) {
+    if constexpr (OWN) {
         if (r0 < cnt) lds_add_values<G, F>(tile + r0 * F, a);
         if (r1 < cnt) lds_add_values<G, F>(tile + r1 * F, b);
     } else if constexpr (sizeof(G) == 4 && F == 2) {

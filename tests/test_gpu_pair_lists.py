@@ -423,3 +423,61 @@ def test_batched_plan_whose_lists_do_not_fit():
     info = plan.info()
     assert info.queries == n * len(times) and info.encode_grid * 256 < 1 << 32
     plan.destroy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", [_lib.F32, _lib.F64], ids=["f32", "f64"])
+@pytest.mark.parametrize("form", ["one_set", "two_sets", "batched"])
+@pytest.mark.parametrize("n,crowded", [(1, False), (3000, False), (2500, True)])
+def test_dense_level_of_more_tiles_than_lists(form, dt, n, crowded):
+    # 512 tiles of x-lines in FP32, 1024 in FP64: two or four tiles share a list
+    if form == "batched" and dt == _lib.F64:
+        pytest.skip("batched plans run F32 or BF16")
+    needs_gpu()
+    import torch
+    L, F, rs, rt, T = 1, 8, [63], [4], 1 << 21
+    og, lg = O.make_grid(L, F, rs, rt, T), _lib.h4d_grid_init(L, F, rs, rt, T)
+    assert lg.dense_list() == [True]
+    rng, x = _inputs(n, n + 3, crowded)
+    real = np.float64 if dt == _lib.F64 else np.float32
+    gf = synth.upstream(n, F, rng)
+    d_table = _dev(np.full((og.E, F), np.nan, real))
+    layout = _lib.QUERY_MAJOR | _lib.GRAD_OVERWRITE
+    ref, scale = O.encode_backward(x, gf, og), O.encode_backward(x, np.abs(gf), og)
+    if form == "one_set":
+        wb = _lib.hash4d_encode_backward_workspace_bytes(lg, n)
+        ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
+        _lib.hash4d_encode_backward(lg, dt, _dev(x), n, _dev(gf.astype(real)), 1.0, d_table, ws, wb, layout)
+    elif form == "two_sets":
+        table, eps = synth.table_init(og.E, F, rng), synth.perturbation(n, rng, 1e-2)
+        loss = torch.zeros(1, dtype=torch.float64 if dt == _lib.F64 else torch.float32, device="cuda")
+        wb = _lib.smoothness_workspace_bytes(lg, dt, n)
+        ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
+        _lib.hash4d_encode_backward_smooth(lg, dt, _dev(table.astype(real)), _dev(x), _dev(eps), n,
+                                           _dev(gf.astype(real)), 1.0, 2.0, loss, d_table, ws, wb, layout)
+        xp = O.perturbed(x, eps)
+        s = 4.0 / n * (np.abs(O.encode(x, table, og) - O.encode(xp, table, og)) + O.encode(x, np.abs(table), og)
+                       + O.encode(xp, np.abs(table), og))
+        ref = ref + O.smoothness(x, eps, table, og, 2.0)[1]
+        scale = scale + O.encode_backward(x, s, og) + O.encode_backward(xp, s, og)
+    else:
+        x = np.clip(np.nan_to_num(x), 0, 1).astype(np.float32)
+        times = [0.25, 0.7]
+        table, params = synth.table_init(og.E, F, rng), synth.decoder_params(F, rng)
+        gd = synth.upstream(n * 2, 10, rng).reshape(2, n, 10)
+        bufs = [_dev(x), _dev(table), _dev(params), torch.empty((2, L, n, F), device="cuda"),
+                torch.empty((2, n, 10), device="cuda"), _dev(gd), torch.full((params.size,), float("nan"), device="cuda")]
+        plan = _lib.BatchedPlan([_lib.scene_desc(lg, n, bufs[0], times, bufs[1], bufs[2], bufs[3], bufs[4], bufs[5],
+                                                 d_table, bufs[6])], _lib.mlp_shape(F), _lib.F32, 1.0,
+                                _lib.PLAN_ZERO_GRADS)
+        plan.run()
+        torch.cuda.synchronize()
+        plan.destroy()
+        ref, scale = np.zeros((og.E, F)), np.zeros((og.E, F))
+        for k, t in enumerate(times):
+            xt = x.copy()
+            xt[:, 3] = np.float32(t)
+            ref += O.deform_backward(xt, table, og, params, gd[k])[0]
+            scale += O.encode_backward(xt, mlp_backward_scale(params, O.encode(xt, table, og), gd[k])[0], og)
+    torch.cuda.synchronize()
+    scaled_close(d_table.cpu().numpy(), ref, scale, 1e-12 if dt == _lib.F64 else RTOL_GRAD, f"{form} n={n}")
