@@ -164,12 +164,13 @@ static h4d_status check_mlp(const h4d_mlp* m, h4d_dtype dt) {
     return check_dtype(dt);
 }
 
-// Workspace of the tiled scatter for grid g and n queries (least: the least it takes).
-static size_t scatter_ws(const h4d_grid* g, int64_t n, bool pair = false, bool least = false) {
+// Workspace of the tiled scatter for grid g and n queries and `more` bytes beside it (least:
+// the least that a call takes).
+static size_t scatter_ws(const h4d_grid* g, int64_t n, bool pair = false, bool least = false, size_t more = 0) {
     int64_t rows[H4D_MAX_LEVELS];
     rows_of(*g, rows);
-    return least ? scatter_ws_least(to_device(*g), rows, (int)n, pair)
-                 : scatter_ws_bytes(to_device(*g), rows, (int)n, pair);
+    return least ? scatter_ws_least(to_device(*g), rows, (int)n, pair, more)
+                 : scatter_ws_bytes(to_device(*g), rows, (int)n, pair) + more;
 }
 
 // Deformation backward workspace: [decoder partials | d_feat [L, n, F] | pair lists].
@@ -470,12 +471,16 @@ h4d_status hash4d_corner_indices(const h4d_grid* g, const float* xyzt, int64_t n
     return hip_status(launch_corner_indices(d, xyzt, (int)n, rows, w, (hipStream_t)stream), "hash4d_corner_indices");
 }
 
-// Smoothness workspace: [d = G(x) - G(x + eps), level-major | pair lists].
+// Smoothness workspace: [d = G(x) - G(x + eps), level-major | partial sums of the loss |
+// pair lists].
 static size_t smooth_d_bytes(const h4d_grid* g, h4d_dtype table_dt, int64_t n) {
     return ((size_t)n * g->L * g->F * (table_dt == H4D_F64 ? sizeof(double) : sizeof(float)) + 255) / 256 * 256;
 }
+static size_t smooth_sum_bytes(const h4d_grid* g, int64_t n) {
+    return (smoothness_sum_bytes(g->L, (int)n) + 255) / 256 * 256;
+}
 static size_t smooth_ws(const h4d_grid* g, h4d_dtype table_dt, int64_t n, bool least = false) {
-    return smooth_d_bytes(g, table_dt, n) + scatter_ws(g, n, true, least);
+    return smooth_d_bytes(g, table_dt, n) + scatter_ws(g, n, true, least, smooth_sum_bytes(g, n));
 }
 
 size_t smoothness_workspace_bytes(const h4d_grid* g, h4d_dtype table_dt, int64_t n) {
@@ -502,20 +507,23 @@ h4d_status smoothness_reg(const h4d_grid* g, h4d_dtype table_dt, const void* tab
     const DevGrid d = to_device(*g);
     const hipStream_t s = (hipStream_t)stream;
     const size_t dbytes = smooth_d_bytes(g, table_dt, n);
-    // pass 1: loss and the feature difference d = G(x) - G(x + eps), level-major [L, n, F];
-    // the loss's partial sums lie where pass 2 puts its pair lists
+    const size_t lists = dbytes + smooth_sum_bytes(g, n);
+    FixedSum rest;
+    // pass 1: partial sums of the loss and the feature difference d = G(x) - G(x + eps),
+    // level-major [L, n, F]
     if ((st = hip_status(launch_smoothness(d, table_dt, table, xyzt, eps, (int)n, (double)lambda, loss,
                                            d_table ? workspace : nullptr,
-                                           d_table ? static_cast<char*>(workspace) + dbytes : nullptr, s),
+                                           d_table ? static_cast<char*>(workspace) + dbytes : nullptr, &rest, s),
                          "smoothness_reg/diff")))
         return st;
     if (!d_table) return H4D_OK;
-    // pass 2: d_table += (2 lambda / n) (d at x's corners - d at x~'s corners)
+    // pass 2: the loss; d_table += (2 lambda / n) (d at x's corners - d at x~'s corners)
     int64_t rows[H4D_MAX_LEVELS];
     rows_of(*g, rows);
     return hip_status(launch_scatter_tiled(d, rows, table_dt == H4D_F64 ? H4D_F64 : H4D_F32, xyzt, eps, (int)n,
                                            workspace, n * g->F, g->F, 2.0 * (double)lambda / (double)n, d_table,
-                                           static_cast<char*>(workspace) + dbytes, ws_bytes - dbytes, s),
+                                           static_cast<char*>(workspace) + lists, ws_bytes - lists, s, false,
+                                           MainGradArg{}, nullptr, rest),
                       "smoothness_reg/scatter");
 }
 
@@ -547,9 +555,11 @@ h4d_status hash4d_encode_backward_smooth(const h4d_grid* g, h4d_dtype table_dt, 
     if (((uintptr_t)workspace) & 15u) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");
     const DevGrid d = to_device(*g);
     const size_t dbytes = smooth_d_bytes(g, table_dt, n);
-    // pass 1: loss and d = G(x) - G(x + eps), level-major [L, n, F], as in smoothness_reg
+    const size_t lists = dbytes + smooth_sum_bytes(g, n);
+    FixedSum rest;
+    // pass 1: partial sums of the loss and d = G(x) - G(x + eps), level-major [L, n, F]
     if ((st = hip_status(launch_smoothness(d, table_dt, table, xyzt, eps, (int)n, (double)lambda, loss, workspace,
-                                           static_cast<char*>(workspace) + dbytes, s),
+                                           static_cast<char*>(workspace) + dbytes, &rest, s),
                          "hash4d_encode_backward_smooth/diff")))
         return st;
     // pass 2: one scatter over both corner sets: x's corners get (2 lambda / n) d +
@@ -563,8 +573,8 @@ h4d_status hash4d_encode_backward_smooth(const h4d_grid* g, h4d_dtype table_dt, 
     main.scale = (double)grad_scale;
     return hip_status(launch_scatter_tiled(d, rows, table_dt == H4D_F64 ? H4D_F64 : H4D_F32, xyzt, eps, (int)n,
                                            workspace, n * g->F, g->F, 2.0 * (double)lambda / (double)n, d_table,
-                                           static_cast<char*>(workspace) + dbytes, ws_bytes - dbytes, s, overwrite,
-                                           main),
+                                           static_cast<char*>(workspace) + lists, ws_bytes - lists, s, overwrite, main,
+                                           nullptr, rest),
                       "hash4d_encode_backward_smooth/scatter");
 }
 

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kEncodeBlock) void k_encode(DevGrid g, const TT* __
 //
 // Dense levels of more than kListTiles tiles share lists among neighbouring tiles rather
 // than scan masks: where queries crowd (one timestamp), a mask form's tiles of consecutive
-// rows get most of a level's updates.  200k queries at one timestamp, one level: 1.1M rows
+// rows get most of a level's updates.  200k queries at one timestamp, one level: 4.1M rows
 // of 4 features 698 -> 127 us, 2M of 8 1076 -> 213, 32M of 2 (2048 tiles) 1505 -> 187; at
 // random times 195 -> 87, 258 -> 115, 500 -> 203.
 //
@@ -75,14 +75,45 @@ __global__ __launch_bounds__(kEncodeBlock) void k_encode(DevGrid g, const TT* __
 // 56 %, none of them alone.  Doubles in the tile with the hardware's FP64 adds, which need
 // no retry, were no faster (the tile then holds half the rows: 431 -> 511 us for a step).
 
-// The pre-pass.  Grid (chunks of the level with the most, L); levels without tiles belong
+// The pre-pass.  Grid (chunks of the level with the most, L, or L + 1 with a sum); levels without tiles belong
 // to another pass (scatter_plan).
+//
+// With PAIR a workgroup past the last level adds up the smoothness loss's partial sums: one
+// FP32 atomic per workgroup of 256 queries in order of arrival (12.5k of them for 200k
+// queries of 16 levels) left the step's outputs 7.3e-7 from the 64-bit ones, this order
+// 2.2e-7.  A launch of its own made calls of 1000 queries 2 us longer (33 us).
+template <typename A>
+__device__ __forceinline__ void add_fixed_sum(const FixedSum& f) {
+    constexpr int kBlock = pre_block(true);
+    __shared__ double part[kBlock / 64];
+    const A* __restrict__ sums = static_cast<const A*>(f.sums);
+    double t = 0.0;
+#pragma unroll 8
+    for (int i = threadIdx.x; i < f.count; i += kBlock) t += (double)sums[i];
+    for (int s = 32; s > 0; s >>= 1) t += __shfl_xor(t, s, 64);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        t = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) t += part[w];
+        atomic_add(static_cast<A*>(f.out), (A)(f.scale * t));  // calls on other streams may add to it too
+    }
+}
+
 template <bool PAIR>
 __global__ __launch_bounds__(pre_block(PAIR)) __attribute__((amdgpu_waves_per_eu(pre_waves_per_eu(PAIR)))) void k_tile_pre(DevGrid g, TileMap tm, const float4* __restrict__ xyzt,
                                                         const float4* __restrict__ eps, int n,
                                                         uint32_t* __restrict__ mask, uint16_t* __restrict__ lists,
-                                                        uint32_t* __restrict__ heads) {
+                                                        uint32_t* __restrict__ heads, FixedSum sum) {
     __shared__ __align__(16) PreShared<PAIR> sh;
+    if constexpr (PAIR) {
+        if ((int)blockIdx.y == g.L) {
+            if (blockIdx.x > 0) return;
+            if (sum.f64) add_fixed_sum<double>(sum);
+            else add_fixed_sum<float>(sum);
+            return;
+        }
+    }
     const int l = blockIdx.y, nchunks = pre_chunks(n, pre_chunk_log(tm, l, PAIR));
     if ((int)blockIdx.x >= nchunks || !(((tm.lists | tm.masks) >> l) & 1u)) return;
     tile_pre<PAIR>(g, tm, l, (int)blockIdx.x, 0, nchunks, n,
@@ -580,8 +611,8 @@ size_t scatter_ws_bytes(const DevGrid& g, const int64_t* level_rows, int n, bool
                : bytes;
 }
 
-size_t scatter_ws_least(const DevGrid& g, const int64_t* level_rows, int n, bool pair) {
-    return std::min(scatter_ws_bytes(g, level_rows, n, pair), former_ws_bytes(g, level_rows, n));
+size_t scatter_ws_least(const DevGrid& g, const int64_t* level_rows, int n, bool pair, size_t more) {
+    return std::min(scatter_ws_bytes(g, level_rows, n, pair) + more, former_ws_bytes(g, level_rows, n));
 }
 
 struct ScatterBufs {
@@ -625,7 +656,7 @@ template <typename G, bool PAIR>
 static hipError_t tiled_g(const DevGrid& g, const int64_t* level_rows, const float* xyzt, const float* eps, int n,
                           const void* src, int64_t ls, int64_t qs, double scale, void* d_table, void* ws,
                           size_t ws_bytes, bool overwrite, const MainGradArg& main, int32_t* nonfinite,
-                          hipStream_t s) {
+                          const FixedSum& sum, hipStream_t s) {
     const ScatterPlan plan = scatter_plan(g, level_rows, n, (int)sizeof(G), PAIR, ws_bytes);
     for (int i = 0; i < plan.passes; ++i) {
         const uint32_t levels = plan.levels[i];
@@ -638,9 +669,10 @@ static hipError_t tiled_g(const DevGrid& g, const int64_t* level_rows, const flo
         int chunks = 0;
         for (int l = 0; l < g.L; ++l)
             if ((levels >> l) & 1u) chunks = std::max(chunks, pre_chunks(n, pre_chunk_log(tm, l, PAIR)));
-        hipLaunchKernelGGL(k_tile_pre<PAIR>, dim3((unsigned)chunks, (unsigned)g.L), dim3(pre_block(PAIR)), 0, s, g, tm,
+        hipLaunchKernelGGL(k_tile_pre<PAIR>, dim3((unsigned)chunks, (unsigned)(g.L + (PAIR && sum.count > 0 && i == 0 ? 1 : 0))),
+                           dim3(pre_block(PAIR)), 0, s, g, tm,
                            reinterpret_cast<const float4*>(xyzt), reinterpret_cast<const float4*>(eps), n, b.mask,
-                           b.lists, b.heads);
+                           b.lists, b.heads, sum);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
 #define H4D_SCATTER(FF) tiled_f<G, FF, PAIR>(g, tm, xyzt, eps, n, b, src, ls, qs, scale, d_table, overwrite, main, nonfinite, s)
@@ -660,10 +692,11 @@ static hipError_t tiled_g(const DevGrid& g, const int64_t* level_rows, const flo
 hipError_t launch_scatter_tiled(const DevGrid& g, const int64_t* level_rows, h4d_dtype grad_dt, const float* xyzt,
                                 const float* eps, int n, const void* src, int64_t ls, int64_t qs, double scale,
                                 void* d_table, void* ws, size_t ws_bytes, hipStream_t s, bool overwrite,
-                                const MainGradArg& main, int32_t* nonfinite) {
-    if (main.src && !eps) return hipErrorInvalidValue;  // the second gradient rides on the pair form only
+                                const MainGradArg& main, int32_t* nonfinite, const FixedSum& sum) {
+    if ((main.src || sum.count) && !eps) return hipErrorInvalidValue;  // these ride on the pair form only
 #define H4D_SCATTER(GG, PP) \
-    tiled_g<GG, PP>(g, level_rows, xyzt, eps, n, src, ls, qs, scale, d_table, ws, ws_bytes, overwrite, main, nonfinite, s)
+    tiled_g<GG, PP>(g, level_rows, xyzt, eps, n, src, ls, qs, scale, d_table, ws, ws_bytes, overwrite, main, nonfinite, \
+                    sum, s)
     if (grad_dt == H4D_F64) return eps ? H4D_SCATTER(double, true) : H4D_SCATTER(double, false);
     return eps ? H4D_SCATTER(float, true) : H4D_SCATTER(float, false);
 #undef H4D_SCATTER

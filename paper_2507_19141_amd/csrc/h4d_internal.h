@@ -98,9 +98,9 @@ TileMap make_tile_map(const DevGrid& g, const int64_t* level_rows, int F, int gb
 // on a 16-byte boundary (the scan reads four masks per load).
 constexpr int64_t mask_stride(int64_t n) { return (n + 3) & ~(int64_t)3; }
 // Workspace that the size query reports for n queries; pair: of the form with eps (two
-// corner sets per query); and the least that a call takes.
+// corner sets per query); and the least that a call takes which needs `more` beside it.
 size_t scatter_ws_bytes(const DevGrid& g, const int64_t* level_rows, int n, bool pair);
-size_t scatter_ws_least(const DevGrid& g, const int64_t* level_rows, int n, bool pair);
+size_t scatter_ws_least(const DevGrid& g, const int64_t* level_rows, int n, bool pair, size_t more);
 // A second feature gradient for the pair form (eps set): added, times scale, at x's
 // corners only.  src == nullptr: none.
 struct MainGradArg {
@@ -108,11 +108,20 @@ struct MainGradArg {
     int64_t lstride = 0, qstride = 0;
     double scale = 0.0;
 };
+// A sum that the pre-pass adds up beside its own work, in a workgroup of its own: *out +=
+// scale * (sums[0] + .. ) in a fixed order and in 64 bits.  count == 0: none.
+struct FixedSum {
+    const void* sums = nullptr;  // FP32, FP64 if f64
+    void* out = nullptr;
+    double scale = 0.0;
+    int count = 0;
+    bool f64 = false;
+};
 hipError_t launch_scatter_tiled(const DevGrid& g, const int64_t* level_rows, h4d_dtype grad_dt, const float* xyzt,
                                 const float* eps, int n, const void* src, int64_t lstride, int64_t qstride,
                                 double scale, void* d_table, void* ws, size_t ws_bytes, hipStream_t s,
                                 bool overwrite = false, const MainGradArg& main = MainGradArg{},
-                                int32_t* nonfinite = nullptr);
+                                int32_t* nonfinite = nullptr, const FixedSum& sum = FixedSum{});
 // The static workspace of hash4d_encode_backward_noalloc: kStaticScratchBytes of
 // device memory per GPU (a file-scope array), its address on the current device.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
@@ -213,10 +222,11 @@ hipError_t launch_deform_apply(const float* delta, int n, int out, const float* 
 
 // ---- smoothness regulariser (smooth.hip) ----
 // Loss (+=) and, if d_out != NULL, the level-major difference G(x) - G(x + eps).  sums:
-// NULL, or at least 8 bytes per level and (started) 256 queries, used until the loss is
-// added; with it the loss is summed in a fixed order and in 64 bits.
+// NULL, or smoothness_sum_bytes that receive the loss's partial sums; *rest is then the sum
+// that remains to be added to the loss.
+size_t smoothness_sum_bytes(int L, int n);
 hipError_t launch_smoothness(const DevGrid& g, h4d_dtype dt, const void* table, const float* xyzt, const float* eps,
-                             int n, double lam, void* loss, void* d_out, void* sums, hipStream_t s);
+                             int n, double lam, void* loss, void* d_out, void* sums, FixedSum* rest, hipStream_t s);
 
 // ---- roofline probes (probe.hip) ----
 hipError_t launch_probe_gather(const void* table, uint32_t rows, int row_bytes, int64_t n_loads, uint32_t seed,

@@ -88,31 +88,9 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth(DevGrid g, const TT* __
     }
 }
 
-// *loss += lam_over_n times the workgroups' sums, added in a fixed order and in 64 bits.
-// One FP32 atomic per workgroup in order of arrival (12.5k of them for 200k queries of 16
-// levels) left the step's outputs 7.3e-7 from the 64-bit ones, this order 2.2e-7; the step
-// takes 834 us either way.
-constexpr int kLossBlock = 1024;
-template <typename A>
-__global__ __launch_bounds__(kLossBlock) void k_smooth_loss(const A* __restrict__ sums, int count, double lam_over_n,
-                                                            A* __restrict__ loss) {
-    __shared__ double part[kLossBlock / 64];
-    double t = 0.0;
-#pragma unroll 8
-    for (int i = threadIdx.x; i < count; i += kLossBlock) t += (double)sums[i];
-    for (int s = 32; s > 0; s >>= 1) t += __shfl_xor(t, s, 64);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = t;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        t = 0.0;
-        for (int w = 0; w < kLossBlock / 64; ++w) t += part[w];
-        atomic_add(loss, (A)(lam_over_n * t));  // calls on other streams may add to the same loss
-    }
-}
-
 template <typename TT>
 static hipError_t smooth_t(const DevGrid& g, const void* table, const float* xyzt, const float* eps, int n, double lam,
-                           void* loss, void* d_out, void* sums, hipStream_t s) {
+                           void* loss, void* d_out, void* sums, FixedSum* rest, hipStream_t s) {
     using A = typename AccOf<TT>::type;
     const int chunks = (n + kSmoothBlock - 1) / kSmoothBlock;
     const dim3 grid((unsigned)(kXcds * xcd_items_per(g.L * chunks))), block(kSmoothBlock);
@@ -138,18 +116,26 @@ static hipError_t smooth_t(const DevGrid& g, const void* table, const float* xyz
         default: return hipErrorInvalidValue;
     }
 #undef H4D_SMOOTH
-    const hipError_t err = hipGetLastError();
-    if (err != hipSuccess || !sums) return err;
-    hipLaunchKernelGGL((k_smooth_loss<A>), dim3(1), dim3(kLossBlock), 0, s, su, g.L * chunks, lam / (double)n, lo);
+    if (sums) {
+        rest->sums = sums;
+        rest->out = loss;
+        rest->scale = lam / (double)n;
+        rest->count = g.L * chunks;
+        rest->f64 = sizeof(A) == 8;
+    }
     return hipGetLastError();
 }
 
+size_t smoothness_sum_bytes(int L, int n) {
+    return (size_t)L * (((size_t)n + kSmoothBlock - 1) / kSmoothBlock) * sizeof(double);
+}
+
 hipError_t launch_smoothness(const DevGrid& g, h4d_dtype dt, const void* table, const float* xyzt, const float* eps,
-                             int n, double lam, void* loss, void* d_out, void* sums, hipStream_t s) {
+                             int n, double lam, void* loss, void* d_out, void* sums, FixedSum* rest, hipStream_t s) {
     switch (dt) {
-        case H4D_F32: return smooth_t<float>(g, table, xyzt, eps, n, lam, loss, d_out, sums, s);
-        case H4D_BF16: return smooth_t<bf16_t>(g, table, xyzt, eps, n, lam, loss, d_out, sums, s);
-        case H4D_F64: return smooth_t<double>(g, table, xyzt, eps, n, lam, loss, d_out, sums, s);
+        case H4D_F32: return smooth_t<float>(g, table, xyzt, eps, n, lam, loss, d_out, sums, rest, s);
+        case H4D_BF16: return smooth_t<bf16_t>(g, table, xyzt, eps, n, lam, loss, d_out, sums, rest, s);
+        case H4D_F64: return smooth_t<double>(g, table, xyzt, eps, n, lam, loss, d_out, sums, rest, s);
     }
     return hipErrorInvalidValue;
 }
