@@ -767,8 +767,8 @@ static h4d_status create_plan(h4d_batched_plan** out, const h4d_scene_desc* scen
             return bail(plan_hip(e, "plan tiles"));
     }
     // decoder spans
-    p->fwd_blocks = mlp_blocks_for(dt, false, queries);
-    p->bwd_blocks = std::max(mlp_blocks_for(dt, true, queries), n_scenes);
+    p->fwd_blocks = mlp_blocks_for(dt, m->in, false, queries);
+    p->bwd_blocks = std::max(mlp_blocks_for(dt, m->in, true, queries), n_scenes);
     p->fwd_blocks = std::max(p->fwd_blocks, n_scenes);
     split_blocks(*p, p->fwd, p->fwd_blocks);
     split_blocks(*p, p->bwd, p->bwd_blocks);

@@ -979,7 +979,19 @@ constexpr int kMlpF64MaxBlocks = 64;   // the FP64 check path spills to scratch:
 // us with 8 / 4 / 2 / 1 tiles: 8 features 49.5 / 46 / 45.2 / 46.6, 32 features 80 / 75 / 75 /
 // 76; 16000 queries 62.9 / 60 / 58.0 / 57.4 and 104 / 101 / 100 / 100; from 8 * 256 tiles on
 // there is no difference.
+//
+// In BF16 an iteration is so short that the partial rows count: above some 50 workgroups of
+// two tiles (125 with 64 features, whose iterations are longer) four are better, above some
+// 100 of four eight, until the cap fills all CUs.  The backward of 8 features in us with 8 /
+// 4 / 2 tiles: 1000 queries 12.0 / 11.2 / 11.7, 2000 12.3 / 11.8 / 12.9, 6000 13.6 / 12.9 /
+// 15.3, 8000 14.1 / 14.3 / 16.5, 12000 14.0 / 15.4 / 15.3, 16000 15.4 / 16.7 / 15.4.
 constexpr int kMlpBwdTiles = 2, kMlpBwdTilesLeast = 8;
+static int mlp_bwd_tiles(h4d_dtype dt, int in, int n) {
+    const int ntiles = (n + 15) / 16;
+    if (dt == H4D_F64) return kMlpBwdTilesLeast;
+    if (dt != H4D_BF16 || ntiles <= (in == 64 ? 250 : 96) || ntiles >= 1000) return kMlpBwdTiles;
+    return ntiles <= 384 ? 4 : 8;
+}
 
 // One workgroup per `each` tiles of 16 queries, at most `cap`.
 static int mlp_blocks(int n, int each, int cap) {
@@ -994,8 +1006,10 @@ static size_t lds_forward(int out) {
     return ((size_t)Tab<Pol, IN>::FWD * sizeof(typename Pol::FE) + 15) / 16 * 16;
 }
 
+// For the most workgroups that any n up to this one runs with.
 size_t mlp_workspace_bytes(h4d_dtype dt, int in, int out, int n) {
-    return mlp_partial_bytes(dt, in, out, mlp_blocks_for(dt, true, n), 1);
+    const int blocks = dt == H4D_F64 ? mlp_blocks_for(dt, in, true, n) : mlp_blocks(n, kMlpBwdTiles, kMlpBwdMaxBlocks);
+    return mlp_partial_bytes(dt, in, out, blocks, 1);
 }
 
 static int mlp_blocks_least(h4d_dtype dt, int n) {
@@ -1070,12 +1084,10 @@ static hipError_t backward_p(int in, const MlpBatch& b, int blocks, int out, dou
 
 static int log2i(int F) { return F == 1 ? 0 : F == 2 ? 1 : F == 4 ? 2 : 3; }
 
-int mlp_blocks_for(h4d_dtype dt, bool backward, int64_t queries) {
+int mlp_blocks_for(h4d_dtype dt, int in, bool backward, int64_t queries) {
     const int cap = dt == H4D_F64 ? kMlpF64MaxBlocks : backward ? kMlpBwdMaxBlocks : kMlpFwdMaxBlocks;
-    return mlp_blocks((int)(queries < 2147483647 ? queries : 2147483647), !backward             ? 4
-                                                                                : dt == H4D_F64 ? kMlpBwdTilesLeast
-                                                                                                : kMlpBwdTiles,
-                      cap);
+    const int n = (int)(queries < 2147483632 ? queries : 2147483632);
+    return mlp_blocks(n, backward ? mlp_bwd_tiles(dt, in, n) : 4, cap);
 }
 
 size_t mlp_partial_bytes(h4d_dtype dt, int in, int out, int blocks, int) {
@@ -1108,7 +1120,7 @@ static MlpBatch single(const void* params, const void* feat, void* delta, const 
 
 hipError_t launch_mlp_forward(h4d_dtype dt, int in, int out, const void* params, const void* feat, int F,
                               int64_t lstride, int64_t qstride, int n, void* delta, hipStream_t s) {
-    const int blocks = mlp_blocks_for(dt, false, n);
+    const int blocks = mlp_blocks_for(dt, in, false, n);
     const MlpBatch b = single(params, feat, delta, nullptr, nullptr, nullptr, F, lstride, qstride, n, blocks);
     return launch_mlp_forward_batch(dt, in, out, b, blocks, s);
 }
@@ -1119,7 +1131,7 @@ hipError_t launch_mlp_backward(h4d_dtype dt, int in, int out, const void* params
                                void* d_params, void* ws, size_t ws_bytes, hipStream_t s, bool overwrite,
                                int32_t* nonfinite) {
     if (dlstride != lstride || dqstride != qstride) return hipErrorInvalidValue;  // d_feat shares feat's layout
-    int blocks = mlp_blocks_for(dt, true, n);
+    int blocks = mlp_blocks_for(dt, in, true, n);
     if (mlp_partial_bytes(dt, in, out, blocks, 1) > ws_bytes) blocks = mlp_blocks_least(dt, n);
     MlpBatch b = single(params, feat, nullptr, d_out, d_feat, d_params, F, lstride, qstride, n, blocks);
     b.overwrite = overwrite ? 1 : 0;

@@ -396,3 +396,37 @@ def test_mlp_backward_grids_f32(n_in, n):
                                  _lib.QUERY_MAJOR | _lib.GRAD_OVERWRITE)
         scaled_close(host(d_feat), rf, sf, RTOL_GRAD, f"d_feat {wb}")
         scaled_close(host(d_params), rp, sp, RTOL_GRAD, f"d_params {wb}")
+
+
+# The BF16 grids: two, four and eight tiles per workgroup, and two again at the cap, at the
+# sizes where the rule changes.  Each value is the sum of as many terms whatever the grid, so
+# the gradients agree with those of a workspace that holds eight tiles' rows only.
+@pytest.mark.parametrize("n", [1, 1536, 1537, 4000, 4001, 6144, 6145, 15984, 15985])
+@pytest.mark.parametrize("n_in", [8, 64])
+def test_mlp_backward_grids_bf16(n_in, n):
+    import torch
+    params, f, g = decoder_case(n_in, n, 98)
+    m = _lib.mlp_shape(n_in)
+    P = O.param_count(n_in)
+    sf, sp = mlp_backward_scale(params, f, g)
+    least = (least_rows(n) * P * 4 + 255) // 256 * 256
+    full = _lib.deform_mlp_workspace_bytes(m, _lib.BF16, n)
+    out = []
+    for wb in (full, least):
+        ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
+        d_feat, d_params = nan_tensor((n, n_in), torch.float32), nan_tensor((P,), torch.float32)
+        _lib.deform_mlp_backward(m, _lib.BF16, bf16_dev(params), dev(f), n, dev(g), 1.0, 1.0, d_feat, d_params, ws, wb,
+                                 _lib.QUERY_MAJOR | _lib.GRAD_OVERWRITE)
+        out.append((host(d_feat), host(d_params)))
+    assert np.array_equal(out[0][0], out[1][0])
+    scaled_close(out[0][1], out[1][1], sp, RTOL_GRAD, "d_params of the two grids")
+    rf, rp = O.mlp_backward(params, f, g)
+    scaled_close(out[0][0], rf, sf, RTOL_BF16, "d_feat")
+    scaled_close(out[0][1], rp, sp, RTOL_BF16, "d_params")
+
+
+@pytest.mark.parametrize("dt", [_lib.F32, _lib.BF16, _lib.F64], ids=["f32", "bf16", "f64"])
+def test_mlp_workspace_never_shrinks(dt):
+    m = _lib.mlp_shape(32)
+    sizes = [_lib.deform_mlp_workspace_bytes(m, dt, n) for n in range(1, 40_000, 13)]
+    assert sizes == sorted(sizes)
