@@ -37,12 +37,14 @@ class DeformField:
         return lo
 
 
-def _written(shape, count, dtype, device) -> torch.Tensor:
-    """A tensor whose first `count` elements the caller writes; any others are zero."""
+def _gradient(shape, count, dtype, device):
+    """A gradient tensor of `shape` and the layout flag of the call that gives its first
+    `count` elements: written where it has them, else (a table cut off after the rows that
+    the queries reach) added to zeros, which touches reached rows only."""
     t = torch.empty(shape, dtype=dtype, device=device)
-    if t.numel() > count:
+    if t.numel() != count:
         t.zero_()
-    return t
+    return t, _lib.GRAD_OVERWRITE if t.numel() >= count else 0
 
 
 class Hash4DDeform(torch.autograd.Function):
@@ -84,18 +86,19 @@ class Hash4DDeform(torch.autograd.Function):
             # are written, not added to, so nothing is cleared first (11 us of fills, and
             # the scatter's reads of what they wrote, for a 30 MB table and 50k queries);
             # a table or parameter tensor with elements past the field's own keeps zeros there
-            LM, OW = _lib.LEVEL_MAJOR, _lib.LEVEL_MAJOR | _lib.GRAD_OVERWRITE
-            d_table = _written(ctx.table_shape, g.E * g.F, field.torch_dtype, dev)
-            d_params = _written(ctx.n_params, m.in_ * 64 + 64 + 64 * 64 + 64 + m.out * 65, field.torch_dtype, dev)
+            LM = _lib.LEVEL_MAJOR
+            d_table, ow_table = _gradient(ctx.table_shape, g.E * g.F, field.torch_dtype, dev)
+            d_params, ow_params = _gradient(ctx.n_params, m.in_ * 64 + 64 + 64 * 64 + 64 + m.out * 65,
+                                            field.torch_dtype, dev)
             d_feat = torch.empty((g.L, n, g.F), dtype=field.torch_dtype, device=dev)
             wb = _lib.deform_mlp_workspace_bytes(m, field.dtype, n)
             ws = torch.empty(max(wb, 1), dtype=torch.uint8, device=dev)
             _lib.deform_mlp_backward(m, field.dtype, p_used, feat, n, d_delta, S, 1.0 / S, d_feat, d_params, ws, wb,
-                                     OW, g.F)
+                                     LM | ow_params, g.F)
             grad_dt = _lib.F64 if field.dtype == _lib.F64 else _lib.F32
             wb = _lib.hash4d_encode_backward_workspace_bytes(g, n)
             ws = torch.empty(max(wb, 1), dtype=torch.uint8, device=dev)
-            _lib.hash4d_encode_backward(g, grad_dt, xyzt, n, d_feat, 1.0, d_table, ws, wb, OW)
+            _lib.hash4d_encode_backward(g, grad_dt, xyzt, n, d_feat, 1.0, d_table, ws, wb, LM | ow_table)
             d_xyzt = torch.zeros((n, 4), dtype=field.torch_dtype, device=dev)
             wb = _lib.hash4d_encode_backward_input_workspace_bytes(g, field.dtype, n)
             ws = torch.empty(max(wb, 1), dtype=torch.uint8, device=dev) if wb else None

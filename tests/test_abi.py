@@ -275,3 +275,12 @@ def test_hash3d_encode_validates_without_launching():
     g.offset[2] += 1
     assert lib.hash3d_encode(gp, 0, fake, fake, 3, 4, 0, fake, None) == -1       # corrupted grid
     assert "inconsistent" in _lib.last_error()
+
+
+def test_gradient_is_written_only_where_it_has_every_element():
+    # the scatter writes every row of its grid: only a tensor that holds them all is written
+    import torch
+    from paper_2507_19141_amd.autograd import _gradient
+    for numel, flag, zeros in ((12, _lib.GRAD_OVERWRITE, False), (13, _lib.GRAD_OVERWRITE, True), (11, 0, True)):
+        t, f = _gradient((numel,), 12, torch.float32, "cpu")
+        assert f == flag and (not zeros or not t.any())
