@@ -381,7 +381,8 @@ static h4d_status encode_backward_call(const h4d_grid* g, h4d_dtype grad_dt, con
         return hip_status(launch_zero_words(d_table, words, (hipStream_t)stream), where);
     }
     if (!d_feat || !d_table) return fail(H4D_EINVAL, "d_feat or d_table is NULL");
-    const size_t need = scatter_ws(g, n, false, !static_ws);
+    size_t need = scatter_ws(g, n);
+    if (!static_ws && ws_bytes < need) need = scatter_ws(g, n, false, true);
     if (static_ws) {
         ws_bytes = kStaticScratchBytes;
         if (need > kStaticScratchBytes)
@@ -500,7 +501,8 @@ h4d_status smoothness_reg(const h4d_grid* g, h4d_dtype table_dt, const void* tab
     if ((st = check_table_alignment(table, table_dt, g->F))) return st;
     if (((uintptr_t)eps) & 15u) return fail(H4D_EINVAL, "eps is not 16-byte aligned");
     if (n * (int64_t)g->L * g->F > kMaxN) return fail(H4D_EINVAL, "n L F exceeds 2^31-1 features");
-    const size_t need = smooth_ws(g, table_dt, n, true);
+    size_t need = smooth_ws(g, table_dt, n);
+    if (ws_bytes < need) need = smooth_ws(g, table_dt, n, true);
     if (d_table && (!workspace || ws_bytes < need))
         return fail(H4D_EINVAL, "workspace of %zu bytes, %zu needed", workspace ? ws_bytes : (size_t)0, need);
     if (workspace && (((uintptr_t)workspace) & 15u)) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");
@@ -549,7 +551,8 @@ h4d_status hash4d_encode_backward_smooth(const h4d_grid* g, h4d_dtype table_dt, 
     if ((st = check_table_alignment(table, table_dt, g->F))) return st;
     if (((uintptr_t)eps) & 15u) return fail(H4D_EINVAL, "eps is not 16-byte aligned");
     if (n * (int64_t)g->L * g->F > kMaxN) return fail(H4D_EINVAL, "n L F exceeds 2^31-1 features");
-    const size_t need = smooth_ws(g, table_dt, n, true);
+    size_t need = smooth_ws(g, table_dt, n);
+    if (ws_bytes < need) need = smooth_ws(g, table_dt, n, true);
     if (!workspace || ws_bytes < need)
         return fail(H4D_EINVAL, "workspace of %zu bytes, %zu needed", workspace ? ws_bytes : (size_t)0, need);
     if (((uintptr_t)workspace) & 15u) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");
@@ -848,11 +851,12 @@ h4d_status hash4d_deform_backward(const h4d_grid* g, const h4d_mlp* m, h4d_dtype
     if ((st = check_deform(g, m, dt, xyzt, n))) return st;
     if (n == 0) return H4D_OK;
     if (!params || !feat || !d_delta || !d_table || !d_params) return fail(H4D_EINVAL, "NULL data pointer");
-    const size_t need = deform_ws(g, m, dt, n, true);
+    const size_t full = deform_ws(g, m, dt, n);
+    const bool least = ws_bytes < full;
+    const size_t need = least ? deform_ws(g, m, dt, n, true) : full;
     if (!workspace || ws_bytes < need)
         return fail(H4D_EINVAL, "workspace of %zu bytes, %zu needed", workspace ? ws_bytes : (size_t)0, need);
     if (((uintptr_t)workspace) & 15u) return fail(H4D_EINVAL, "workspace is not 16-byte aligned");
-    const bool least = ws_bytes < deform_ws(g, m, dt, n);
     const DevGrid d = to_device(*g);
     const hipStream_t s = (hipStream_t)stream;
     const int64_t ls = n * g->F, qs = g->F;

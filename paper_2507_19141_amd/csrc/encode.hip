@@ -533,8 +533,8 @@ static ScatterPass scatter_pass(const DevGrid& g, const int64_t* level_rows, int
     return w;
 }
 
-// How a workspace of `avail` bytes is used: one pass over all levels if their lists fit,
-// else passes over runs of levels, one after the other in the same memory.  The runs have
+// How a workspace of `avail` bytes is used that does not hold the lists of all levels: by
+// passes over runs of levels, one after the other in the same memory.  The runs have
 // equal numbers of levels or about equal bytes, whichever fits with fewer rounds of
 // workgroups over the CUs (a tile fills one): 16 levels of 2^14 rows at 200k queries take
 // 173 us in passes of 256 tiles, 217 us where one has 11 levels.  Masks on the levels that
@@ -551,10 +551,8 @@ static ScatterPlan scatter_plan(const DevGrid& g, const int64_t* level_rows, int
                                 size_t avail) {
     ScatterPlan best;
     memset(&best, 0, sizeof best);
-    best.passes = 1;
-    best.listed = best.levels[0] = level_bits(g.L);
+    best.listed = level_bits(g.L);
     auto pass = [&](uint32_t levels) { return scatter_pass(g, level_rows, n, gbytes, pair, levels, best.listed); };
-    if (pass(best.listed).total <= avail) return best;
     size_t level[H4D_MAX_LEVELS], total = 0;
     for (int l = 0; l < g.L; ++l) {
         if (pass(1u << l).total > avail) best.listed &= ~(1u << l);
@@ -660,11 +658,16 @@ static hipError_t tiled_g(const DevGrid& g, const int64_t* level_rows, const flo
                           const void* src, int64_t ls, int64_t qs, double scale, void* d_table, void* ws,
                           size_t ws_bytes, bool overwrite, const MainGradArg& main, int32_t* nonfinite,
                           const FixedSum& sum, hipStream_t s) {
-    const ScatterPlan plan = scatter_plan(g, level_rows, n, (int)sizeof(G), PAIR, ws_bytes);
+    const uint32_t all = level_bits(g.L);
+    ScatterPass w = scatter_pass(g, level_rows, n, (int)sizeof(G), PAIR, all, all);
+    const bool whole = w.total <= ws_bytes;
+    const ScatterPlan plan = whole ? ScatterPlan{1, all, {all}}
+                                   : scatter_plan(g, level_rows, n, (int)sizeof(G), PAIR, ws_bytes);
+    if (plan.passes == 0) return hipErrorInvalidValue;  // less than the least workspace
     for (int i = 0; i < plan.passes; ++i) {
         const uint32_t levels = plan.levels[i];
         if (!levels) continue;
-        const ScatterPass w = scatter_pass(g, level_rows, n, (int)sizeof(G), PAIR, levels, plan.listed);
+        if (!whole) w = scatter_pass(g, level_rows, n, (int)sizeof(G), PAIR, levels, plan.listed);
         const TileMap& tm = w.tm;
         char* at = static_cast<char*>(ws);
         const ScatterBufs b{reinterpret_cast<uint16_t*>(at), reinterpret_cast<uint32_t*>(at + w.heads),
