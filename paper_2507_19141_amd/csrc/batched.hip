@@ -729,7 +729,8 @@ static h4d_status create_plan(h4d_batched_plan** out, const h4d_scene_desc* scen
     // each to the XCD with the least work so far.  A level costs its queries, and up to
     // twice that where it is coarse: its updates crowd into few rows, whose swaps then
     // fail and are tried again (3.2M queries at four timestamps: 1.35 to 1.8 times the
-    // finest levels' time for N_s = 16 to 42, 1.2 times for 150).
+    // finest levels' time for N_s = 16 to 42, 1.2 times for 150).  Without that weight a step
+    // of five scenes takes 10.98 ms, with it 10.75.
     {
         struct Level {
             int scene, level;

@@ -25,9 +25,9 @@ __device__ __forceinline__ uint32_t motion_key(const float* __restrict__ dp, int
 }
 
 // A pass reads 12 bytes per Gaussian, so the launches were what the split took its time
-// for: 11 of them, 40 us for 200k Gaussians.  Now each kernel starts with the reduction
+// for: 11 of them, 42 us for 200k Gaussians.  Now each kernel starts with the reduction
 // that its predecessor left, every workgroup for itself (the pick of a digit from 256
-// bins; the sums of the block counts): 7 launches, 29 us.  Letting the workgroup that
+// bins; the sums of the block counts): 7 launches, 28 us.  Letting the workgroup that
 // ends a pass last pick its digit took 8.5 us per pass, against 4.0 + 2.3 in two launches:
 // every workgroup's release writes its L2 back.
 

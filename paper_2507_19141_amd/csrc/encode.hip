@@ -1,6 +1,6 @@
 // 4D hash encoder forward and backward kernels (DASH Section 4.2, Eqs. 8-9).
 //
-// Forward: one thread per (query, level).  Work items (level, 256 queries) are
+// Forward: one thread per (query, level).  Work items (level, 64 queries) are
 // placed on XCDs level by level (xcd_item), so each XCD's L2 holds mostly one
 // level's slice of the table (4 MiB FP32 / 2 MiB BF16 for a 2^19-row, F = 2 level)
 // instead of every XCD streaming the whole table through its L2.
