@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kDecBlock) void k_split_write(const float* __restri
 
 // Small splits in one launch of one workgroup: every Gaussian's key stays in a register of
 // its thread (up to 16 of them), so nothing but the outputs leaves the CU.  1000 Gaussians
-// 44 -> 16 us, 16000 45 -> 31 us, a microsecond more per 1000: one CU's loads and LDS
+// 40 -> 10 us, 16000 38 -> 27 us, a microsecond more per 1000: one CU's loads and LDS
 // atomics.  Past 16 keys a thread would read them again for each digit, and near 30k it
 // would take as long as the launches.
 constexpr int kSmallBlock = 1024, kSmallRuns = 16;
