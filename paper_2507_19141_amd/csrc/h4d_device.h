@@ -280,12 +280,22 @@ __device__ __forceinline__ void gather_pairs(const TT* __restrict__ table, uint3
     }
 }
 
-// Quadrilinear weights along the axes, and of the corners of x-pair p: the products of
-// level_weights in its order.
+// Weights of the corners of x-pair p.  All 16 are formed at once (level_weights) where the
+// loop over the pairs is unrolled; PER_PAIR: where it is asked for, from the weights along
+// the axes, the same products in the same order.
+template <typename W, bool PER_PAIR>
+struct CornerWeights {
+    W w[16];
+    __device__ __forceinline__ explicit CornerWeights(const Cell& c) { level_weights<W>(c, w); }
+    __device__ __forceinline__ void pair(int p, W& lo, W& hi) const {
+        lo = w[2 * p];
+        hi = w[2 * p + 1];
+    }
+};
 template <typename W>
-struct AxisWeights {
+struct CornerWeights<W, true> {
     W x[2], y[2], z[2], t[2];
-    __device__ __forceinline__ explicit AxisWeights(const Cell& c)
+    __device__ __forceinline__ explicit CornerWeights(const Cell& c)
         : x{W(1) - W(c.fx), W(c.fx)}, y{W(1) - W(c.fy), W(c.fy)}, z{W(1) - W(c.fz), W(c.fz)}, t{W(1) - W(c.ft), W(c.ft)} {}
     __device__ __forceinline__ void pair(int p, W& lo, W& hi) const {
         const W wy = p & 1 ? y[1] : y[0], wz = p & 2 ? z[1] : z[0], wt = p & 4 ? t[1] : t[0];
@@ -342,7 +352,7 @@ __device__ __forceinline__ void pair_rows_xy(const DevGrid& g, int l, const Cell
 // rolled.  200k queries, 8 levels of 2^18 rows, all at once -> in groups: smoothness pass
 // FP32 408 -> 346 us, BF16 219 -> 150, input gradient FP32 223 -> 200, encode 192 -> 187.
 template <typename TT, int F>
-constexpr int kPairGroup = F < 8 ? 8 : sizeof(TT) == 4 ? 2 : 4;
+constexpr int kPairGroup = F < 8 || sizeof(TT) == 8 ? 8 : sizeof(TT) == 4 ? 2 : 4;
 
 template <typename TT, int F, bool WIDE, typename Each>
 __device__ __forceinline__ void each_pair(const DevGrid& g, int l, const TT* __restrict__ table, const Cell& c, Each each) {
@@ -373,7 +383,7 @@ __device__ __forceinline__ void each_pair(const DevGrid& g, int l, const TT* __r
 template <typename TT, int F, bool WIDE, typename A>
 __device__ __forceinline__ void interpolate(const DevGrid& g, int l, const TT* __restrict__ table, const Cell& c,
                                             A (&acc)[F]) {
-    const AxisWeights<A> w(c);
+    const CornerWeights<A, (kPairGroup<TT, F> < 8)> w(c);
 #pragma unroll
     for (int f = 0; f < F; ++f) acc[f] = A(0);
     each_pair<TT, F, WIDE>(g, l, table, c, [&](int p, const A (&lo)[F], const A (&hi)[F]) {

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth(DevGrid g, const TT* __
         const Cell c0 = level_cell(g, l, x);
         const Cell c1 = level_cell(g, l, xp);
         const bool same = c0.ix == c1.ix && c0.iy == c1.iy && c0.iz == c1.iz && c0.it == c1.it;
-        const AxisWeights<A> w0(c0), w1(c1);
+        const CornerWeights<A, (kPairGroup<TT, F> < 8)> w0(c0), w1(c1);
         A d[F], a0[F];
 #pragma unroll
         for (int f = 0; f < F; ++f) d[f] = a0[f] = A(0);
